@@ -37,8 +37,10 @@
  *     reentrant, and calls on different streams with disjoint buffers may
  *     run concurrently.
  *   - Fast (matrix-core) paths need 16-byte aligned pointers and Cg, Kg that
- *     are multiples of 8; other valid shapes run on slower direct kernels
- *     with identical semantics.
+ *     are multiples of 8, or one group: other channel counts are then padded
+ *     with zero channels in the workspace (operands that are copied for it
+ *     may have any alignment).  Other valid shapes run on slower direct
+ *     kernels with identical semantics.
  *   - Depthwise convolution (groups == c == k, one channel per group, the
  *     MobileNet / EfficientNet layers trained with the paper's framework)
  *     with c a multiple of 8, a square 3x3, 5x5 or 7x7 filter and 16-byte
@@ -121,7 +123,12 @@ nnconv_status nnconv_output_dims(const nnconv_desc *desc, int32_t *p, int32_t *q
 /* Bytes of device workspace that nnconv_fwd / nnconv_dgrad / nnconv_wgrad
  * need for this geometry (0 is a valid answer).  Depends only on desc and
  * pass.  Workspace contents need not be initialised and are garbage after
- * the call. */
+ * the call.  With one group and a channel count that is not a multiple of 8
+ * the answer covers channel-last copies with padded channels for the
+ * matrix-core kernels; such a call also accepts less, down to nothing
+ * (forward, backward-data) or the direct kernel's fp32 partials
+ * (backward-weight: up to 64 of dw), and then runs on the slow direct
+ * kernels. */
 nnconv_status nnconv_workspace_size(const nnconv_desc *desc, nnconv_pass pass, size_t *bytes);
 
 /* Forward pass (definition above): y = alpha * conv(x, w).
@@ -207,11 +214,12 @@ nnconv_status nnconv_wgrad(const nnconv_desc *desc, const void *x, const void *d
  * hipMalloc: nnconv_wgrad with the workspace taken from a library-owned
  * scratch array of NNCONV_NOALLOC_WS_BYTES (64 MiB) instead of an argument.
  * Same arguments (minus ws, ws_bytes), semantics, results (bitwise equal to
- * nnconv_wgrad's) and errors, plus NNCONV_ERR_WORKSPACE, returned before
+ * nnconv_wgrad's with a workspace of the same size) and errors, plus NNCONV_ERR_WORKSPACE, returned before
  * anything is queued, when the geometry needs more workspace than the
  * scratch holds (nnconv_workspace_size(desc, NNCONV_WGRAD) >
- * NNCONV_NOALLOC_WS_BYTES; every channel-last ResNet-50 layer at batch 256
- * fits).
+ * NNCONV_NOALLOC_WS_BYTES, for channel counts that are multiples of 8; others
+ * run on the direct kernels then; every channel-last ResNet-50 layer at batch
+ * 256 fits).
  *   - The scratch is a device array of the library: every GPU the library
  *     runs on holds one copy from the first call on it (made with that GPU
  *     current, outside graph capture) until the process ends.  The call

@@ -166,6 +166,13 @@ hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, 
 // 16-bit transforms
 // ---------------------------------------------------------------------------
 
+// A batched transpose; source rows are src_ld elements apart (>= cols).
+struct T16 {
+    const uint16_t *src;
+    uint16_t *dst;
+    int64_t rows, cols, src_ld, dst_ld, tiles_c, tiles_r;
+};
+
 // dst[b][cc][rr] = rr < rows ? src[b][rr][cc] : 0, through a 64x64 LDS tile
 // (reads coalesced along cc, writes coalesced along rr).
 //
@@ -174,20 +181,19 @@ hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, 
 // One 64x64 tile (index t) of a batched transpose with 2-byte accesses (any
 // sizes and alignment).
 template <bool SCAN>
-__device__ __forceinline__ void transpose16_tile(const uint16_t *src, uint16_t *dst, int64_t rows,
-                                                 int64_t cols, int64_t dst_ld, int64_t tiles_c,
-                                                 int64_t tiles_r, int64_t t, uint16_t (*tile)[65],
+__device__ __forceinline__ void transpose16_tile(const T16 &p, int64_t t, uint16_t (*tile)[65],
                                                  uint32_t expmask, int32_t *flags) {
-    const int64_t b = t / (tiles_c * tiles_r);
-    const int64_t rem = t - b * tiles_c * tiles_r;
-    const int64_t tr = rem / tiles_c, tc = rem - (rem / tiles_c) * tiles_c;
+    const int64_t rows = p.rows, cols = p.cols, dst_ld = p.dst_ld;
+    const int64_t b = t / (p.tiles_c * p.tiles_r);
+    const int64_t rem = t - b * p.tiles_c * p.tiles_r;
+    const int64_t tr = rem / p.tiles_c, tc = rem - (rem / p.tiles_c) * p.tiles_c;
     const int64_t r0 = tr * 64, c0 = tc * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const uint16_t *s = src + b * rows * cols;
+    const uint16_t *s = p.src + b * rows * p.src_ld;
     int bad = 0;
     for (int i = ty; i < 64; i += 4) {
         const int64_t rr = r0 + i, cc = c0 + tx;
-        const uint16_t v = (rr < rows && cc < cols) ? s[rr * cols + cc] : (uint16_t)0;
+        const uint16_t v = (rr < rows && cc < cols) ? s[rr * p.src_ld + cc] : (uint16_t)0;
         tile[i][tx] = v;
         if constexpr (SCAN) bad |= (v & expmask) == expmask;
     }
@@ -197,7 +203,7 @@ __device__ __forceinline__ void transpose16_tile(const uint16_t *src, uint16_t *
     } else {
         __syncthreads();
     }
-    uint16_t *d = dst + b * cols * dst_ld;
+    uint16_t *d = p.dst + b * cols * dst_ld;
     for (int i = ty; i < 64; i += 4) {
         const int64_t cc = c0 + i, rr = r0 + tx;
         if (cc < cols && rr < dst_ld) d[cc * dst_ld + rr] = tile[tx][i];
@@ -205,23 +211,13 @@ __device__ __forceinline__ void transpose16_tile(const uint16_t *src, uint16_t *
 }
 
 template <bool SCAN>
-__global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t *__restrict__ src,
-                                                          uint16_t *__restrict__ dst, int64_t rows,
-                                                          int64_t cols, int64_t dst_ld,
-                                                          int64_t tiles_c, int64_t tiles_r,
-                                                          uint32_t expmask, int32_t *flags) {
+__global__ __launch_bounds__(256) void transpose16_kernel(const T16 p, uint32_t expmask,
+                                                          int32_t *flags) {
     __shared__ uint16_t tile[64][65];
-    transpose16_tile<SCAN>(src, dst, rows, cols, dst_ld, tiles_c, tiles_r, blockIdx.x, tile,
-                           expmask, flags);
+    transpose16_tile<SCAN>(p, blockIdx.x, tile, expmask, flags);
 }
 
 // One 64x64 tile (index t) of a batched transpose, 16-byte accesses.
-struct T16 {
-    const uint16_t *src;
-    uint16_t *dst;
-    int64_t rows, cols, dst_ld, tiles_c, tiles_r;
-};
-
 template <bool SCAN>
 __device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, uint16_t *tile,
                                                      uint32_t expmask, int32_t *flags) {
@@ -229,7 +225,7 @@ __device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, ui
     const int64_t rem = t - b * p.tiles_c * p.tiles_r;
     const int64_t tr = rem / p.tiles_c, tc = rem - (rem / p.tiles_c) * p.tiles_c;
     const int64_t r0 = tr * 64, c0 = tc * 64;
-    const uint16_t *s = p.src + b * p.rows * p.cols;
+    const uint16_t *s = p.src + b * p.rows * p.src_ld;
     int bad = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -237,7 +233,7 @@ __device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, ui
         const int row = id >> 3, cc = (id & 7) * 8;
         const int64_t rr = r0 + row, col = c0 + cc;
         u32x4 v = u32x4{};
-        if (rr < p.rows && col < p.cols) v = *(const u32x4 *)(s + rr * p.cols + col);
+        if (rr < p.rows && col < p.cols) v = *(const u32x4 *)(s + rr * p.src_ld + col);
         *(u32x4 *)(&tile[row * 64 + (((cc >> 3) ^ ((row >> 3) & 7)) << 3)]) = v;
         if constexpr (SCAN) {
 #pragma unroll
@@ -270,9 +266,9 @@ __device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, ui
     }
 }
 
-// Same transpose with 16-byte accesses on both sides (cols, dst_ld and rows
+// Same transpose with 16-byte accesses on both sides (src_ld, dst_ld and rows
 // multiples of 8, 16-byte aligned buffers): a 64x64 tile is read as 8-element
-// row chunks, and each output chunk gathers 8 consecutive rows of one column
+// row chunks (the last one of a row may hold padding columns), and each output chunk gathers 8 consecutive rows of one column
 // from LDS.  The gather of a wave touches rows 8 apart, which share banks
 // for any row pitch that keeps chunks 16-byte aligned, so chunk c of row r
 // is stored at chunk c ^ ((r >> 3) & 7) instead of padding the rows.
@@ -297,8 +293,7 @@ __global__ __launch_bounds__(256) void transpose16_pair_kernel(const T16 p0, con
     if (t < n0 ? vec0 : vec1)
         transpose16_vec_tile<false>(p, u, &tile[0][0], 0u, nullptr);
     else
-        transpose16_tile<false>(p.src, p.dst, p.rows, p.cols, p.dst_ld, p.tiles_c, p.tiles_r, u,
-                                tile, 0u, nullptr);
+        transpose16_tile<false>(p, u, tile, 0u, nullptr);
 }
 
 // Block-diagonal super-group weights: dst[k][t][c'] (c' < sg, t < rs) is
@@ -339,45 +334,52 @@ int64_t transpose16_blocks(int64_t batch, int64_t cols, int64_t dst_ld) {
     return batch * ((cols + 63) / 64) * ((dst_ld + 63) / 64);
 }
 
-static T16 t16(const void *src, void *dst, int64_t rows, int64_t cols, int64_t dst_ld) {
+static T16 t16(const void *src, void *dst, int64_t rows, int64_t cols, int64_t src_ld,
+               int64_t dst_ld) {
     T16 p;
     p.src = (const uint16_t *)src;
     p.dst = (uint16_t *)dst;
     p.rows = rows;
     p.cols = cols;
+    p.src_ld = src_ld;
     p.dst_ld = dst_ld;
     p.tiles_c = (cols + 63) / 64;
     p.tiles_r = (dst_ld + 63) / 64;
     return p;
 }
 
-static bool t16_vec(const void *src, const void *dst, int64_t rows, int64_t cols,
+static bool t16_vec(const void *src, const void *dst, int64_t rows, int64_t src_ld,
                     int64_t dst_ld) {
-    return cols % 8 == 0 && dst_ld % 8 == 0 && rows % 8 == 0 && (uintptr_t)src % 16 == 0 &&
+    return src_ld % 8 == 0 && dst_ld % 8 == 0 && rows % 8 == 0 && (uintptr_t)src % 16 == 0 &&
            (uintptr_t)dst % 16 == 0;
 }
 
 template <bool SCAN>
 static hipError_t transpose16_go(const void *src, void *dst, int64_t batch, int64_t rows,
-                                 int64_t cols, int64_t dst_ld, uint32_t expmask, int32_t *flags,
-                                 hipStream_t st) {
+                                 int64_t cols, int64_t src_ld, int64_t dst_ld, uint32_t expmask,
+                                 int32_t *flags, hipStream_t st) {
     const int64_t tiles_c = (cols + 63) / 64, tiles_r = (dst_ld + 63) / 64;
     const int64_t nb = batch * tiles_c * tiles_r;
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
-    if (t16_vec(src, dst, rows, cols, dst_ld))
-        hipLaunchKernelGGL(transpose16_vec_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st,
-                           t16(src, dst, rows, cols, dst_ld), expmask, flags);
+    const T16 p = t16(src, dst, rows, cols, src_ld, dst_ld);
+    if (t16_vec(src, dst, rows, src_ld, dst_ld))
+        hipLaunchKernelGGL(transpose16_vec_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st, p,
+                           expmask, flags);
     else
-        hipLaunchKernelGGL(transpose16_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st,
-                           (const uint16_t *)src, (uint16_t *)dst, rows, cols, dst_ld, tiles_c,
-                           tiles_r, expmask, flags);
+        hipLaunchKernelGGL(transpose16_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st, p,
+                           expmask, flags);
     return hipGetLastError();
 }
 
 hipError_t launch_transpose16(const void *src, void *dst, int64_t batch, int64_t rows,
                               int64_t cols, int64_t dst_ld, hipStream_t st) {
-    return transpose16_go<false>(src, dst, batch, rows, cols, dst_ld, 0u, nullptr, st);
+    return transpose16_go<false>(src, dst, batch, rows, cols, cols, dst_ld, 0u, nullptr, st);
+}
+
+hipError_t launch_transpose16_ld(const void *src, void *dst, int64_t batch, int64_t rows,
+                                 int64_t cols, int64_t src_ld, int64_t dst_ld, hipStream_t st) {
+    return transpose16_go<false>(src, dst, batch, rows, cols, src_ld, dst_ld, 0u, nullptr, st);
 }
 
 hipError_t launch_transpose16_pair(const void *src0, void *dst0, int64_t batch0, int64_t rows0,
@@ -392,8 +394,8 @@ hipError_t launch_transpose16_pair(const void *src0, void *dst0, int64_t batch0,
         return launch_transpose16(src1, dst1, batch1, rows1, cols1, dst_ld1, st);
     }
     hipLaunchKernelGGL(transpose16_pair_kernel, dim3((uint32_t)(n0 + n1)), dim3(256), 0, st,
-                       t16(src0, dst0, rows0, cols0, dst_ld0),
-                       t16(src1, dst1, rows1, cols1, dst_ld1), n0,
+                       t16(src0, dst0, rows0, cols0, cols0, dst_ld0),
+                       t16(src1, dst1, rows1, cols1, cols1, dst_ld1), n0,
                        (int)t16_vec(src0, dst0, rows0, cols0, dst_ld0),
                        (int)t16_vec(src1, dst1, rows1, cols1, dst_ld1));
     return hipGetLastError();
@@ -402,7 +404,7 @@ hipError_t launch_transpose16_pair(const void *src0, void *dst0, int64_t batch0,
 hipError_t launch_transpose16_scan(const void *src, void *dst, int64_t batch, int64_t rows,
                                    int64_t cols, int64_t dst_ld, int dtype, int32_t *flags,
                                    hipStream_t st) {
-    return transpose16_go<true>(src, dst, batch, rows, cols, dst_ld, expmask16(dtype), flags,
+    return transpose16_go<true>(src, dst, batch, rows, cols, cols, dst_ld, expmask16(dtype), flags,
                                 st);
 }
 
@@ -594,6 +596,181 @@ hipError_t launch_pad_channels16(const void *src, void *dst, int64_t rows, int32
         hipLaunchKernelGGL(pad_channels16_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256),
                            0, st, (const uint16_t *)src, (uint16_t *)dst, total, c, c_pad);
     }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// channel padding of convolutions whose channel counts are not multiples of
+// 8 (the matrix-core kernels read 8-channel chunks)
+// ---------------------------------------------------------------------------
+
+// Channel-first images of at most 8 channels (RGB, grey) to channel-last
+// pixels of CP = 4 or 8 channels: dst[n][i][ch] = ch < c ? src[n][ch][i] : 0.
+// A 64x64 transpose tile would leave all but c of its 64 rows idle.  A thread
+// builds two neighbouring pixels from one 4-byte load per plane (PAIR: hw
+// even and src 4-byte aligned; otherwise 2-byte loads) and stores them whole.
+template <int CP, bool PAIR>
+__global__ __launch_bounds__(256) void interleave16_kernel(const uint16_t *__restrict__ src,
+                                                           uint16_t *__restrict__ dst, int64_t n,
+                                                           int32_t c, int64_t hw) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2;
+    if (i >= hw) return;
+    for (int64_t b = blockIdx.y; b < n; b += gridDim.y) {
+        const uint16_t *s = src + b * c * hw + i;
+        uint32_t lo[CP] = {}, hi[CP] = {};
+#pragma unroll
+        for (int ch = 0; ch < CP; ++ch) {
+            if (ch < c) {
+                if constexpr (PAIR) {
+                    const uint32_t v = *(const uint32_t *)(s + ch * hw);
+                    lo[ch] = v & 0xFFFFu;
+                    hi[ch] = v >> 16;
+                } else {
+                    lo[ch] = s[ch * hw];
+                    hi[ch] = i + 1 < hw ? s[ch * hw + 1] : (uint16_t)0;
+                }
+            }
+        }
+        uint16_t *d = dst + (b * hw + i) * CP;
+#pragma unroll
+        for (int ch = 0; ch < CP; ch += 4)
+            *(u32x2 *)(d + ch) = u32x2{lo[ch] | (lo[ch + 1] << 16), lo[ch + 2] | (lo[ch + 3] << 16)};
+        if (i + 1 < hw) {
+#pragma unroll
+            for (int ch = 0; ch < CP; ch += 4)
+                *(u32x2 *)(d + CP + ch) =
+                    u32x2{hi[ch] | (hi[ch + 1] << 16), hi[ch + 2] | (hi[ch + 3] << 16)};
+        }
+    }
+}
+
+hipError_t launch_interleave16(const void *src, void *dst, int64_t n, int32_t c, int64_t hw,
+                               int32_t c_pad, hipStream_t st) {
+    if (n <= 0 || hw <= 0) return hipSuccess;
+    if (c > c_pad || (c_pad != 4 && c_pad != 8) || (uintptr_t)dst % 16 != 0)
+        return hipErrorInvalidValue;
+    const int64_t nb = (hw + 511) / 512;
+    if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const dim3 grid((uint32_t)nb, (uint32_t)(n < 65535 ? n : 65535));
+    const bool pair = hw % 2 == 0 && (uintptr_t)src % 4 == 0;
+    const uint16_t *sp = (const uint16_t *)src;
+    uint16_t *dp = (uint16_t *)dst;
+    if (c_pad == 4 && pair)
+        hipLaunchKernelGGL((interleave16_kernel<4, true>), grid, dim3(256), 0, st, sp, dp, n, c, hw);
+    else if (c_pad == 4)
+        hipLaunchKernelGGL((interleave16_kernel<4, false>), grid, dim3(256), 0, st, sp, dp, n, c, hw);
+    else if (pair)
+        hipLaunchKernelGGL((interleave16_kernel<8, true>), grid, dim3(256), 0, st, sp, dp, n, c, hw);
+    else
+        hipLaunchKernelGGL((interleave16_kernel<8, false>), grid, dim3(256), 0, st, sp, dp, n, c, hw);
+    return hipGetLastError();
+}
+
+// Weights with both channel counts padded: dst is [k_pad][rs][c_pad]
+// (CKLAST = false, the forward operand) or [rs][c_pad][k_pad] (true, the
+// backward-data operand), zero where k >= K or c >= C; element (k, c, tap)
+// of src is at k * sk + c * sc + tap * st.  flags (may be null): whether any
+// of the block's 2048 elements is inf or NaN.
+template <bool KLAST>
+__global__ __launch_bounds__(256) void pad_weights16_kernel(
+    const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int32_t kn, int32_t cn,
+    int32_t k_pad, int32_t c_pad, int32_t rs, int64_t sk, int64_t sc, int64_t stap,
+    uint32_t expmask, int32_t *flags) {
+    const int64_t count = (int64_t)k_pad * c_pad * rs;
+    int bad = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int64_t e = (int64_t)blockIdx.x * 2048 + u * 256 + threadIdx.x;
+        if (e >= count) break;
+        int64_t k, c, t;
+        if constexpr (KLAST) {
+            const int64_t f = e / k_pad;
+            k = e - f * k_pad;
+            t = f / c_pad;
+            c = f - t * c_pad;
+        } else {
+            const int64_t f = e / c_pad;
+            c = e - f * c_pad;
+            k = f / rs;
+            t = f - k * rs;
+        }
+        const uint16_t v = k < kn && c < cn ? src[k * sk + c * sc + t * stap] : (uint16_t)0;
+        bad |= (v & expmask) == expmask;
+        dst[e] = v;
+    }
+    if (flags) {
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) flags[blockIdx.x] = bad;
+    }
+}
+
+int64_t pad_weights16_blocks(int64_t k_pad, int64_t c_pad, int64_t rs) {
+    return (k_pad * c_pad * rs + 2047) / 2048;
+}
+
+hipError_t launch_pad_weights16(const void *src, void *dst, int32_t k, int32_t c, int32_t k_pad,
+                                int32_t c_pad, int32_t rs, int kcrs, bool klast, int dtype,
+                                int32_t *flags, hipStream_t st) {
+    const int64_t nb = pad_weights16_blocks(k_pad, c_pad, rs);
+    if (nb <= 0) return hipSuccess;
+    if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const int64_t sk = (int64_t)c * rs, sc = kcrs ? rs : 1, stap = kcrs ? 1 : c;
+    const uint32_t em = expmask16(dtype);
+    if (klast)
+        hipLaunchKernelGGL(pad_weights16_kernel<true>, dim3((uint32_t)nb), dim3(256), 0, st,
+                           (const uint16_t *)src, (uint16_t *)dst, k, c, k_pad, c_pad, rs, sk, sc,
+                           stap, em, flags);
+    else
+        hipLaunchKernelGGL(pad_weights16_kernel<false>, dim3((uint32_t)nb), dim3(256), 0, st,
+                           (const uint16_t *)src, (uint16_t *)dst, k, c, k_pad, c_pad, rs, sk, sc,
+                           stap, em, flags);
+    return hipGetLastError();
+}
+
+// dst[rows][c] = src[rows][c_pad] without the padding channels.  A thread
+// stores 8 consecutive elements of the flat result (16 bytes when dst is
+// aligned for it), whatever rows they fall in.
+__global__ __launch_bounds__(256) void unpad_channels16_kernel(const uint16_t *__restrict__ src,
+                                                               uint16_t *__restrict__ dst,
+                                                               int64_t total, FastDiv div_c,
+                                                               int32_t c, int32_t c_pad, int vec) {
+    const int64_t e0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (e0 >= total) return;
+    const uint32_t row = fdiv((uint32_t)e0, div_c);
+    int32_t ch = (int32_t)((uint32_t)e0 - row * (uint32_t)c);
+    int64_t at = (int64_t)row * c_pad + ch;
+    uint16_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        v[u] = e0 + u < total ? src[at] : (uint16_t)0;
+        ++at;
+        if (++ch == c) {
+            ch = 0;
+            at += c_pad - c;
+        }
+    }
+    if (vec && e0 + 8 <= total) {
+        uint32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = (uint32_t)v[2 * u] | ((uint32_t)v[2 * u + 1] << 16);
+        *(u32x4 *)(dst + e0) = u32x4{w[0], w[1], w[2], w[3]};
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e0 + u < total) dst[e0 + u] = v[u];
+    }
+}
+
+// rows * c below 2^31 (the padded tensor is within the 2 GiB buffer range).
+hipError_t launch_unpad_channels16(const void *src, void *dst, int64_t rows, int32_t c,
+                                   int32_t c_pad, hipStream_t st) {
+    const int64_t total = rows * c;
+    if (total <= 0) return hipSuccess;
+    if (c > c_pad || total > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const int64_t nb = (total + 2047) / 2048;
+    hipLaunchKernelGGL(unpad_channels16_kernel, dim3((uint32_t)nb), dim3(256), 0, st,
+                       (const uint16_t *)src, (uint16_t *)dst, total, make_fastdiv((uint32_t)c), c,
+                       c_pad, (int)((uintptr_t)dst % 16 == 0));
     return hipGetLastError();
 }
 

@@ -255,17 +255,22 @@ hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, 
 // [K][rs][m] (kcrs = 0) or [K][m][rs] (kcrs = 1).
 hipError_t launch_expand_group_weights(const void *src, void *dst, int64_t k, int32_t rs, int32_t m,
                                        int32_t sg, int kcrs, hipStream_t st);
-// dw[k][t][c] (c < m; [K][m][R][S] when kcrs) = (accumulate ? dw : 0) +
-// inv_scale * sum_s ws[s][k][t][((k % sg) / m) * m + c]: the diagonal blocks
-// of the super-group weight-gradient partials.
-hipError_t launch_wgrad_reduce_diag(const float *ws, int32_t splits, int64_t k, int32_t rs,
-                                    int32_t m, int32_t sg, void *dw, int out_dtype,
-                                    float inv_scale, int accumulate, int32_t *flag, int kcrs,
-                                    hipStream_t st);
+// dw[k][t][c] (k < K, c < m; [K][m][R][S] when kcrs) = (accumulate ? dw : 0) +
+// inv_scale * sum_s ws[s][k][t][base(k) + c] over partials of pcount elements
+// whose taps are `pitch` elements apart: base(k) = ((k % pitch) / m) * m with
+// diag (the diagonal blocks of super-group weight-gradient partials), 0
+// without (partials of a convolution with padded channel counts).
+hipError_t launch_wgrad_reduce_pick(const float *ws, int32_t splits, int64_t pcount, int64_t k,
+                                    int32_t rs, int32_t m, int32_t pitch, bool diag, void *dw,
+                                    int out_dtype, float inv_scale, int accumulate, int32_t *flag,
+                                    int kcrs, hipStream_t st);
 
 // dst[b][cc][rr] = rr < rows ? src[b][rr][cc] : 0   for rr < dst_ld, cc < cols
 hipError_t launch_transpose16(const void *src, void *dst, int64_t batch, int64_t rows,
                               int64_t cols, int64_t dst_ld, hipStream_t st);
+// The same from source rows src_ld >= cols elements apart.
+hipError_t launch_transpose16_ld(const void *src, void *dst, int64_t batch, int64_t rows,
+                                 int64_t cols, int64_t src_ld, int64_t dst_ld, hipStream_t st);
 // launch_transpose16 that also stores, per workgroup b of the
 // transpose16_blocks(batch, cols, dst_ld) it launches, whether its tile of
 // src held an inf or NaN of the given operand dtype into flags[b].
@@ -294,6 +299,20 @@ hipError_t launch_dgrad_border(int dtype, const DirectParams &p, const void *dy,
 // dst[row][ch] = ch < c ? src[row][ch] : 0   for ch < c_pad
 hipError_t launch_pad_channels16(const void *src, void *dst, int64_t rows, int32_t c,
                                  int32_t c_pad, hipStream_t st);
+
+// dst[row][ch] = src[row][ch] for ch < c, source rows of c_pad channels
+hipError_t launch_unpad_channels16(const void *src, void *dst, int64_t rows, int32_t c,
+                                   int32_t c_pad, hipStream_t st);
+// dst[n][i][ch] = ch < c ? src[n][ch][i] : 0 for i < hw, ch < c_pad = 4 or 8
+hipError_t launch_interleave16(const void *src, void *dst, int64_t n, int32_t c, int64_t hw,
+                               int32_t c_pad, hipStream_t st);
+// [K][C][rs] (kcrs) or [K][rs][C] weights into [k_pad][rs][c_pad], or with
+// klast into [rs][c_pad][k_pad], zero-padded; flags (may be null): per block
+// of the pad_weights16_blocks(), whether it holds an inf or NaN.
+int64_t pad_weights16_blocks(int64_t k_pad, int64_t c_pad, int64_t rs);
+hipError_t launch_pad_weights16(const void *src, void *dst, int32_t k, int32_t c, int32_t k_pad,
+                                int32_t c_pad, int32_t rs, int kcrs, bool klast, int dtype,
+                                int32_t *flags, hipStream_t st);
 
 // Depthwise convolution (groups = C = K), channel-last, C % 8 == 0, square
 // 3x3 / 5x5 / 7x7 filters (depthwise.hip).  Weights are [C][R][S] (the

@@ -140,45 +140,54 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
     if (reduce_store<OUT>(sum, t, dw, inv_scale, accumulate, kcrs, cg, rs) && flag) *flag = 1;
 }
 
-// Grouped convolution run as super-groups of SG channels with block-diagonal
-// weights: the partials hold the whole [K][R*S][SG] super-group gradient;
-// this keeps only each output channel's own group (m channels starting at
-// ((k % SG) / m) * m) and finishes it like the other reductions.  One final
-// element (in [K][R][S][m] order) per thread, splits in increasing order.
-template <int OUT>
-__global__ __launch_bounds__(256) void wgrad_reduce_diag_kernel(
+// The same from partials that hold more than dw: grouped convolution run as
+// super-groups of `pitch` channels with block-diagonal weights (the partials
+// hold the whole [K][R*S][pitch] super-group gradient, of which each output
+// channel's own group is kept: m channels from ((k % pitch) / m) * m), and
+// convolutions run with zero-padded channel counts (the first m channels of
+// the first K filters are kept).  A workgroup's 256 threads are 256/L final
+// elements (in [K][R][S][m] order) x L split lanes, summed as in the vector
+// kernel above: with one thread per element summing every split in turn, the
+// 18,432 elements x 256 splits of a 256-channel layer of 8-channel groups ran
+// as 72 workgroups of one long chain of loads (17.5 us; 4.9 us with 16 lanes).
+template <int OUT, int L>
+__global__ __launch_bounds__(256) void wgrad_reduce_pick_kernel(
     const float *__restrict__ ws, int32_t splits, int64_t count, int64_t pcount, int32_t rs,
-    int32_t m, int32_t sg, void *dw, float inv_scale, int accumulate, int32_t *flag, int kcrs) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= count) return;
-    const int64_t per_k = (int64_t)rs * m;
-    const int64_t k = e / per_k;
-    const int64_t rem = e - k * per_k;
-    const int64_t tap = rem / m;
-    const int64_t c = rem - tap * m;
-    const int64_t pe = k * rs * sg + tap * sg + ((k % sg) / m) * m + c;
+    int32_t m, int32_t pitch, int diag, void *dw, float inv_scale, int accumulate, int32_t *flag,
+    int kcrs) {
+    constexpr int COLS = 256 / L;
+    const int col = threadIdx.x % COLS, sl = threadIdx.x / COLS;
+    const int64_t e = (int64_t)blockIdx.x * COLS + col;
     float sum = 0.f;
-    for (int sp = 0; sp < splits; ++sp) sum += ws[(int64_t)sp * pcount + pe];
+    if (e < count) {
+        const int64_t per_k = (int64_t)rs * m;
+        const int64_t k = e / per_k;
+        const int64_t rem = e - k * per_k;
+        const int64_t tap = rem / m;
+        const int64_t base = diag ? ((k % pitch) / m) * m : 0;
+        const float *src = ws + (int64_t)sl * pcount + (k * rs + tap) * pitch + base + rem - tap * m;
+        const int64_t step = (int64_t)L * pcount;
+        int sp = sl;
+        for (; sp + 3 * L < splits; sp += 4 * L, src += 4 * step) {
+            const float a = *src, b = src[step], c = src[2 * step], d = src[3 * step];
+            sum += a;
+            sum += b;
+            sum += c;
+            sum += d;
+        }
+        for (; sp < splits; sp += L, src += step) sum += *src;
+    }
+    if constexpr (L > 1) {
+        __shared__ float part[L][COLS];
+        part[sl][col] = sum;
+        __syncthreads();
+        if (sl != 0) return;
+        sum = part[0][col];
+#pragma unroll
+        for (int l = 1; l < L; ++l) sum += part[l][col];
+    }
+    if (e >= count) return;
     if (reduce_store<OUT>(sum, e, dw, inv_scale, accumulate, kcrs, m, rs) && flag) *flag = 1;
-}
-
-hipError_t launch_wgrad_reduce_diag(const float *ws, int32_t splits, int64_t k, int32_t rs,
-                                    int32_t m, int32_t sg, void *dw, int out_dtype,
-                                    float inv_scale, int accumulate, int32_t *flag, int kcrs,
-                                    hipStream_t st) {
-    const int64_t count = k * rs * m, pcount = k * rs * sg;
-    if (count <= 0) return hipSuccess;
-    const int64_t nb = (count + 255) / 256;
-    if (out_dtype == 2)
-        hipLaunchKernelGGL((wgrad_reduce_diag_kernel<2>), dim3((uint32_t)nb), dim3(256), 0, st, ws,
-                           splits, count, pcount, rs, m, sg, dw, inv_scale, accumulate, flag, kcrs);
-    else if (out_dtype == 0)
-        hipLaunchKernelGGL((wgrad_reduce_diag_kernel<0>), dim3((uint32_t)nb), dim3(256), 0, st, ws,
-                           splits, count, pcount, rs, m, sg, dw, inv_scale, accumulate, flag, kcrs);
-    else
-        hipLaunchKernelGGL((wgrad_reduce_diag_kernel<1>), dim3((uint32_t)nb), dim3(256), 0, st, ws,
-                           splits, count, pcount, rs, m, sg, dw, inv_scale, accumulate, flag, kcrs);
-    return hipGetLastError();
 }
 
 template <int OUT, int L>
@@ -199,6 +208,47 @@ int reduce_split_lanes(int32_t splits, int64_t count) {
     int l = 1;
     while (l < 16 && 2 * l <= splits && (count / 4) * l < (1 << 19)) l *= 2;
     return l;
+}
+
+template <int OUT, int L>
+static void launch_reduce_pick_l(const float *ws, int32_t splits, int64_t count, int64_t pcount,
+                                 int32_t rs, int32_t m, int32_t pitch, bool diag, void *dw,
+                                 float inv_scale, int accumulate, int32_t *flag, int kcrs,
+                                 hipStream_t st) {
+    constexpr int COLS = 256 / L;
+    hipLaunchKernelGGL((wgrad_reduce_pick_kernel<OUT, L>), dim3((uint32_t)((count + COLS - 1) / COLS)),
+                       dim3(256), 0, st, ws, splits, count, pcount, rs, m, pitch, (int)diag, dw,
+                       inv_scale, accumulate, flag, kcrs);
+}
+
+// Split lanes as above, counted for one element per thread.
+template <int OUT>
+static void launch_reduce_pick_out(const float *ws, int32_t splits, int64_t count, int64_t pcount,
+                                   int32_t rs, int32_t m, int32_t pitch, bool diag, void *dw,
+                                   float inv_scale, int accumulate, int32_t *flag, int kcrs,
+                                   hipStream_t st) {
+    const int l = reduce_split_lanes(splits, 4 * count);
+    if (l >= 16)
+        launch_reduce_pick_l<OUT, 16>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+    else if (l >= 4)
+        launch_reduce_pick_l<OUT, 4>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+    else
+        launch_reduce_pick_l<OUT, 1>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+}
+
+hipError_t launch_wgrad_reduce_pick(const float *ws, int32_t splits, int64_t pcount, int64_t k,
+                                    int32_t rs, int32_t m, int32_t pitch, bool diag, void *dw,
+                                    int out_dtype, float inv_scale, int accumulate, int32_t *flag,
+                                    int kcrs, hipStream_t st) {
+    const int64_t count = k * rs * m;
+    if (count <= 0) return hipSuccess;
+    if (out_dtype == 2)
+        launch_reduce_pick_out<2>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+    else if (out_dtype == 0)
+        launch_reduce_pick_out<0>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+    else
+        launch_reduce_pick_out<1>(ws, splits, count, pcount, rs, m, pitch, diag, dw, inv_scale, accumulate, flag, kcrs, st);
+    return hipGetLastError();
 }
 
 template <int OUT>

@@ -1,0 +1,98 @@
+"""Channel counts that are not multiples of 8 with one group: padded by zero
+channels for the matrix-core kernels when the workspace holds the copies, on
+the direct kernels when it does not.  Both against the fp64 oracle, at the
+edges of the padding (one channel, one below and one above a multiple of 8),
+of the copies (odd image sizes, one pixel) and of the stem's 4-channel form."""
+import numpy as np
+import pytest
+
+import oracle.oracle as orc
+import gpu_util as U
+from gpu_util import TOL, Case, full_parity, nchw_f64, oracle_conv, to_nchw
+from paper_2102_06725_amd import inputs as I
+from paper_2102_06725_amd import nnconv as nc
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # name, n, c, h, w, k, r, stride, pad, dil
+    ("rgb7x7s2", 2, 3, 34, 36, 64, 7, 2, 3, 1),       # 4-channel stem pixels
+    ("rgb7x7s2_oddw", 2, 3, 33, 35, 64, 7, 2, 3, 1),  # odd width: 8-channel stem pixels
+    ("grey7x7s2", 1, 1, 30, 32, 64, 7, 2, 3, 1),
+    ("rgb3x3s2", 3, 3, 29, 31, 32, 3, 2, 1, 1),
+    ("grey5x5", 2, 1, 28, 28, 6, 5, 1, 0, 1),
+    ("c7k9", 2, 7, 13, 11, 9, 3, 1, 1, 1),
+    ("c9k7_dil2", 1, 9, 12, 14, 7, 3, 1, 2, 2),
+    ("one_pixel", 3, 5, 1, 1, 3, 1, 1, 0, 1),
+    ("head3x3", 2, 64, 9, 13, 21, 3, 1, 1, 1),        # only K is padded
+    ("head1x1", 2, 128, 7, 8, 91, 1, 1, 0, 1),
+    ("stem_k", 2, 13, 9, 10, 64, 3, 2, 1, 1),         # only C is padded
+    ("c65k130", 1, 65, 8, 8, 130, 3, 1, 1, 1),
+]
+
+
+def _case(s, layout, dtype):
+    name, n, c, h, w, k, r, stride, pad, dil = s
+    return Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil), layout=layout, dtype=dtype,
+                loss_scale=128.0, cfg=97, layer_id=SHAPES.index(s))
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
+def test_padded_channels(nnlib, oracle_lib, s, layout, dtype):
+    full_parity(_case(s, layout, dtype))
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", SHAPES[3:6] + SHAPES[8:9], ids=[s[0] for s in SHAPES[3:6] + SHAPES[8:9]])
+def test_small_workspace_takes_the_direct_kernels(nnlib, oracle_lib, s, layout, monkeypatch):
+    """No workspace forward and backward-data, the direct kernel's partials
+    backward-weight: accepted, and the same result within the tolerance."""
+    case = _case(s, layout, I.F16)
+    d = case.desc()
+    L = case.layer
+    part = 4 * L.k * L.r * L.s * L.c * min(64, max(1, -(-L.n * L.p * L.q // 2048)))
+    full = U.workspace
+
+    def small(desc, pass_):
+        ws, nb = full(desc, pass_)
+        need = 0 if pass_ != nc.NNCONV_WGRAD else -(-part // 256) * 256
+        assert nb > need
+        return ws, need
+
+    monkeypatch.setattr(U, "workspace", small)
+    full_parity(case)
+    st, nb = nc.nnconv_workspace_size(d, nc.NNCONV_WGRAD)
+    assert nc.nnconv_wgrad(d, 16, 16, 16, nc.NNCONV_F32, 1.0, 0, None, 16, 0, None) == \
+        nc.NNCONV_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("where", ["x", "w", "dy"])
+def test_non_finite_values_stay_where_the_definition_has_them(nnlib, oracle_lib, layout, where):
+    """One +inf: the non-finite outputs of every pass are exactly the oracle's
+    (the zero channels add none, the borders of backward-data lose none)."""
+    case = Case(I.Layer("nonfin", 2, 11, 7, 9, 13, 3, 3, 1, 1), layout=layout, cfg=97, layer_id=40)
+    t = case.tensors()
+    flat = t[where].reshape(-1)
+    flat[flat.size // 3] = 0x7C00
+    got = U.run_gpu(case, t)
+    x, w, dy = nchw_f64(case, t)
+    cv = oracle_conv(case)
+    with np.errstate(invalid="ignore"):
+        refs = {"y": cv.fwd(x, w), "dx": cv.dgrad(dy, w), "dw": cv.wgrad(x, dy)}
+    for k, ref in refs.items():
+        g = to_nchw(case, k, got[k])
+        assert np.array_equal(np.isfinite(g), np.isfinite(ref)), k
+        ok = np.isfinite(ref)
+        assert orc.rel_err(g[ok], ref[ok]) <= TOL[I.F16]
+
+
+@pytest.mark.parametrize("cg,n,h,stride", [(4, 3, 9, 1), (8, 40, 16, 1), (32, 5, 12, 2), (2, 1, 5, 2)])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_grouped_reduction_split_lanes(nnlib, oracle_lib, cg, n, h, stride, layout):
+    """Backward-weight of small groups: the split lanes of the picking
+    reduction at one, a few and many splits."""
+    L = I.Layer("grp", n, 64, h, h, 64, 3, 3, stride, 1, groups=64 // cg)
+    full_parity(Case(L, layout=layout, loss_scale=128.0, cfg=97, layer_id=50), passes=("wgrad",))
