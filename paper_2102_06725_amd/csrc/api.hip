@@ -652,6 +652,57 @@ int pick_halo(const TNParams &p, bool pack) {
     return HALO_256x64;
 }
 
+// Estimated time of an implicit-GEMM launch, in microseconds: a + c * red for
+// one workgroup per CU, plus (b + d * red) for each further one (red =
+// reduction length).  Constants fitted to the forward passes of the ResNet-50
+// layers at batch 1 to 64 (154 shapes, 8-14% rms per tile).
+struct TileCost {
+    int bm, bn;
+    double a, c, b, d;
+    double us(const TNParams &p, int64_t red, int cus) const {
+        int64_t wgs = 0;
+        for (int i = 0; i < p.nphase; ++i) wgs += (p.ph[i].M + bm - 1) / bm;
+        wgs *= (int64_t)((p.ncols + bn - 1) / bn) * p.groups;
+        const double more = (double)wgs / cus - 1.0;
+        return a + c * red + (more > 0.0 ? more * (b + d * red) : 0.0);
+    }
+};
+
+// The split-reduction tile (igemm_wk.hip) for a launch with its phases set,
+// or -1 where the larger tiles are the better ones: the smallest estimate
+// against the tile that the 64-channel-slice rule below would take.  The
+// large tiles cost 5 us and 10-12 us per 1000 elements of reduction as long
+// as they fit one per CU, the small ones 4-5 and 1-3.5, and more of them are
+// needed: over the 52 forward layers of ResNet-50 after the stem the picked
+// tiles take 283 us of device time at batch 1 (the large ones alone 829), 418
+// at 8 (854), 800 at 32 (983), and at batch 256 none is picked.
+constexpr TileCost WK_COST[] = {{32, 32, 3.85, 0.00149, 1.18, 0.00150},
+                                {32, 32, 4.94, 0.00094, 2.53, 0.00209},
+                                {64, 64, 4.73, 0.00352, 1.82, 0.00455},
+                                {64, 64, 5.57, 0.00209, 3.73, 0.00576}};
+constexpr TileCost C64_COST[] = {{128, 64, 3.71, 0.00989, 0.70, 0.00507},    // C64S_128x64
+                                 {128, 128, 4.62, 0.01260, 1.15, 0.00905},   // C64S_128x128
+                                 {128, 128, 5.04, 0.01045, 1.67, 0.01242}};  // C64_128x128
+// Block-diagonal weights (p.diag32) take the 32-column tiles, which read only
+// the half of the 64 channels that their columns meet.
+int pick_wk(const TNParams &p, int64_t rows, int64_t red) {
+    if (red <= 0) return -1;
+    const int cus = device_cus();
+    const C64Config big = pick_c64(rows, p.ncols, red);
+    double best = C64_COST[big == C64S_128x64 ? 0 : big == C64S_128x128 ? 1 : 2].us(p, red, cus);
+    int pick = -1;
+    for (int i = 0; i < (int)(sizeof(WK_COST) / sizeof(WK_COST[0])); ++i) {
+        // 5% off, so that the larger tile stays where the two are close
+        if (p.diag32 && WK_COST[i].bn != 32) continue;
+        const double t = 1.05 * WK_COST[i].us(p, p.diag32 ? red / 2 : red, cus);
+        if (t < best) {
+            best = t;
+            pick = i;
+        }
+    }
+    return pick;
+}
+
 // Compute units of the current device (the persistent kernels launch one
 // workgroup per CU).
 int device_cus() {
@@ -732,6 +783,7 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
     p.oi_mul = 1; p.oi_add = 0; p.oj_mul = 1; p.oj_add = 0;
     p.alpha = alpha;
     p.groups = (int32_t)G.g;
+    p.diag32 = G.diag32;
     // Tap order of the 64-channel-slice kernel: the centre tap first.  Its
     // slice reads the tile's own pixels (first touch, from HBM); the other
     // taps then read pixels already in L2 (the tile's own or its
@@ -750,9 +802,12 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
     }
     p.taps.n = t;
     p.k_iters = (int32_t)((int64_t(t) * G.cg + 63) / 64);
+    p.nphase = 1;
+    p.ph[0] = phase_of(p.M, p.mi, p.mj, 0, 0, 0, t);
+    const int wc = tile < 0 ? pick_wk(p, p.M, (int64_t)t * G.cg) : -1;
+    if (wc >= 0)
+        return hip_status(launch_igemm_wk(G.dtype, (WKConfig)wc, p, G.ph > 0 || G.pw > 0, st));
     if (G.cg % 64 == 0) {
-        p.nphase = 1;
-        p.ph[0] = phase_of(p.M, p.mi, p.mj, 0, 0, 0, t);
         const int hc = halo_tile(tile) ? tile - HALO_TILE0 : tile < 0 ? pick_halo(p, pack != nullptr) : -1;
         if (hc >= 0) {
             if (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack))
@@ -793,6 +848,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
     base.oj_mul = (int32_t)G.sw;
     base.alpha = alpha;
     base.groups = (int32_t)G.g;
+    base.diag32 = G.diag32;
     const bool pad = !(G.r == 1 && G.s == 1 && G.ph == 0 && G.pw == 0);
     // taps of output phase (phh, phw), appended to p.taps; returns their count
     auto add_phase_taps = [&](TNParams &p, int64_t phh, int64_t phw) {
@@ -813,7 +869,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
         p.taps.n += t;
         return t;
     };
-    if (c64_dgrad_shape(G)) {
+    if (G.sh * G.sw <= MAX_PHASES) {
         // every stride phase in one launch; a phase without taps writes zeros
         TNParams p = base;
         p.taps.n = 0;
@@ -834,7 +890,10 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             }
         }
         if (p.nphase == 0) return NNCONV_OK;
-        const int hc = halo_tile(tile) ? tile - HALO_TILE0 : tile < 0 ? pick_halo(p, pack != nullptr) : -1;
+        const int wc = tile < 0 ? pick_wk(p, rows, red_rows / rows) : -1;
+        if (wc >= 0) return hip_status(launch_igemm_wk(G.dtype, (WKConfig)wc, p, pad, st));
+        const bool c64 = G.kg % 64 == 0;
+        const int hc = !c64 ? -1 : halo_tile(tile) ? tile - HALO_TILE0 : tile < 0 ? pick_halo(p, pack != nullptr) : -1;
         if (hc >= 0) {
             if (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack))
                 return NNCONV_ERR_UNSUPPORTED;
@@ -843,7 +902,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
         }
         const C64Config cfg =
             tile >= 0 ? (C64Config)tile : pick_c64_geom(G, rows, G.cg, red_rows / rows);
-        return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
+        if (c64) return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
     }
     // Otherwise sigma_h * sigma_w launches, one per output phase (h mod
     // sigma_h, w mod sigma_w): within a phase every pixel sees the same set of

@@ -68,6 +68,7 @@ struct TNParams {
     int32_t oi_mul, oi_add, oj_mul, oj_add;
     float alpha;
     int32_t groups;
+    int32_t diag32;  // igemm_wk only: 64x64 weight blocks, block-diagonal in 32x32 blocks
     int32_t tiles_m, tiles_n;  // per group; filled by the launcher
     TapTable taps;
     int32_t nphase;            // igemm_c64 only: phases in ph[]
@@ -96,6 +97,12 @@ enum C64Config { C64_256x256 = 0,   // 8 waves, 64-element slices, 2 stages
                  C64R_256x128 = 7,    // 4 waves of 128x64, 3 stages (72 KB), 2 per CU
                  C64R_256x64 = 8 };   // 4 waves of 64x64, 4 stages (80 KB), 2 per CU
 hipError_t launch_igemm_c64(int dtype, C64Config cfg, TNParams &p, bool pad, hipStream_t st);
+
+// Small grids, any cr: the waves of a workgroup split the reduction of one
+// small tile (igemm_wk.hip); phases as in the 64-channel-slice kernel.
+// Names: pixels x channels, waves.
+enum WKConfig { WK_32x32_4W = 0, WK_32x32_8W = 1, WK_64x64_4W = 2, WK_64x64_8W = 3 };
+hipError_t launch_igemm_wk(int dtype, WKConfig cfg, TNParams &p, bool pad, hipStream_t st);
 
 // Halo staging for stride-1 "same" geometries (igemm_halo.hip): single
 // phase, one group, cr % 64 == 0, A image of the output's size, at most 32

@@ -1,0 +1,69 @@
+"""The split-reduction tiles (the waves of a workgroup share one small tile),
+which forward and backward-data take where the grid is small, against the fp64
+oracle: one row or column below, at and above the 32- and 64-wide tiles, fewer
+reduction steps than waves, reductions whose 32-element steps mix taps
+(channels not a multiple of 32), stride phases of different sizes and without
+taps, groups, and the block-diagonal weights of small groups.  The last shapes
+are large enough for the 64x64 tiles (784 and 196 of them)."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+from paper_2102_06725_amd import inputs as I
+from paper_2102_06725_amd import nnconv as nc
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # name, n, c, h, w, k, r, stride, pad, dil, groups
+    ("m31", 1, 64, 1, 31, 32, 1, 1, 0, 1, 1),
+    ("m33n40", 1, 64, 3, 11, 40, 1, 1, 0, 1, 1),
+    ("m65n72", 1, 128, 5, 13, 72, 3, 1, 1, 1, 1),
+    ("two_steps", 2, 64, 4, 4, 64, 1, 1, 0, 1, 1),       # fewer than the waves
+    ("one_pixel_long", 1, 1024, 1, 1, 64, 1, 1, 0, 1, 1),
+    ("c8", 2, 8, 9, 7, 8, 3, 1, 1, 1, 1),                # 9 chunks of 8 in 3 steps
+    ("c16k24", 2, 16, 10, 6, 24, 3, 2, 1, 1, 1),
+    ("c40k56", 1, 40, 8, 9, 56, 3, 1, 1, 1, 1),
+    ("c96k32_5x5", 1, 96, 7, 7, 32, 5, 1, 2, 1, 1),
+    ("dil2", 1, 64, 12, 9, 64, 3, 1, 2, 2, 1),
+    ("s2_phases", 1, 64, 13, 11, 128, 3, 2, 1, 1, 1),
+    ("s2_tapless", 3, 64, 7, 6, 64, 1, 2, 0, 1, 1),
+    ("s3_c24", 1, 24, 10, 11, 16, 3, 3, 1, 1, 1),        # 9 phases: one launch each
+    ("groups64", 1, 192, 6, 7, 192, 3, 1, 1, 1, 3),
+    ("groups24", 1, 48, 6, 7, 48, 3, 1, 1, 1, 2),
+    ("diag4", 1, 128, 9, 9, 128, 3, 1, 1, 1, 32),
+    ("diag32_s2", 2, 128, 7, 8, 128, 3, 2, 1, 1, 4),
+    ("tiles64_4w", 8, 512, 28, 27, 120, 1, 1, 0, 1, 1),
+    ("tiles64_8w", 8, 128, 27, 29, 120, 3, 1, 1, 1, 1),
+]
+
+
+def _case(s, dtype, layout="nhwc"):
+    name, n, c, h, w, k, r, stride, pad, dil, groups = s
+    return U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), layout=layout, dtype=dtype,
+                  x_kind="normal", cfg=98, layer_id=SHAPES.index(s), alpha=-0.5)
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
+def test_small_grid_parity(nnlib, oracle_lib, s, dtype):
+    U.full_parity(_case(s, dtype), passes=("fwd", "dgrad"))
+
+
+@pytest.mark.parametrize("s", [SHAPES[2], SHAPES[5], SHAPES[10], SHAPES[15]], ids=lambda s: s[0])
+def test_small_grid_is_reproducible(nnlib, s):
+    case = _case(s, I.F16)
+    t = case.tensors()
+    a, b = (U.run_gpu(case, t, ("fwd", "dgrad")) for _ in range(2))
+    assert np.array_equal(a["y_bits"], b["y_bits"]) and np.array_equal(a["dx_bits"], b["dx_bits"])
+
+
+@pytest.mark.parametrize("where", ["x", "w"])
+def test_small_grid_block_diagonal_keeps_inf_in_its_half(nnlib, where):
+    """An inf reaches at most the 32 channels that share its diagonal block,
+    as in the larger block-diagonal tiles."""
+    case = _case(SHAPES[15], I.F16)
+    t = case.tensors()
+    t[where].reshape(t[where].shape[0], -1)[0, 0] = 0x7C00  # channel 0 / filter 0
+    y = U.run_gpu(case, t, ("fwd",))["y"].reshape(U.shape_of(case, "y"))
+    assert not np.all(np.isfinite(y[..., :32])) and np.all(np.isfinite(y[..., 32:]))
