@@ -547,7 +547,19 @@ TNParams tn_base() {
     return p;
 }
 
-C8Config pick_c8(int64_t ncols) { return ncols <= 64 ? C8_256x64 : C8_128x128; }
+// Tile for reductions whose channels per tap are not a multiple of 64 (rows =
+// GEMM rows, red = reduction length).  Single-stage tiles cover each other's
+// load latency when several share a CU; with at most two workgroups per CU
+// and more than four slices the two-stage tile is the faster one (672 -> 112
+// 1x1 over 128 14x14 images: 15.5 us against 18.5; 264 -> 296 3x3 over 8
+// 31x31: 36.8 against 41.4), with more it loses (40 -> 80 3x3 over 64 56x56:
+// 52.5 against 39.0).
+int device_cus();
+C64Config pick_mix(int64_t rows, int64_t ncols, int64_t groups, int64_t red) {
+    if (ncols <= 64) return C64M_128x64;
+    const int64_t tiles = (rows + 127) / 128 * ((ncols + 127) / 128) * groups;
+    return red > 256 && tiles <= 2 * device_cus() ? C64M2_128x128 : C64M_128x128;
+}
 
 // Tile configuration for the 64-channel-slice kernel, from measurements on
 // the ResNet-50 layers at batch 256 (m = GEMM rows, ncols = output channels
@@ -692,9 +704,9 @@ int pick_wk(const TNParams &p, int64_t rows, int64_t red) {
     double best = C64_COST[big == C64S_128x64 ? 0 : big == C64S_128x128 ? 1 : 2].us(p, red, cus);
     int pick = -1;
     for (int i = 0; i < (int)(sizeof(WK_COST) / sizeof(WK_COST[0])); ++i) {
-        // 5% off, so that the larger tile stays where the two are close
+        // 10% off, so that the larger tile stays where the two are close
         if (p.diag32 && WK_COST[i].bn != 32) continue;
-        const double t = 1.05 * WK_COST[i].us(p, p.diag32 ? red / 2 : red, cus);
+        const double t = 1.10 * WK_COST[i].us(p, p.diag32 ? red / 2 : red, cus);
         if (t < best) {
             best = t;
             pick = i;
@@ -801,7 +813,6 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
         p.taps.boff[t] = (int32_t)(lin * G.cg);
     }
     p.taps.n = t;
-    p.k_iters = (int32_t)((int64_t(t) * G.cg + 63) / 64);
     p.nphase = 1;
     p.ph[0] = phase_of(p.M, p.mi, p.mj, 0, 0, 0, t);
     const int wc = tile < 0 ? pick_wk(p, p.M, (int64_t)t * G.cg) : -1;
@@ -819,7 +830,8 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
             tile >= 0 ? (C64Config)tile : pick_c64_geom(G, p.M, G.kg, (int64_t)t * G.cg);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, G.ph > 0 || G.pw > 0, st));
     }
-    return hip_status(launch_igemm_c8(G.dtype, pick_c8(G.kg), p, st));
+    return hip_status(launch_igemm_c64(G.dtype, pick_mix(p.M, G.kg, G.g, (int64_t)t * G.cg), p,
+                                       G.ph > 0 || G.pw > 0, st));
 }
 
 // Backward-data as sigma_h * sigma_w independent implicit GEMMs, one per
@@ -900,9 +912,10 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             return hip_status(
                 launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, st));
         }
-        const C64Config cfg =
-            tile >= 0 ? (C64Config)tile : pick_c64_geom(G, rows, G.cg, red_rows / rows);
-        if (c64) return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
+        const C64Config cfg = tile >= 0 ? (C64Config)tile
+                              : c64     ? pick_c64_geom(G, rows, G.cg, red_rows / rows)
+                                        : pick_mix(rows, G.cg, G.g, red_rows / rows);
+        return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
     }
     // Otherwise sigma_h * sigma_w launches, one per output phase (h mod
     // sigma_h, w mod sigma_w): within a phase every pixel sees the same set of
@@ -922,15 +935,12 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             p.div_mi = make_fastdiv((uint32_t)mi);
             p.oi_add = (int32_t)phh;
             p.oj_add = (int32_t)phw;
-            p.k_iters = (int32_t)((int64_t(t) * G.kg + 63) / 64);
-            if (G.kg % 64 == 0) {
-                p.nphase = 1;
-                p.ph[0] = phase_of(p.M, mi, mj, phh, phw, 0, t);
-                TRY_HIP(launch_igemm_c64(G.dtype, pick_c64_geom(G, p.M, G.cg, (int64_t)t * G.kg), p, pad,
-                                         st));
-            } else {
-                TRY_HIP(launch_igemm_c8(G.dtype, pick_c8(G.cg), p, st));
-            }
+            p.nphase = 1;
+            p.ph[0] = phase_of(p.M, mi, mj, phh, phw, 0, t);
+            const int64_t red = (int64_t)t * G.kg;
+            const C64Config cfg = G.kg % 64 == 0 ? pick_c64_geom(G, p.M, G.cg, red)
+                                                 : pick_mix(p.M, G.cg, G.g, red);
+            TRY_HIP(launch_igemm_c64(G.dtype, cfg, p, pad, st));
         }
     }
     return NNCONV_OK;

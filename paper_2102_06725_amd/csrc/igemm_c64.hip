@@ -1,7 +1,7 @@
 // igemm_c64.hip -- large-tile implicit-GEMM convolution for the forward pass
-// and each stride phase of the backward-data pass, for reductions whose
-// per-tap channel count is a multiple of 64 (every ResNet-50 layer but the
-// stem).
+// and each stride phase of the backward-data pass: reductions whose per-tap
+// channel count is a multiple of 64 (every ResNet-50 layer but the stem), and
+// a variant of the 128-row tiles for any multiple of 8.
 //
 // Design (gfx950):
 //   - block tile BM x BN, NW = WM x WN waves, wave tiles built from
@@ -53,8 +53,17 @@ __device__ __forceinline__ int slot(int r, int c) {
 // issues the matrix-core instructions of the current one, so LDS latency
 // overlaps MFMA work inside the wave instead of relying on other waves.
 // OCC: resident workgroups per CU the register budget is sized for.
+//
+// MIX: any cr that is a multiple of 8 (P.div_crv set).  The reduction is cut
+// into 64-element slices across taps, tap after tap; each 16-byte chunk of a
+// slice has its own tap, decoded per lane.  These layers are bound by their
+// tensors' bytes: against a 4-stage pipeline of 32-element slices that stored
+// 8 bytes per lane straight from the accumulators, the shared output stage
+// (whole lines, streaming) and the smaller tiles' occupancy took 40 -> 240 and
+// 240 -> 40 1x1 over 128 28x28 images from 25-31 to 20 us a pass (56 MB: 11 us
+// at the copy rate), 16 -> 96 over 128 112x112 from 154 to 82.
 template <class T, int BM, int BN, int WM, int WN, int BKC, int STAGES, bool PAD, bool DIAG,
-          bool RING, int OCC>
+          bool RING, int OCC, bool MIX = false>
 __global__ __launch_bounds__(WM * WN * 64, OCC)
 void igemm_c64_kernel(const TNParams P) {
     using namespace c64;
@@ -70,6 +79,7 @@ void igemm_c64_kernel(const TNParams P) {
     constexpr int LOADS = A_LD + B_LD;
     static_assert(FM >= 1 && FN >= 1 && A_LD >= 1 && B_LD >= 1, "tile shape");
     static_assert(!DIAG || (FN == 1 && WTN == 32 && BKC == 8), "block-diagonal: 32-column waves");
+    static_assert(!MIX || (BKC == 8 && !RING && !DIAG), "mixed taps: 64-element slices");
 
     constexpr int LDS_SLOTS = STAGES * STAGE_SLOTS > BM * BN / 8 ? STAGES * STAGE_SLOTS : BM * BN / 8;
     __shared__ u32x4 lds[LDS_SLOTS];
@@ -122,7 +132,7 @@ void igemm_c64_kernel(const TNParams P) {
             // byte offset of this row's base pixel and chunk (may wrap below 0
             // for padded rows: only used together with a valid tap shift)
             a_voff[j] = (uint32_t)(((n * P.a_h + bh) * P.a_w + bw) * P.a_c + g * P.a_cg_ofs) * 2u +
-                        (uint32_t)lchunk * 16u;
+                        (MIX ? 0u : (uint32_t)lchunk * 16u);
             if constexpr (PAD) {
                 for (int t = 0; t < ntaps; ++t) {
                     const int h = bh + P.taps.dh[tap0 + t], w = bw + P.taps.dw[tap0 + t];
@@ -141,7 +151,8 @@ void igemm_c64_kernel(const TNParams P) {
         const int lchunk = pch ^ swz<BKC>(r);
         const int col = n0 + r;
         b_voff[j] = col < P.ncols
-                        ? (uint32_t)(g * P.b_g_ofs + col * P.b_ld) * 2u + (uint32_t)lchunk * 16u
+                        ? (uint32_t)(g * P.b_g_ofs + col * P.b_ld) * 2u +
+                              (MIX ? 0u : (uint32_t)lchunk * 16u)
                         : OOB_OFFSET;
     }
 
@@ -163,7 +174,30 @@ void igemm_c64_kernel(const TNParams P) {
     uint32_t sl_ashift = 0, sl_sb = 0;
     int sl_t = 0;
     i32x4 sl_da = {}, sl_db = {};
+    // MIX: of the lane's two possible chunks of a slice (rows in the even and
+    // the odd 8-row blocks of the tile): the byte shifts of A and B and the
+    // tap, -1 past the end of the reduction
+    const int mx_chunks = ntaps * (P.cr >> 3);
+    int mx_base = 0, mx_t[2] = {0, 0};
+    uint32_t mx_a[2] = {0, 0}, mx_b[2] = {0, 0};
     auto prepare = [&](int buf, bool live) {
+        if constexpr (MIX) {
+            sl_sb = lds0 + (uint32_t)(buf * STAGE_SLOTS) * 16u;
+            sl_da = desc_of(P.a, P.a_bytes);
+            sl_db = desc_of(P.b, P.b_bytes);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int gv = mx_base + (pch ^ ((lrow >> 1) + 4 * u));
+                const bool ok = gv < mx_chunks;
+                const int t = ok ? (int)fdiv((uint32_t)gv, P.div_crv) : 0;
+                const uint32_t cofs = (uint32_t)(gv - t * (P.cr >> 3)) * 16u;
+                mx_t[u] = ok ? t : -1;
+                mx_a[u] = (uint32_t)__shfl((int)tap_ashift, t) + cofs;
+                mx_b[u] = (uint32_t)__shfl((int)tap_boff, t) + cofs;
+            }
+            mx_base += 8;
+            return;
+        }
         // A: x / dy rows; the tap's pixel shift can be negative, so it is
         // added to the lane offsets; the channel base moves the descriptor
         sl_ashift = (uint32_t)__builtin_amdgcn_readlane((int)tap_ashift, ld_t);
@@ -180,6 +214,21 @@ void igemm_c64_kernel(const TNParams P) {
         }
     };
     auto load = [&](int j) {
+        if constexpr (MIX) {
+            if (j < A_LD) {
+                const int u = (wave * A_LD + j) & 1, t = mx_t[u];
+                const bool ok = t >= 0 && (PAD ? ((a_mask[j] >> (t & 63)) & 1) != 0
+                                               : a_voff[j] != OOB_OFFSET);
+                dma16(sl_sb + (uint32_t)((wave * A_LD + j) * 64) * 16u,
+                      ok ? a_voff[j] + mx_a[u] : OOB_OFFSET, sl_da);
+            } else {
+                const int jb = j - A_LD, u = (wave * B_LD + jb) & 1;
+                dma16(sl_sb + (uint32_t)(A_SLOTS + (wave * B_LD + jb) * 64) * 16u,
+                      mx_t[u] >= 0 && b_voff[jb] != OOB_OFFSET ? b_voff[jb] + mx_b[u] : OOB_OFFSET,
+                      sl_db);
+            }
+            return;
+        }
         if (j < A_LD) {
             uint32_t off = a_voff[j] + sl_ashift;
             if constexpr (PAD) {
@@ -207,7 +256,7 @@ void igemm_c64_kernel(const TNParams P) {
 
     const int l32 = lane & 31;
     const int khalf = lane >> 5;
-    const int k_iters = ntaps * (P.cr / BK);
+    const int k_iters = MIX ? (mx_chunks + BKC - 1) / BKC : ntaps * (P.cr / BK);
 
     auto compute = [&](const u32x4 *st) {
         if constexpr (DIAG) {
@@ -353,7 +402,7 @@ void igemm_c64_kernel(const TNParams P) {
 
 template <class T, int BM, int BN, int WM, int WN, int BKC, int STAGES, bool DIAG = false,
           bool RING = false,
-          int OCC = (WM * WN == 4) ? ((BM * BN <= 128 * 128) ? 4 : 2) : 1>
+          int OCC = (WM * WN == 4) ? ((BM * BN <= 128 * 128) ? 4 : 2) : 1, bool MIX = false>
 static hipError_t launch_c64_cfg(TNParams &p, bool pad, hipStream_t st) {
     p.tiles_n = (p.ncols + BN - 1) / BN;
     int64_t nb = 0;
@@ -365,10 +414,10 @@ static hipError_t launch_c64_cfg(TNParams &p, bool pad, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
     if (pad)
-        hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, true, DIAG, RING, OCC>),
+        hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, true, DIAG, RING, OCC, MIX>),
                            dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p);
     else
-        hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, false, DIAG, RING, OCC>),
+        hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, false, DIAG, RING, OCC, MIX>),
                            dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p);
     return hipGetLastError();
 }
@@ -394,6 +443,9 @@ static hipError_t launch_c64_t(C64Config cfg, TNParams &p, bool pad, hipStream_t
         case C64R_256x256: return launch_c64_cfg<T, 256, 256, 2, 2, 4, 4, false, true, 1>(p, pad, st);
         case C64R_256x128: return launch_c64_cfg<T, 256, 128, 2, 2, 4, 3, false, true, 2>(p, pad, st);
         case C64R_256x64: return launch_c64_cfg<T, 256, 64, 4, 1, 4, 4, false, true, 2>(p, pad, st);
+        case C64M_128x64: return launch_c64_cfg<T, 128, 64, 2, 2, 8, 1, false, false, 4, true>(p, pad, st);
+        case C64M2_128x128: return launch_c64_cfg<T, 128, 128, 2, 2, 8, 2, false, false, 2, true>(p, pad, st);
+        case C64M_128x128: return launch_c64_cfg<T, 128, 128, 2, 2, 8, 1, false, false, 4, true>(p, pad, st);
         case C64S_128x128:
         default: return launch_c64_cfg<T, 128, 128, 2, 2, 8, 1>(p, pad, st);
     }

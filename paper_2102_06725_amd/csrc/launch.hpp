@@ -61,7 +61,6 @@ struct TNParams {
     int32_t ai_mul, ai_add, aj_mul, aj_add;
     int32_t cr;            // reduction channels per tap (multiple of 8)
     FastDiv div_crv;       // division by cr / 8
-    int32_t k_iters;       // ceil(taps * cr / 64)
     int32_t ncols;         // output columns per group (multiple of 8)
     int32_t b_ld, b_g_ofs;
     int32_t o_h, o_w, o_c, o_cg_ofs;
@@ -75,13 +74,7 @@ struct TNParams {
     TNPhase ph[MAX_PHASES];
 };
 
-// Any cr (a multiple of 8): the reduction is cut into slices of 32 elements
-// built from 8-channel chunks of consecutive taps (recomputes k_iters for
-// its own slice depth).
-enum C8Config { C8_128x128 = 0, C8_256x64 = 1, C8_256x128 = 2 };
-hipError_t launch_igemm_c8(int dtype, C8Config cfg, TNParams &p, hipStream_t st);
-
-// cr % 64 == 0: 64-channel slices of one tap (k_iters is derived from the
+// 64-element slices, of one tap where cr % 64 == 0 (the C64M tiles: of any
 // taps).  pad: some (row, tap) pairs fall outside the A image and must read
 // zeros.
 enum C64Config { C64_256x256 = 0,   // 8 waves, 64-element slices, 2 stages
@@ -95,7 +88,9 @@ enum C64Config { C64_256x256 = 0,   // 8 waves, 64-element slices, 2 stages
                  // fragments (one wave per SIMD for 256x256: 128x128 per wave)
                  C64R_256x256 = 6,    // 4 waves of 128x128, 4 stages (128 KB)
                  C64R_256x128 = 7,    // 4 waves of 128x64, 3 stages (72 KB), 2 per CU
-                 C64R_256x64 = 8 };   // 4 waves of 64x64, 4 stages (80 KB), 2 per CU
+                 C64R_256x64 = 8,     // 4 waves of 64x64, 4 stages (80 KB), 2 per CU
+                 // any cr that is a multiple of 8: single stage, and two stages
+                 C64M_128x64 = 32, C64M_128x128 = 33, C64M2_128x128 = 34 };
 hipError_t launch_igemm_c64(int dtype, C64Config cfg, TNParams &p, bool pad, hipStream_t st);
 
 // Small grids, any cr: the waves of a workgroup split the reduction of one

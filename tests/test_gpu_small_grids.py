@@ -67,3 +67,25 @@ def test_small_grid_block_diagonal_keeps_inf_in_its_half(nnlib, where):
     t[where].reshape(t[where].shape[0], -1)[0, 0] = 0x7C00  # channel 0 / filter 0
     y = U.run_gpu(case, t, ("fwd",))["y"].reshape(U.shape_of(case, "y"))
     assert not np.all(np.isfinite(y[..., :32])) and np.all(np.isfinite(y[..., 32:]))
+
+
+# Grids past the split-reduction tiles whose channels per tap are not a
+# multiple of 64: the mixed-tap tiles of the 64-element-slice kernel.
+MIX_SHAPES = [
+    # name, n, c, h, w, k, r, stride, pad, dil, groups
+    ("c40k240", 2, 40, 112, 111, 240, 1, 1, 0, 1, 1),        # one slice, ragged rows and columns
+    ("c240k40", 2, 240, 112, 111, 40, 1, 1, 0, 1, 1),        # 64-column tile, 3.75 slices
+    ("c24k72_s2", 3, 24, 120, 121, 72, 3, 2, 1, 1, 1),       # four phases, chunks across taps
+    ("c8k16_5x5", 2, 8, 150, 151, 16, 5, 1, 2, 1, 1),        # a tap per chunk, 25 taps
+    ("c16k88_s3", 2, 16, 200, 170, 88, 3, 3, 1, 1, 1),       # nine phases: one launch each
+    ("c264k72_2stage", 8, 264, 56, 56, 72, 1, 1, 0, 1, 1),   # two-stage tile
+    ("c72g3", 1, 72, 130, 131, 72, 3, 1, 1, 1, 3),           # groups of 24
+]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("s", MIX_SHAPES, ids=[s[0] for s in MIX_SHAPES])
+def test_mixed_tap_tiles(nnlib, oracle_lib, s, dtype):
+    name, n, c, h, w, k, r, stride, pad, dil, groups = s
+    U.full_parity(U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
+                         x_kind="normal", cfg=99, layer_id=MIX_SHAPES.index(s)), passes=("fwd", "dgrad"))
