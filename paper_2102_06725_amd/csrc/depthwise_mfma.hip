@@ -1,0 +1,329 @@
+// depthwise_mfma.hip -- stride-1 depthwise convolution on the matrix cores:
+// forward, and backward-data (the forward correlation of dy with the rotated
+// filter); no dilation, 3x3 / 5x5 / 7x7, channel-last.
+//
+// On the vector ALUs a 5x5 layer needs 25 multiply-adds per output, and with
+// bf16 operands each also widens a weight: 128 images of 28x28x240 took 62 us
+// (fp16 39) where the tensors' bytes take 19.  v_mfma_f32_16x16x32 does 512 products per
+// clock and SIMD against 16, so it pays even though only 1 of 16 is useful:
+//   D[channel, pixel] += sum_k W[channel, k] * X[k, pixel],
+//   k = (one of two filter columns s, one of 16 channels),
+// where W is the 16x16 diagonal matrix of the filter's weights at (r, s).  X is
+// read from the channel-last LDS tile as it lies (8 consecutive channels of a
+// pixel are a lane's 16 bytes), D holds 4 consecutive channels of a pixel per
+// lane.  An X fragment (one tile row, one pair of filter columns) serves every
+// filter row, each into its own output row, so 3 fragment reads feed 15 MFMAs
+// of a 5x5 layer.  Per 16x16 outputs: R * ceil(R/2) MFMAs of 16 clocks.
+//
+// The zeros off the diagonal must not meet an inf or NaN of another channel
+// (0 * inf = NaN): the staging checks every element, and a workgroup whose
+// tile holds one computes it on the vector ALUs, channel by channel.
+// 128 images of 28x28x240, 5x5: bf16 61.5 -> 29.5 us, fp16 39 -> 29.5; 56x56x144,
+// 3x3: bf16 65 -> 44, fp16 56 -> 47.
+#include <cstring>
+
+#include "launch.hpp"
+
+namespace nnconv {
+
+namespace dwm {
+
+template <class T>
+__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c);
+template <>
+__device__ __forceinline__ f32x4 mfma16<Half>(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
+                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ f32x4 mfma16<BFloat>(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Running maximum of the magnitudes of 16-bit values, two at a time; at or
+// above INF one of them was inf or NaN.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+template <class T>
+constexpr uint32_t INF = T::id == Half::id ? 0x7C00u : 0x7F80u;
+__device__ __forceinline__ void max_abs(u16x2 &m, u32x4 v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v[i] & 0x7FFF7FFFu));
+}
+
+// Tile: NCG groups of 16 channels x NCB blocks of 16 pixels, one wave each;
+// a block is 16 columns of a row (PXW = 16), or 8 columns of two rows TR rows
+// apart (PXW = 8, narrow images).  TR: output rows per strip of a wave.
+template <int R, int NCG, int NCB, int PXW, int TR>
+struct Tile {
+    static constexpr int CPP = NCG * 2;  // 16-byte chunks per pixel
+    static constexpr int TW = NCB * PXW;
+    static constexpr int HALVES = 16 / PXW;
+    static constexpr int TH = TR * HALVES;
+    static constexpr int IW = TW - 1 + R;
+    static constexpr int IH = TH - 1 + R;
+    static constexpr int CHUNKS = IH * IW * CPP;
+    static constexpr int NL = (CHUNKS + 255) / 256;
+    static constexpr int NP = (R + 1) / 2;  // pairs of filter columns
+    static constexpr int RS = R * R;
+};
+
+// Swizzle of the 16-byte chunks of a pixel in tile column c: any 16
+// consecutive columns at one chunk fall in 16 distinct 16-byte bank groups.
+template <int CPP>
+__device__ __forceinline__ int swz(int c) {
+    return CPP == 2 ? (c >> 3) & 1 : CPP == 4 ? (c >> 2) & 3 : (c >> 1) & 7;
+}
+
+}  // namespace dwm
+
+// out[n, o, u, c] = alpha * sum_{r,s} in[n, o - ph + r, u - pw + s, c] * w'[c, r, s]
+// with w' = w, or w rotated by 180 degrees (FLIP).
+template <class T, int R, int NCG, int NCB, int PXW, int TR, bool FLIP>
+__global__ __launch_bounds__(256) void dwm_fwd_kernel(const DWTParams P,
+                                                      const uint16_t *__restrict__ in,
+                                                      const uint16_t *__restrict__ w,
+                                                      uint16_t *__restrict__ out) {
+    using namespace dwm;
+    using F = Tile<R, NCG, NCB, PXW, TR>;
+    static_assert(NCG * NCB == 4, "four waves");
+    constexpr int CW = NCG * 16;  // channels of the block
+    __shared__ u32x4 tile[F::CHUNKS];
+    __shared__ uint16_t wl[CW * F::RS];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int cb = (int)(b % (uint32_t)P.cblocks);
+    b /= (uint32_t)P.cblocks;
+    const int tw = (int)(b % (uint32_t)P.tiles_w);
+    b /= (uint32_t)P.tiles_w;
+    const int th = (int)(b % (uint32_t)P.tiles_h);
+    const int n = (int)(b / (uint32_t)P.tiles_h);
+    const int oh0 = th * F::TH, ow0 = tw * F::TW;
+
+    // The whole input tile in flight; outside the image (or past the last
+    // channel vector) the range check returns zeros.  A thread keeps its
+    // chunk of a pixel and walks PX pixels (in tile raster order) per load.
+    constexpr int PX = 256 / F::CPP, DROW = PX / F::IW, DCOL = PX % F::IW;
+    const int cvl = tid % F::CPP;
+    const int row0 = (tid / F::CPP) / F::IW, col0 = (tid / F::CPP) % F::IW;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, P.in_bytes);
+    u32x4 ld[F::NL];
+    {
+        const int h0 = oh0 - P.ph, w0 = ow0 - P.pw;
+        const int c2 = P.c * 2;
+        int h = h0 + row0, wc = w0 + col0;
+        uint32_t off = (uint32_t)((n * P.ih + h) * P.iw + wc) * (uint32_t)c2 +
+                       (uint32_t)(cb * F::CPP + cvl) * 16u;
+        const uint32_t step = (uint32_t)((DROW * P.iw + DCOL) * c2);
+        const uint32_t wrap = (uint32_t)((P.iw - F::IW) * c2);
+        // rows past the tile fail the row test
+        const int h_end = min(P.ih, h0 + F::IH);
+        const int w_lim = w0 + F::IW;
+        const bool lane_in = cb * F::CPP + cvl < P.c8;
+#pragma unroll
+        for (int k = 0; k < F::NL; ++k) {
+            const bool ok = lane_in && h >= 0 && h < h_end && (unsigned)wc < (unsigned)P.iw;
+            ld[k] = load16(rin, ok ? off : OOB_OFFSET);
+            h += DROW;
+            wc += DCOL;
+            off += step;
+            if (wc >= w_lim) {
+                wc -= F::IW;
+                h += 1;
+                off += wrap;
+            }
+        }
+    }
+    // weights of the block's channels, [channel][tap] as in memory
+    for (int e = tid; e < CW * F::RS; e += 256) {
+        const int64_t g0 = (int64_t)cb * CW * F::RS;
+        const int cl = e / F::RS, t = e - cl * F::RS;
+        wl[e] = cb * CW + cl < P.c ? w[g0 + (FLIP ? cl * F::RS + F::RS - 1 - t : e)] : (uint16_t)0;
+    }
+    u16x2 big = {};
+    {
+        int col = col0;
+#pragma unroll
+        for (int k = 0; k < F::NL; ++k) {
+            max_abs(big, ld[k]);
+            if (F::NL * 256 == F::CHUNKS || k * 256 + tid < F::CHUNKS)
+                tile[(k * PX + tid / F::CPP) * F::CPP + (cvl ^ swz<F::CPP>(col))] = ld[k];
+            col += DCOL;
+            if (col >= F::IW) col -= F::IW;
+        }
+    }
+    const bool bad = __syncthreads_or(big[0] >= INF<T> || big[1] >= INF<T>);
+
+    if (bad) {
+        // one output element at a time from the tile, in the order of the taps
+        const uint16_t *t16 = (const uint16_t *)&tile[0];
+        for (int e = tid; e < F::TH * F::TW * CW; e += 256) {
+            const int cl = e % CW, px = e / CW;
+            const int i = px / F::TW, j = px - i * F::TW;
+            const int ch = cb * CW + cl, oh = oh0 + i, ow = ow0 + j;
+            if (ch >= P.c || oh >= P.oh || ow >= P.ow) continue;
+            float acc = 0.f;
+            for (int r = 0; r < R; ++r)
+                for (int s = 0; s < R; ++s) {
+                    const int sl = ((i + r) * F::IW + j + s) * F::CPP +
+                                   ((cl >> 3) ^ swz<F::CPP>(j + s));
+                    acc = __builtin_fmaf(from16<T>(t16[sl * 8 + (cl & 7)]),
+                                         from16<T>(wl[cl * F::RS + r * R + s]), acc);
+                }
+            out[(((int64_t)n * P.oh + oh) * P.ow + ow) * P.c + ch] = (uint16_t)to16<T>(acc * P.alpha);
+        }
+        return;
+    }
+
+    const int g = wave % NCG, blk = wave / NCG;  // channel group, pixel block
+    const int l16 = lane & 15, q = lane >> 4;
+    // diagonal weight fragments: lane row = channel l16, k = 8 q + e is
+    // channel 8 (q & 1) + e of filter column 2 pr + (q >> 1)
+    u32x4 wf[R][F::NP];
+    {
+        const bool diag = (q & 1) == (l16 >> 3);
+        const int dword = (l16 & 7) >> 1, sh = (l16 & 1) * 16;
+        const uint16_t *wc = wl + (g * 16 + l16) * F::RS;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int pr = 0; pr < F::NP; ++pr) {
+                const int s = 2 * pr + (q >> 1);
+                const uint32_t v =
+                    diag && s < R ? (uint32_t)wc[r * R + (s < R ? s : 0)] << sh : 0u;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) wf[r][pr][d] = d == dword ? v : 0u;
+            }
+    }
+    // LDS address of the lane's 16 bytes per pair of filter columns (a column
+    // past the filter re-reads the last one: its weight is zero, and what it
+    // reads is finite)
+    const int dr = PXW == 16 ? 0 : l16 / PXW, dc = l16 % PXW;
+    const int col = blk * PXW + dc;
+    const u32x4 *xb[F::NP];
+#pragma unroll
+    for (int pr = 0; pr < F::NP; ++pr) {
+        const int c = col + (2 * pr + (q >> 1) < R ? 2 * pr + (q >> 1) : R - 1);
+        xb[pr] = tile + (dr * TR * F::IW + c) * F::CPP + ((g * 2 + (q & 1)) ^ swz<F::CPP>(c));
+    }
+
+    const int ch = (cb * NCG + g) * 16 + 4 * q;
+    const int ow = ow0 + col;
+    // output rows of this lane's strip inside the image
+    const int live = ch < P.c && ow < P.ow ? P.oh - (oh0 + dr * TR) : 0;
+    uint16_t *o = out + (((int64_t)n * P.oh + oh0 + dr * TR) * P.ow + ow) * P.c + ch;
+    const int64_t ostep = (int64_t)P.ow * P.c;
+    f32x4 acc[TR];
+#pragma unroll
+    for (int hh = 0; hh < TR - 1 + R; ++hh) {
+        u32x4 xf[F::NP];
+#pragma unroll
+        for (int pr = 0; pr < F::NP; ++pr) xf[pr] = xb[pr][hh * (F::IW * F::CPP)];
+        // input row hh is filter row r of output row hh - r
+#pragma unroll
+        for (int pr = 0; pr < F::NP; ++pr)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (hh - r >= 0 && hh - r < TR)
+                    acc[hh - r] = mfma16<T>(wf[r][pr], xf[pr],
+                                            r == 0 && pr == 0 ? f32x4{} : acc[hh - r]);
+        if (hh >= R - 1) {  // its last filter row
+            const int p = hh - (R - 1);
+            if (p < live) {
+                u32x2 pk;
+                pk[0] = to16<T>(acc[p][0] * P.alpha) | (to16<T>(acc[p][1] * P.alpha) << 16);
+                pk[1] = to16<T>(acc[p][2] * P.alpha) | (to16<T>(acc[p][3] * P.alpha) << 16);
+                *(u32x2 *)(o + p * ostep) = pk;
+            }
+        }
+    }
+}
+
+namespace {
+
+constexpr int strip_rows(int r) { return r <= 5 ? 14 : 7; }
+
+struct DwmPlan {
+    int cfg;      // as in launch_dwm_rs
+    int64_t wgs;
+};
+DwmPlan plan(const DWTParams &q, int r) {
+    const int tr = strip_rows(r);
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    if (q.ow <= 8) return {0, q.n * up(q.c, 64) * up(q.oh, 8)};
+    if (q.ow <= 16) return {1, q.n * up(q.c, 64) * up(q.oh, tr)};
+    // wider images, tiles 32 pixels wide: 32 channels x tr rows, or 16
+    // channels x 2 tr rows (less halo where the image's height fills it),
+    // whichever stages fewer vectors
+    const int64_t tw = up(q.ow, 32);
+    const int64_t a = up(q.c, 32) * up(q.oh, tr), va = a * (tr - 1 + r) * (31 + r) * 4;
+    const int64_t b = up(q.c, 16) * up(q.oh, 2 * tr), vb = b * (2 * tr - 1 + r) * (31 + r) * 2;
+    return vb < va ? DwmPlan{2, q.n * tw * b} : DwmPlan{3, q.n * tw * a};
+}
+
+template <class T, int R, int NCG, int NCB, int PXW, int TR, bool FLIP>
+hipError_t launch_dwm_cfg(DWTParams q, const void *in, const void *w, void *out, hipStream_t st) {
+    using F = dwm::Tile<R, NCG, NCB, PXW, TR>;
+    q.cblocks = (q.c + NCG * 16 - 1) / (NCG * 16);
+    q.tiles_w = (q.ow + F::TW - 1) / F::TW;
+    q.tiles_h = (q.oh + F::TH - 1) / F::TH;
+    const int64_t nb = (int64_t)q.n * q.tiles_h * q.tiles_w * q.cblocks;
+    if (nb <= 0) return hipSuccess;
+    if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dwm_fwd_kernel<T, R, NCG, NCB, PXW, TR, FLIP>), dim3((uint32_t)nb),
+                       dim3(256), 0, st, q, (const uint16_t *)in, (const uint16_t *)w,
+                       (uint16_t *)out);
+    return hipGetLastError();
+}
+
+template <class T, int R, bool FLIP>
+hipError_t launch_dwm_rs(const DWTParams &q, const void *in, const void *w, void *out,
+                         hipStream_t st) {
+    constexpr int TR = strip_rows(R);
+    switch (plan(q, R).cfg) {
+        case 0: return launch_dwm_cfg<T, R, 4, 1, 8, 4, FLIP>(q, in, w, out, st);
+        case 1: return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
+        case 2: return launch_dwm_cfg<T, R, 1, 4, 8, TR, FLIP>(q, in, w, out, st);
+        default: return launch_dwm_cfg<T, R, 2, 2, 16, TR, FLIP>(q, in, w, out, st);
+    }
+}
+
+template <class T, bool FLIP>
+hipError_t launch_dwm_t(const DWTParams &q, int r, const void *in, const void *w, void *out,
+                        hipStream_t st) {
+    switch (r) {
+        case 3: return launch_dwm_rs<T, 3, FLIP>(q, in, w, out, st);
+        case 5: return launch_dwm_rs<T, 5, FLIP>(q, in, w, out, st);
+        case 7: return launch_dwm_rs<T, 7, FLIP>(q, in, w, out, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// A workgroup's strips are long: below about two workgroups per CU (one for
+// 5x5 and 7x7, which gain more per output) the LDS-tiled vector kernel's
+// smaller tiles are the faster ones, and for 3x3 on images up to 8 wide, where
+// a tile is little more than its set-up (480 channels, 14x14, 3x3: 32 images
+// 6.0 us there against 6.7 here, 128 images 14.6 against 13.3; 5x5: 16 images
+// 7.0 against 8.3, 32 9.0 against 8.8; 1152 channels, 7x7, 3x3, 128 images 9.4
+// against 10.7).
+bool depthwise_mfma_pays(const DWTParams &q, int r) {
+    if (r == 3 && q.ow <= 8) return false;
+    return plan(q, r).wgs >= (r == 3 ? 512 : 256);
+}
+
+hipError_t launch_depthwise_mfma(int dtype, const DWTParams &q, int r, bool flip, const void *in,
+                                 const void *w, void *out, hipStream_t st) {
+    if (dtype == Half::id)
+        return flip ? launch_dwm_t<Half, true>(q, r, in, w, out, st)
+                    : launch_dwm_t<Half, false>(q, r, in, w, out, st);
+    return flip ? launch_dwm_t<BFloat, true>(q, r, in, w, out, st)
+                : launch_dwm_t<BFloat, false>(q, r, in, w, out, st);
+}
+
+}  // namespace nnconv

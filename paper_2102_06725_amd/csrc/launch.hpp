@@ -356,6 +356,14 @@ int32_t dw_tiled_wgrad_splits(const DWParams &p);
 hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const void *a,
                                   const void *b, void *out, hipStream_t st);
 
+// Stride-1 depthwise on the matrix cores (depthwise_mfma.hip): forward, or the
+// forward correlation with the rotated filter (flip: backward-data); the input
+// and output images, padding and byte sizes are set in p.
+// whether it is the faster kernel for this launch
+bool depthwise_mfma_pays(const DWTParams &p, int r);
+hipError_t launch_depthwise_mfma(int dtype, const DWTParams &p, int r, bool flip, const void *in,
+                                 const void *w, void *out, hipStream_t st);
+
 // Training-step pieces (update.hip).  The state type is the C ABI's.
 hipError_t launch_loss_scaler_init(nnconv_loss_scaler *s, float scale, float factor,
                                    int32_t interval, hipStream_t st);

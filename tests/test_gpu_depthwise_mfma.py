@@ -1,0 +1,75 @@
+"""The matrix-core depthwise kernel (stride 1, from one or two workgroups per
+CU up) against the fp64 oracle: each of its four tiles at ragged image sizes
+and channel counts, every filter size, padding 0 to R-1, and inf / NaN inputs,
+which must stay in their own channel."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+import oracle.oracle as orc
+from paper_2102_06725_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# n, c, h, w, r, pad: workgroups = n * channel blocks * row tiles * column tiles,
+# at least 512 for 3x3 and 256 for 5x5 / 7x7
+SHAPES = [
+    ("w7_5x5", 86, 136, 7, 7, 5, 2),        # 8-wide tile, 3 blocks of 64 channels, 8 past the end
+    ("w8_7x7", 128, 72, 9, 8, 7, 3),        # two row tiles
+    ("w14_3x3", 171, 136, 14, 14, 3, 1),    # 16-wide tile
+    ("w15_5x5", 43, 136, 17, 15, 5, 0),     # padding 0: 13x11 outputs
+    ("w16_7x7", 64, 72, 15, 10, 7, 6),      # padding R-1: 21x16 outputs
+    ("w28_5x5", 17, 240, 28, 28, 5, 2),     # 16 channels x 28 rows
+    ("w33_3x3", 19, 72, 29, 33, 3, 1),      # 32 channels x 14 rows, ragged second tile column
+    ("w17_7x7", 22, 72, 27, 17, 7, 3),
+    ("w40_3x3", 65, 24, 56, 33, 3, 1),      # 16-channel tile, 24 channels
+]
+
+
+def _case(s, layout, dtype):
+    name, n, c, h, w, r, pad = s
+    return U.Case(I.Layer(name, n, c, h, w, c, r, r, 1, pad, groups=c), layout=layout, dtype=dtype,
+                  x_kind="normal", cfg=100, layer_id=SHAPES.index(s), alpha=0.5)
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
+def test_depthwise_mfma_parity(nnlib, oracle_lib, s, dtype):
+    U.full_parity(_case(s, "nhwc", dtype), passes=("fwd", "dgrad"))
+
+
+def test_depthwise_mfma_nchw(nnlib, oracle_lib):
+    U.full_parity(_case(SHAPES[5], "nchw", I.BF16), passes=("fwd", "dgrad"))
+
+
+@pytest.mark.parametrize("bits", [0x7C00, 0xFC00, 0x7E01], ids=["inf", "-inf", "nan"])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[2], SHAPES[5], SHAPES[6]], ids=lambda s: s[0])
+def test_depthwise_mfma_non_finite(nnlib, oracle_lib, s, bits):
+    case = _case(s, "nhwc", I.F16)
+    t = case.tensors()
+    for k in ("x", "dy"):
+        flat = t[k].reshape(-1)
+        flat[flat.size // 2 + 5] = bits
+    t["w"].reshape(-1)[7] = bits  # channel 0
+    got = U.run_gpu(case, t, ("fwd", "dgrad"))
+    x, w, dy = U.nchw_f64(case, t)
+    cv = U.oracle_conv(case)
+    with np.errstate(invalid="ignore"):
+        refs = {"y": cv.fwd(x, w, alpha=case.alpha), "dx": cv.dgrad(dy, w, alpha=case.alpha)}
+    for k, ref in refs.items():
+        g = U.to_nchw(case, k, got[k])
+        assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.array_equal(np.isinf(g), np.isinf(ref)), k
+        ok = np.isfinite(ref)
+        assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
+
+
+def test_depthwise_mfma_largest_finite_values(nnlib, oracle_lib):
+    """The largest finite value does not count as inf."""
+    case = _case(SHAPES[2], "nhwc", I.BF16)
+    t = case.tensors()
+    t["x"].reshape(-1)[::977] = 0x7F7F
+    t["w"].reshape(-1)[:] = I.to_bits(I.from_bits(t["w"].reshape(-1), I.BF16) * 1e-3, I.BF16)
+    got = U.run_gpu(case, t, ("fwd",))
+    x, w, _ = U.nchw_f64(case, t)
+    ref = U.oracle_conv(case).fwd(x, w, alpha=case.alpha)
+    assert orc.rel_err(U.to_nchw(case, "y", got["y"]), ref) <= U.TOL[I.BF16]
