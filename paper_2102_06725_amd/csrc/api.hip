@@ -500,6 +500,18 @@ DirectParams direct_params_cl(const Geom &G, float alpha) {
     return P;
 }
 
+// Whether a pass runs on the one-launch kernel for very small convolutions
+// (one group, operands of any alignment, no workspace).
+bool tiny_shape(const Geom &G, int pass) {
+    if (G.g != 1 || dw_shape(G)) return false;
+    const int64_t lim = int64_t(1) << 24;  // elements per tensor
+    if (G.n * G.h * G.w * G.c > lim || G.n * G.p * G.q * G.k > lim || G.k * G.r * G.s * G.c > lim)
+        return false;
+    // without copies the other path is few launches
+    const bool single = G.layout == NNCONV_NHWC && fast_pass(G, (nnconv_pass)pass);
+    return tiny_pays(direct_params(G, 1.0f), pass, single);
+}
+
 // dx rows (cols) at the top / bottom (left / right) that may have filter
 // taps outside dy: row i reaches p < 0 only if i < (R-1)*dil - pad, and
 // p >= P only if i >= P*stride - pad.
@@ -1307,6 +1319,9 @@ static nnconv_status fwd_impl(const nnconv_desc *desc, const void *x, const void
             return NNCONV_ERR_UNSUPPORTED;
     }
     clear_stale_error();
+    if (tile < 0 && tiny_shape(G, 0))
+        return hip_status(launch_igemm_tiny(G.dtype, 0, direct_params(G, alpha), x, w, y, 0, 1.0f,
+                                            0, nullptr, s));
     if (dw_shape(G)) {
         if (!aligned(x, 16) || !aligned(w, 2) || !aligned(y, 16) || !aligned(ws, 16))
             return hip_status(launch_direct_fwd(G.dtype, direct_params(G, alpha), x, w, y, s));
@@ -1362,6 +1377,9 @@ static nnconv_status dgrad_impl(const nnconv_desc *desc, const void *dy, const v
             return NNCONV_ERR_UNSUPPORTED;
     }
     clear_stale_error();
+    if (tile < 0 && tiny_shape(G, 1))
+        return hip_status(launch_igemm_tiny(G.dtype, 1, direct_params(G, alpha), dy, w, dx, 0, 1.0f,
+                                            0, nullptr, s));
     if (dw_shape(G)) {
         if (!aligned(dy, 16) || !aligned(w, 2) || !aligned(dx, 16) || !aligned(ws, 16))
             return hip_status(
@@ -1453,6 +1471,9 @@ static nnconv_status wgrad_run(const Geom &G, const void *x, const void *dy, voi
     const int out_code = dw_dtype == NNCONV_F32 ? 2 : (dw_dtype == NNCONV_F16 ? 0 : 1);
     const int64_t count = G.k * G.r * G.s * G.cg;
     const int kcrs = G.layout == NNCONV_NCHW;
+    if (tiny_shape(G, 2))
+        return hip_status(launch_igemm_tiny(G.dtype, 2, direct_params(G, 1.0f), dy, x, dw, out_code,
+                                            inv_loss_scale, accumulate, overflow_flag, s));
     if (dw_shape(G) && aligned(x, 16) && aligned(dy, 16) && aligned(ws, 16))
         return dw_wgrad(G, x, dy, dw, out_code, inv_loss_scale, accumulate, overflow_flag,
                         (char *)ws, s);

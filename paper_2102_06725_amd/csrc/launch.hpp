@@ -251,6 +251,15 @@ hipError_t launch_direct_dgrad(int dtype, const DirectParams &p, const void *dy,
 hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, const void *dy,
                                float *ws, int32_t splits, hipStream_t st);
 
+// The three passes of very small convolutions, one launch each, in either
+// layout (igemm_tiny.hip): pass 0 out = y from a = x, b = w; 1 out = dx from
+// a = dy, b = w; 2 out = dw (0 fp16, 1 bf16, 2 fp32) from a = dy, b = x with the
+// loss-scale step of launch_wgrad_reduce.
+bool tiny_pays(const DirectParams &p, int pass, bool single);
+hipError_t launch_igemm_tiny(int dtype, int pass, const DirectParams &p, const void *a,
+                             const void *b, void *out, int out_code, float inv_scale,
+                             int accumulate, int32_t *flag, hipStream_t st);
+
 // Grouped convolution as super-groups of sg channels (block-diagonal
 // weights).  dst[k][t][c'] = w[k][c' - base][t] inside output channel k's
 // own group of m channels (base = ((k % sg) / m) * m), else 0; src is

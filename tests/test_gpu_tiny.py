@@ -1,0 +1,100 @@
+"""The one-launch kernel for very small convolutions against the fp64 oracle:
+16x16 tiles and 32-element steps at their edges, fewer steps than waves, both
+layouts, strides, dilation, odd channel counts, one pixel, unaligned operands,
+every output mode of backward-weight, and inf / NaN (exact patterns: taps
+outside dy have no term in backward-data)."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+import oracle.oracle as orc
+from paper_2102_06725_amd import inputs as I
+from paper_2102_06725_amd import nnconv as nc
+
+from test_gpu_padded import tiny_steps
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # name, n, c, h, w, k, r, s, stride, pad, dil
+    ("c16", 2, 16, 16, 16, 16, 3, 3, 1, 1, 1),
+    ("one", 1, 1, 1, 1, 1, 1, 1, 1, 0, 1),
+    ("c7k17", 1, 7, 5, 9, 17, 3, 3, 1, 1, 1),      # one past a tile and a chunk
+    ("c15k15", 2, 15, 4, 8, 15, 1, 1, 1, 0, 1),    # one short of them
+    ("c9k33_s2", 1, 9, 9, 7, 33, 3, 3, 2, 1, 1),
+    ("rgb_s2", 1, 3, 16, 17, 8, 5, 5, 2, 2, 1),
+    ("r1s4_s3", 2, 4, 6, 19, 12, 1, 4, 3, 1, 1),   # columns of x no output reads
+    ("dil2", 1, 8, 9, 10, 8, 3, 2, 1, 2, 2),
+    ("c40k24", 1, 40, 6, 6, 24, 3, 3, 1, 1, 1),
+]
+
+
+def _case(s, layout, dtype=I.F16):
+    name, n, c, h, w, k, r, ss, stride, pad, dil = s
+    L = I.Layer(name, n, c, h, w, k, r, ss, stride, pad, dil)
+    assert all(tiny_steps(L, p) <= 4 for p in ("fwd", "dgrad"))
+    return U.Case(L, layout=layout, dtype=dtype, loss_scale=64.0, x_kind="normal", cfg=101,
+                  layer_id=SHAPES.index(s), alpha=-1.5)
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
+def test_tiny_parity(nnlib, oracle_lib, s, layout, dtype):
+    U.full_parity(_case(s, layout, dtype))
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_tiny_unaligned(nnlib, oracle_lib, layout):
+    case = _case(SHAPES[0], layout)
+    t = case.tensors()
+    a, b = U.run_gpu(case, t), U.run_gpu(case, t, in_shift=3, out_shift=1, dw_shift=1)
+    if layout == "nchw":  # the same kernel: alignment plays no part
+        assert all(np.array_equal(a[k + "_bits"], b[k + "_bits"]) for k in ("y", "dx", "dw"))
+    x, w, dy = U.nchw_f64(case, t)
+    assert orc.rel_err(U.to_nchw(case, "y", b["y"]), U.oracle_conv(case).fwd(x, w, alpha=case.alpha)) <= U.TOL[I.F16]
+
+
+@pytest.mark.parametrize("dw_dtype", [nc.NNCONV_F32, nc.NNCONV_F16])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_tiny_backward_weight_modes(nnlib, oracle_lib, dw_dtype, accumulate):
+    case = _case(SHAPES[2], "nchw")
+    t = case.tensors()
+    rng = np.random.default_rng(5)
+    old = rng.standard_normal(17 * 7 * 9).astype(np.float32)
+    old_bits = old if dw_dtype == nc.NNCONV_F32 else I.to_bits(old, I.F16)
+    old_val = old.astype(np.float64) if dw_dtype == nc.NNCONV_F32 else I.from_bits(old_bits, I.F16)
+    flag = U.torch().zeros(1, dtype=U.torch().int32, device="cuda")
+    got = U.run_gpu(case, t, ("wgrad",), dw_dtype=dw_dtype, accumulate=accumulate, dw_old=old_bits,
+                    flag=flag)
+    x, w, dy = U.nchw_f64(case, t)
+    ref = U.oracle_conv(case).wgrad(x, dy, 1.0 / case.loss_scale)
+    if accumulate:
+        ref = ref + old_val.reshape(ref.shape)
+    assert orc.rel_err(U.to_nchw(case, "dw", got["dw"]), ref) <= U.TOL[I.F16]
+    assert int(flag.item()) == 0
+    t["dy"].reshape(-1)[11] = 0x7C00
+    U.run_gpu(case, t, ("wgrad",), dw_dtype=dw_dtype, flag=flag)
+    assert int(flag.item()) == 1
+
+
+@pytest.mark.parametrize("bits", [0x7C00, 0x7E00], ids=["inf", "nan"])
+@pytest.mark.parametrize("where", ["x", "w", "dy"])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[4], SHAPES[7]], ids=lambda s: s[0])
+def test_tiny_non_finite(nnlib, oracle_lib, s, where, bits):
+    case = _case(s, "nchw")
+    t = case.tensors()
+    flat = t[where].reshape(-1)
+    flat[flat.size // 3] = bits
+    got = U.run_gpu(case, t)
+    x, w, dy = U.nchw_f64(case, t)
+    cv = U.oracle_conv(case)
+    with np.errstate(invalid="ignore"):
+        refs = {"y": cv.fwd(x, w, alpha=case.alpha), "dx": cv.dgrad(dy, w, alpha=case.alpha),
+                "dw": cv.wgrad(x, dy, 1.0 / case.loss_scale)}
+    for k, ref in refs.items():
+        g = U.to_nchw(case, k, got[k])
+        assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.array_equal(np.isinf(g), np.isinf(ref)), k
+        ok = np.isfinite(ref)
+        if ok.any():
+            assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
