@@ -124,8 +124,9 @@ Geom sg_geom(const Geom &G) {
 // The 64-channel-slice tile for a GEMM with ncols output columns: the
 // block-diagonal variant of the 64-column tile when the weights allow it.
 C64Config pick_c64(int64_t m, int64_t ncols, int64_t red);
-C64Config pick_c64_geom(const Geom &G, int64_t m, int64_t ncols, int64_t red) {
-    const C64Config c = pick_c64(m, ncols, red);
+C64Config pick_8w(const TNParams &p, C64Config c, int64_t red);
+C64Config pick_c64_geom(const Geom &G, const TNParams &p, int64_t m, int64_t ncols, int64_t red) {
+    const C64Config c = pick_8w(p, pick_c64(m, ncols, red), red);
     return (G.diag32 && ncols == SUPER_GROUP && c == C64S_128x64) ? C64D_128x64 : c;
 }
 
@@ -727,6 +728,16 @@ int pick_wk(const TNParams &p, int64_t rows, int64_t red) {
     return pick;
 }
 
+// The 8-wave form of a 128x128 tile where it is estimated at least 5% faster
+// (up to about two tiles per CU; fitted to the same layers at batch 16 to 128).
+constexpr TileCost COST_8W = {128, 128, 4.20, 0.01014, 1.69, 0.00921};
+C64Config pick_8w(const TNParams &p, C64Config c, int64_t red) {
+    if (c != C64S_128x128 && c != C64_128x128) return c;
+    const int cus = device_cus();
+    const double big = C64_COST[c == C64S_128x128 ? 1 : 2].us(p, red, cus);
+    return 1.05 * COST_8W.us(p, red, cus) < big ? C64E_128x128 : c;
+}
+
 // Compute units of the current device (the persistent kernels launch one
 // workgroup per CU).
 int device_cus() {
@@ -839,7 +850,7 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
                 launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, st));
         }
         const C64Config cfg =
-            tile >= 0 ? (C64Config)tile : pick_c64_geom(G, p.M, G.kg, (int64_t)t * G.cg);
+            tile >= 0 ? (C64Config)tile : pick_c64_geom(G, p, p.M, G.kg, (int64_t)t * G.cg);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, G.ph > 0 || G.pw > 0, st));
     }
     return hip_status(launch_igemm_c64(G.dtype, pick_mix(p.M, G.kg, G.g, (int64_t)t * G.cg), p,
@@ -925,7 +936,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
                 launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, st));
         }
         const C64Config cfg = tile >= 0 ? (C64Config)tile
-                              : c64     ? pick_c64_geom(G, rows, G.cg, red_rows / rows)
+                              : c64     ? pick_c64_geom(G, p, rows, G.cg, red_rows / rows)
                                         : pick_mix(rows, G.cg, G.g, red_rows / rows);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
     }
@@ -950,7 +961,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             p.nphase = 1;
             p.ph[0] = phase_of(p.M, mi, mj, phh, phw, 0, t);
             const int64_t red = (int64_t)t * G.kg;
-            const C64Config cfg = G.kg % 64 == 0 ? pick_c64_geom(G, p.M, G.cg, red)
+            const C64Config cfg = G.kg % 64 == 0 ? pick_c64_geom(G, p, p.M, G.cg, red)
                                                  : pick_mix(p.M, G.cg, G.g, red);
             TRY_HIP(launch_igemm_c64(G.dtype, cfg, p, pad, st));
         }

@@ -427,7 +427,12 @@ static hipError_t launch_c64_cfg(TNParams &p, bool pad, hipStream_t st) {
 //   256x256 wide: 16 waves of 64x64, same LDS; four waves per SIMD hide
 //            the fragment-read latency better on some mid-size layers
 //   128x128: 4 waves of 64x64, 64-element slices, 2 stages (64 KB; two
-//            workgroups per CU)
+//            workgroups per CU), or 8 waves of 32x64: with about one tile per
+//            CU the second wave per SIMD is what covers the fragment reads and
+//            the barriers (128 -> 128 3x3 over 32 images of 28x28, 196 tiles:
+//            16.9 us against 22.6 single-stage; from three tiles per CU on the
+//            workgroups cover each other and it loses, 84.0 against 79.5 us on
+//            256 images)
 // Single-stage tiles, whose small LDS footprint lets 3-5 workgroups share a
 // CU and cover each other's load latency:
 //   128x128: 4 waves of 64x64 (32 KB);  128x64: 4 waves of 64x32 (24 KB),
@@ -443,6 +448,7 @@ static hipError_t launch_c64_t(C64Config cfg, TNParams &p, bool pad, hipStream_t
         case C64R_256x256: return launch_c64_cfg<T, 256, 256, 2, 2, 4, 4, false, true, 1>(p, pad, st);
         case C64R_256x128: return launch_c64_cfg<T, 256, 128, 2, 2, 4, 3, false, true, 2>(p, pad, st);
         case C64R_256x64: return launch_c64_cfg<T, 256, 64, 4, 1, 4, 4, false, true, 2>(p, pad, st);
+        case C64E_128x128: return launch_c64_cfg<T, 128, 128, 4, 2, 8, 2, false, false, 2>(p, pad, st);
         case C64M_128x64: return launch_c64_cfg<T, 128, 64, 2, 2, 8, 1, false, false, 4, true>(p, pad, st);
         case C64M2_128x128: return launch_c64_cfg<T, 128, 128, 2, 2, 8, 2, false, false, 2, true>(p, pad, st);
         case C64M_128x128: return launch_c64_cfg<T, 128, 128, 2, 2, 8, 1, false, false, 4, true>(p, pad, st);

@@ -89,6 +89,7 @@ enum C64Config { C64_256x256 = 0,   // 8 waves, 64-element slices, 2 stages
                  C64R_256x256 = 6,    // 4 waves of 128x128, 4 stages (128 KB)
                  C64R_256x128 = 7,    // 4 waves of 128x64, 3 stages (72 KB), 2 per CU
                  C64R_256x64 = 8,     // 4 waves of 64x64, 4 stages (80 KB), 2 per CU
+                 C64E_128x128 = 36,   // 8 waves of 32x64, 2 stages
                  // any cr that is a multiple of 8: single stage, and two stages
                  C64M_128x64 = 32, C64M_128x128 = 33, C64M2_128x128 = 34 };
 hipError_t launch_igemm_c64(int dtype, C64Config cfg, TNParams &p, bool pad, hipStream_t st);

@@ -83,6 +83,21 @@ MIX_SHAPES = [
 ]
 
 
+# About one 128x128 tile per CU: the 8-wave form of that tile.
+W8_SHAPES = [
+    ("k512", 31, 512, 29, 28, 120, 1, 1, 0, 1, 1),           # ragged rows and columns
+    ("k576", 15, 64, 57, 29, 136, 3, 1, 1, 1, 1),            # padded 3x3
+]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("s", W8_SHAPES, ids=[s[0] for s in W8_SHAPES])
+def test_eight_wave_tile(nnlib, oracle_lib, s, dtype):
+    name, n, c, h, w, k, r, stride, pad, dil, groups = s
+    U.full_parity(U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
+                         x_kind="normal", cfg=102, layer_id=W8_SHAPES.index(s)), passes=("fwd", "dgrad"))
+
+
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16])
 @pytest.mark.parametrize("s", MIX_SHAPES, ids=[s[0] for s in MIX_SHAPES])
 def test_mixed_tap_tiles(nnlib, oracle_lib, s, dtype):
