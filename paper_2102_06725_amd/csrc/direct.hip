@@ -173,72 +173,76 @@ struct T16 {
     int64_t rows, cols, src_ld, dst_ld, tiles_c, tiles_r;
 };
 
-// dst[b][cc][rr] = rr < rows ? src[b][rr][cc] : 0, through a 64x64 LDS tile
-// (reads coalesced along cc, writes coalesced along rr).
+// dst[b][cc][rr] = rr < rows ? src[b][rr][cc] : 0, one 64x64 tile (index t)
+// through LDS.  vr: 16-byte loads (src_ld a multiple of 8, src 16-byte
+// aligned; the last chunk of a row may hold padding columns); vw: 16-byte
+// stores (dst_ld a multiple of 8, dst aligned).  Without them 2-byte accesses,
+// all 16 of a thread in flight at once: images with an odd number of pixels
+// have one such side (256 channels x 16 images of 33x45, both sides
+// element-wise and a load per loop turn before: to channel-last 12.3 -> 10.5
+// us, back 18.0 -> 8.6).
 //
-// SCAN: also store into flags[blockIdx.x] whether any element of the tile is
-// inf or NaN (all exponent bits of expmask set).
-// One 64x64 tile (index t) of a batched transpose with 2-byte accesses (any
-// sizes and alignment).
+// For 16-byte stores a thread gathers 8 consecutive rows of one column; a
+// wave's gather touches rows 8 apart, which share banks for any row pitch that
+// keeps chunks 16-byte aligned, so chunk c of row r is stored at chunk
+// c ^ ((r >> 3) & 7).  For 2-byte stores a wave reads 64 rows of a column:
+// rows are 65 elements apart.
+//
+// SCAN: also store into flags[t] whether any element of the tile is inf or
+// NaN (all exponent bits of expmask set).
+constexpr int T16_LDS = 64 * 65 + 8;  // elements, 16-byte aligned
+
 template <bool SCAN>
-__device__ __forceinline__ void transpose16_tile(const T16 &p, int64_t t, uint16_t (*tile)[65],
-                                                 uint32_t expmask, int32_t *flags) {
-    const int64_t rows = p.rows, cols = p.cols, dst_ld = p.dst_ld;
+__device__ __forceinline__ void transpose16_tile(const T16 &p, int64_t t, bool vr, bool vw,
+                                                 uint16_t *tile, uint32_t expmask, int32_t *flags) {
     const int64_t b = t / (p.tiles_c * p.tiles_r);
     const int64_t rem = t - b * p.tiles_c * p.tiles_r;
     const int64_t tr = rem / p.tiles_c, tc = rem - (rem / p.tiles_c) * p.tiles_c;
     const int64_t r0 = tr * 64, c0 = tc * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const uint16_t *s = p.src + b * rows * p.src_ld;
-    int bad = 0;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t rr = r0 + i, cc = c0 + tx;
-        const uint16_t v = (rr < rows && cc < cols) ? s[rr * p.src_ld + cc] : (uint16_t)0;
-        tile[i][tx] = v;
-        if constexpr (SCAN) bad |= (v & expmask) == expmask;
-    }
-    if constexpr (SCAN) {
-        bad = __syncthreads_or(bad);
-        if (threadIdx.x == 0) flags[t] = bad;
-    } else {
-        __syncthreads();
-    }
-    uint16_t *d = p.dst + b * cols * dst_ld;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t cc = c0 + i, rr = r0 + tx;
-        if (cc < cols && rr < dst_ld) d[cc * dst_ld + rr] = tile[tx][i];
-    }
-}
-
-template <bool SCAN>
-__global__ __launch_bounds__(256) void transpose16_kernel(const T16 p, uint32_t expmask,
-                                                          int32_t *flags) {
-    __shared__ uint16_t tile[64][65];
-    transpose16_tile<SCAN>(p, blockIdx.x, tile, expmask, flags);
-}
-
-// One 64x64 tile (index t) of a batched transpose, 16-byte accesses.
-template <bool SCAN>
-__device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, uint16_t *tile,
-                                                     uint32_t expmask, int32_t *flags) {
-    const int64_t b = t / (p.tiles_c * p.tiles_r);
-    const int64_t rem = t - b * p.tiles_c * p.tiles_r;
-    const int64_t tr = rem / p.tiles_c, tc = rem - (rem / p.tiles_c) * p.tiles_c;
-    const int64_t r0 = tr * 64, c0 = tc * 64;
     const uint16_t *s = p.src + b * p.rows * p.src_ld;
     int bad = 0;
+    if (vr) {
+        u32x4 v[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int id = threadIdx.x + 256 * i;
-        const int row = id >> 3, cc = (id & 7) * 8;
-        const int64_t rr = r0 + row, col = c0 + cc;
-        u32x4 v = u32x4{};
-        if (rr < p.rows && col < p.cols) v = *(const u32x4 *)(s + rr * p.src_ld + col);
-        *(u32x4 *)(&tile[row * 64 + (((cc >> 3) ^ ((row >> 3) & 7)) << 3)]) = v;
-        if constexpr (SCAN) {
+        for (int i = 0; i < 2; ++i) {
+            const int id = threadIdx.x + 256 * i;
+            const int64_t rr = r0 + (id >> 3), col = c0 + (id & 7) * 8;
+            v[i] = u32x4{};
+            if (rr < p.rows && col < p.cols) v[i] = *(const u32x4 *)(s + rr * p.src_ld + col);
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                bad |= ((v[e] & expmask) == expmask) | (((v[e] >> 16) & expmask) == expmask);
+        for (int i = 0; i < 2; ++i) {
+            const int id = threadIdx.x + 256 * i;
+            const int row = id >> 3, cc = id & 7;
+            if (vw) {
+                *(u32x4 *)(&tile[row * 64 + ((cc ^ ((row >> 3) & 7)) << 3)]) = v[i];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    tile[row * 65 + cc * 8 + e] = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
+            }
+            if constexpr (SCAN) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    bad |= ((v[i][e] & expmask) == expmask) |
+                           (((v[i][e] >> 16) & expmask) == expmask);
+            }
+        }
+    } else {
+        uint16_t v[16];
+        const int64_t cc = c0 + tx;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int64_t rr = r0 + ty + 4 * i;
+            v[i] = rr < p.rows && cc < p.cols ? s[rr * p.src_ld + cc] : (uint16_t)0;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int row = ty + 4 * i;
+            tile[vw ? row * 64 + (((tx >> 3) ^ ((row >> 3) & 7)) << 3) + (tx & 7) : row * 65 + tx] =
+                v[i];
+            if constexpr (SCAN) bad |= (v[i] & expmask) == expmask;
         }
     }
     if constexpr (SCAN) {
@@ -248,52 +252,58 @@ __device__ __forceinline__ void transpose16_vec_tile(const T16 &p, int64_t t, ui
         __syncthreads();
     }
     uint16_t *d = p.dst + b * p.cols * p.dst_ld;
+    if (vw) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int id = threadIdx.x + 256 * i;
-        const int oc = id >> 3, rc = (id & 7) * 8;
-        const int64_t col = c0 + oc, rr = r0 + rc;
-        if (col < p.cols && rr < p.dst_ld) {
-            // rows rc .. rc + 7 share (r >> 3) = rc >> 3
-            const int pc = (((oc >> 3) ^ ((rc >> 3) & 7)) << 3) + (oc & 7);
-            uint32_t w[4];
+        for (int i = 0; i < 2; ++i) {
+            const int id = threadIdx.x + 256 * i;
+            const int oc = id >> 3, rc = (id & 7) * 8;
+            const int64_t col = c0 + oc, rr = r0 + rc;
+            if (col < p.cols && rr < p.dst_ld) {
+                // rows rc .. rc + 7 share (r >> 3) = rc >> 3
+                const int pc = (((oc >> 3) ^ ((rc >> 3) & 7)) << 3) + (oc & 7);
+                uint32_t w[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                w[e] = (uint32_t)tile[(rc + 2 * e) * 64 + pc] |
-                       ((uint32_t)tile[(rc + 2 * e + 1) * 64 + pc] << 16);
-            *(u32x4 *)(d + col * p.dst_ld + rr) = u32x4{w[0], w[1], w[2], w[3]};
+                for (int e = 0; e < 4; ++e)
+                    w[e] = (uint32_t)tile[(rc + 2 * e) * 64 + pc] |
+                           ((uint32_t)tile[(rc + 2 * e + 1) * 64 + pc] << 16);
+                *(u32x4 *)(d + col * p.dst_ld + rr) = u32x4{w[0], w[1], w[2], w[3]};
+            }
+        }
+    } else {
+        const int64_t rr = r0 + tx;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int64_t col = c0 + ty + 4 * i;
+            if (col < p.cols && rr < p.dst_ld) d[col * p.dst_ld + rr] = tile[tx * 65 + ty + 4 * i];
         }
     }
 }
 
-// Same transpose with 16-byte accesses on both sides (src_ld, dst_ld and rows
-// multiples of 8, 16-byte aligned buffers): a 64x64 tile is read as 8-element
-// row chunks (the last one of a row may hold padding columns), and each output chunk gathers 8 consecutive rows of one column
-// from LDS.  The gather of a wave touches rows 8 apart, which share banks
-// for any row pitch that keeps chunks 16-byte aligned, so chunk c of row r
-// is stored at chunk c ^ ((r >> 3) & 7) instead of padding the rows.
+template <bool SCAN>
+__global__ __launch_bounds__(256) void transpose16_kernel(const T16 p, int vr, int vw,
+                                                          uint32_t expmask, int32_t *flags) {
+    __shared__ __align__(16) uint16_t tile[T16_LDS];
+    transpose16_tile<SCAN>(p, blockIdx.x, vr, vw, tile, expmask, flags);
+}
+
+// Both sides 16 bytes wide.
 template <bool SCAN>
 __global__ __launch_bounds__(256) void transpose16_vec_kernel(const T16 p, uint32_t expmask,
                                                               int32_t *flags) {
     __shared__ __align__(16) uint16_t tile[64 * 64];
-    transpose16_vec_tile<SCAN>(p, blockIdx.x, tile, expmask, flags);
+    transpose16_tile<SCAN>(p, blockIdx.x, true, true, tile, expmask, flags);
 }
 
 // Two independent transposes in one launch (workgroups [0, n0) do the first,
-// the rest the second), each with 16-byte accesses where its sizes and
-// alignment allow (vec0, vec1): the layout copies on the input side of a
-// channel-first call, one launch instead of two.
+// the rest the second): the layout copies on the input side of a channel-first
+// call, one launch instead of two.  vec: bits 0, 1 of each are vr, vw.
 __global__ __launch_bounds__(256) void transpose16_pair_kernel(const T16 p0, const T16 p1,
                                                                int64_t n0, int vec0, int vec1) {
-    // 16-byte aligned: the 16-byte tile path stores whole chunks
-    __shared__ __align__(16) uint16_t tile[64][65];
+    __shared__ __align__(16) uint16_t tile[T16_LDS];
     const int64_t t = blockIdx.x;
-    const T16 &p = t < n0 ? p0 : p1;
-    const int64_t u = t < n0 ? t : t - n0;
-    if (t < n0 ? vec0 : vec1)
-        transpose16_vec_tile<false>(p, u, &tile[0][0], 0u, nullptr);
-    else
-        transpose16_tile<false>(p, u, tile, 0u, nullptr);
+    const bool first = t < n0;
+    const int vec = first ? vec0 : vec1;
+    transpose16_tile<false>(first ? p0 : p1, first ? t : t - n0, vec & 1, vec & 2, tile, 0u, nullptr);
 }
 
 // Block-diagonal super-group weights: dst[k][t][c'] (c' < sg, t < rs) is
@@ -348,10 +358,10 @@ static T16 t16(const void *src, void *dst, int64_t rows, int64_t cols, int64_t s
     return p;
 }
 
-static bool t16_vec(const void *src, const void *dst, int64_t rows, int64_t src_ld,
-                    int64_t dst_ld) {
-    return src_ld % 8 == 0 && dst_ld % 8 == 0 && rows % 8 == 0 && (uintptr_t)src % 16 == 0 &&
-           (uintptr_t)dst % 16 == 0;
+// which sides take 16-byte accesses: bit 0 loads, bit 1 stores
+static int t16_vec(const T16 &p) {
+    return (p.src_ld % 8 == 0 && (uintptr_t)p.src % 16 == 0 ? 1 : 0) |
+           (p.dst_ld % 8 == 0 && (uintptr_t)p.dst % 16 == 0 ? 2 : 0);
 }
 
 template <bool SCAN>
@@ -363,12 +373,13 @@ static hipError_t transpose16_go(const void *src, void *dst, int64_t batch, int6
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
     const T16 p = t16(src, dst, rows, cols, src_ld, dst_ld);
-    if (t16_vec(src, dst, rows, src_ld, dst_ld))
+    const int vec = t16_vec(p);
+    if (vec == 3)
         hipLaunchKernelGGL(transpose16_vec_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st, p,
                            expmask, flags);
     else
         hipLaunchKernelGGL(transpose16_kernel<SCAN>, dim3((uint32_t)nb), dim3(256), 0, st, p,
-                           expmask, flags);
+                           vec & 1, vec & 2, expmask, flags);
     return hipGetLastError();
 }
 
@@ -393,11 +404,10 @@ hipError_t launch_transpose16_pair(const void *src0, void *dst0, int64_t batch0,
         if (e != hipSuccess) return e;
         return launch_transpose16(src1, dst1, batch1, rows1, cols1, dst_ld1, st);
     }
-    hipLaunchKernelGGL(transpose16_pair_kernel, dim3((uint32_t)(n0 + n1)), dim3(256), 0, st,
-                       t16(src0, dst0, rows0, cols0, cols0, dst_ld0),
-                       t16(src1, dst1, rows1, cols1, cols1, dst_ld1), n0,
-                       (int)t16_vec(src0, dst0, rows0, cols0, dst_ld0),
-                       (int)t16_vec(src1, dst1, rows1, cols1, dst_ld1));
+    const T16 p0 = t16(src0, dst0, rows0, cols0, cols0, dst_ld0);
+    const T16 p1 = t16(src1, dst1, rows1, cols1, cols1, dst_ld1);
+    hipLaunchKernelGGL(transpose16_pair_kernel, dim3((uint32_t)(n0 + n1)), dim3(256), 0, st, p0, p1,
+                       n0, t16_vec(p0), t16_vec(p1));
     return hipGetLastError();
 }
 
@@ -667,36 +677,42 @@ hipError_t launch_interleave16(const void *src, void *dst, int64_t n, int32_t c,
 }
 
 // Weights with both channel counts padded: dst is [k_pad][rs][c_pad]
-// (CKLAST = false, the forward operand) or [rs][c_pad][k_pad] (true, the
+// (KLAST = false, the forward operand) or [rs][c_pad][k_pad] (true, the
 // backward-data operand), zero where k >= K or c >= C; element (k, c, tap)
 // of src is at k * sk + c * sc + tap * st.  flags (may be null): whether any
-// of the block's 2048 elements is inf or NaN.
+// of the block's PW_ELEMS elements is inf or NaN.  At most 2^30 elements.
+constexpr int PW_ELEMS = 512;
 template <bool KLAST>
 __global__ __launch_bounds__(256) void pad_weights16_kernel(
     const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int32_t kn, int32_t cn,
-    int32_t k_pad, int32_t c_pad, int32_t rs, int64_t sk, int64_t sc, int64_t stap,
+    FastDiv k_pad, FastDiv c_pad, FastDiv rs, uint32_t sk, uint32_t sc, uint32_t stap,
     uint32_t expmask, int32_t *flags) {
-    const int64_t count = (int64_t)k_pad * c_pad * rs;
+    const uint32_t count = k_pad.d * c_pad.d * rs.d;
+    uint16_t v[PW_ELEMS / 256];
+#pragma unroll
+    for (int u = 0; u < PW_ELEMS / 256; ++u) {
+        const uint32_t e = blockIdx.x * PW_ELEMS + u * 256 + threadIdx.x;
+        uint32_t k, c, t;
+        if constexpr (KLAST) {
+            const uint32_t f = fdiv(e, k_pad);
+            k = e - f * k_pad.d;
+            t = fdiv(f, c_pad);
+            c = f - t * c_pad.d;
+        } else {
+            const uint32_t f = fdiv(e, c_pad);
+            c = e - f * c_pad.d;
+            k = fdiv(f, rs);
+            t = f - k * rs.d;
+        }
+        v[u] = e < count && k < (uint32_t)kn && c < (uint32_t)cn ? src[k * sk + c * sc + t * stap]
+                                                                 : (uint16_t)0;
+    }
     int bad = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int64_t e = (int64_t)blockIdx.x * 2048 + u * 256 + threadIdx.x;
-        if (e >= count) break;
-        int64_t k, c, t;
-        if constexpr (KLAST) {
-            const int64_t f = e / k_pad;
-            k = e - f * k_pad;
-            t = f / c_pad;
-            c = f - t * c_pad;
-        } else {
-            const int64_t f = e / c_pad;
-            c = e - f * c_pad;
-            k = f / rs;
-            t = f - k * rs;
-        }
-        const uint16_t v = k < kn && c < cn ? src[k * sk + c * sc + t * stap] : (uint16_t)0;
-        bad |= (v & expmask) == expmask;
-        dst[e] = v;
+    for (int u = 0; u < PW_ELEMS / 256; ++u) {
+        const uint32_t e = blockIdx.x * PW_ELEMS + u * 256 + threadIdx.x;
+        if (e < count) dst[e] = v[u];
+        bad |= (v[u] & expmask) == expmask;
     }
     if (flags) {
         bad = __syncthreads_or(bad);
@@ -705,7 +721,7 @@ __global__ __launch_bounds__(256) void pad_weights16_kernel(
 }
 
 int64_t pad_weights16_blocks(int64_t k_pad, int64_t c_pad, int64_t rs) {
-    return (k_pad * c_pad * rs + 2047) / 2048;
+    return (k_pad * c_pad * rs + PW_ELEMS - 1) / PW_ELEMS;
 }
 
 hipError_t launch_pad_weights16(const void *src, void *dst, int32_t k, int32_t c, int32_t k_pad,
@@ -713,17 +729,19 @@ hipError_t launch_pad_weights16(const void *src, void *dst, int32_t k, int32_t c
                                 int32_t *flags, hipStream_t st) {
     const int64_t nb = pad_weights16_blocks(k_pad, c_pad, rs);
     if (nb <= 0) return hipSuccess;
-    if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const int64_t sk = (int64_t)c * rs, sc = kcrs ? rs : 1, stap = kcrs ? 1 : c;
+    if ((int64_t)k_pad * c_pad * rs > (int64_t(1) << 30)) return hipErrorInvalidValue;
+    const uint32_t sk = (uint32_t)(c * rs), sc = kcrs ? rs : 1, stap = kcrs ? 1 : c;
     const uint32_t em = expmask16(dtype);
+    const FastDiv dk = make_fastdiv((uint32_t)k_pad), dc = make_fastdiv((uint32_t)c_pad);
+    const FastDiv dr = make_fastdiv((uint32_t)rs);
     if (klast)
         hipLaunchKernelGGL(pad_weights16_kernel<true>, dim3((uint32_t)nb), dim3(256), 0, st,
-                           (const uint16_t *)src, (uint16_t *)dst, k, c, k_pad, c_pad, rs, sk, sc,
-                           stap, em, flags);
+                           (const uint16_t *)src, (uint16_t *)dst, k, c, dk, dc, dr, sk, sc, stap, em,
+                           flags);
     else
         hipLaunchKernelGGL(pad_weights16_kernel<false>, dim3((uint32_t)nb), dim3(256), 0, st,
-                           (const uint16_t *)src, (uint16_t *)dst, k, c, k_pad, c_pad, rs, sk, sc,
-                           stap, em, flags);
+                           (const uint16_t *)src, (uint16_t *)dst, k, c, dk, dc, dr, sk, sc, stap, em,
+                           flags);
     return hipGetLastError();
 }
 
