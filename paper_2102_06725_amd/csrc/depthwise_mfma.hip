@@ -243,6 +243,169 @@ __global__ __launch_bounds__(256) void dwm_fwd_kernel(const DWTParams P,
     }
 }
 
+// Backward-weight of the same layers (3x3 and 5x5, stride 1): partials
+// ws[split][c][r*R + s] = sum over the split's pixels of dy * x.
+//
+//   D[i, j] += sum_k dy[pixel k, channel i] * x[pixel k + tap, channel j]
+//
+// of which the diagonal i = j is the gradient: 1 of 16 products is useful, at
+// 512 a clock, and an inf or NaN cannot leave its own row and column.  Both
+// operands are pixel-major in LDS and read with the transposing reads; k runs
+// over 32 pixels, COLS columns of 32 / COLS image rows HR apart, so that one
+// x fragment (an input row, a column shift s) meets the dy fragments of all R
+// filter rows: R + 1 fragment reads feed R*R MFMAs.
+//
+// A workgroup is two pairs of waves; wave g of a pair owns 16 of the block's
+// 32 channels, and the pairs take every other block of HR * 32 / COLS rows x
+// COLS columns of the split, staged by buffer_load ... lds, rows and columns
+// outside the image as zeros.  The pairs' sums are added in order at the end.
+// 128 images of 28x28x240, 5x5: 47.7 -> 28.8 us (with the split reduction);
+// 14x14x480, 5x5: 31.8 -> 20.1; 7x7x1152, 3x3: 15.3 -> 10.7; 56x56x144, 3x3:
+// 54 -> 51 (the bytes take 47 at the copy rate).
+namespace dwm {
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+template <int R, int COLS, int HR>
+struct WBlock {
+    static constexpr int PARTS = 32 / COLS;      // row ranges of a k-step
+    static constexpr int ROWS = PARTS * HR;      // dy rows
+    static constexpr int IW = COLS + R - 1;
+    static constexpr int XP = (ROWS + R - 1) * IW, DP = ROWS * COLS;  // pixels of 64 bytes
+    static constexpr int NX = (XP * 4 + 63) / 64, ND = (DP * 4 + 63) / 64;  // 1 KB loads
+    static constexpr int BYTES = (NX + ND) * 1024;
+};
+}  // namespace dwm
+
+template <class T, int R, int COLS, int HR>
+__global__ __launch_bounds__(256) void dwm_wgrad_kernel(const DWTParams P,
+                                                        const uint16_t *__restrict__ x,
+                                                        const uint16_t *__restrict__ dy,
+                                                        float *__restrict__ ws) {
+    using namespace dwm;
+    using W = WBlock<R, COLS, HR>;
+    constexpr int RS = R * R;
+    __shared__ __align__(16) char lds[2 * W::BYTES];
+    static_assert(2 * W::BYTES >= 2 * RS * 16 * 4, "the second pair's sums");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int pair = wave >> 1, g = wave & 1;
+    const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int cb = (int)(b % (uint32_t)P.cblocks);  // 32 channels
+    const int split = (int)(b / (uint32_t)P.cblocks);
+    const int nblocks = P.n * P.tiles_h * P.tiles_w;
+    const int begin = split * P.tiles_per_split;
+    const int end = min(nblocks, begin + P.tiles_per_split);
+
+    const i32x4 rx = desc_of(x, P.in_bytes);
+    const i32x4 rdy = desc_of(dy, P.dy_bytes);
+    const uint32_t lx = (uint32_t)(uintptr_t)(lds_void *)&lds[0] + (uint32_t)(pair * W::BYTES);
+    const uint32_t ld = lx + W::NX * 1024u;
+    const int c2 = P.c * 2;
+    const int cvl = lane & 3;
+    const bool ch_ok = cb * 4 + cvl < P.c8;
+    const uint32_t ch_ofs = (uint32_t)(cb * 4 + cvl) * 16u;
+
+    auto stage = [&](int t) {
+        const bool live = t < end;
+        const int tw = t % P.tiles_w;
+        const int t2 = t / P.tiles_w;
+        const int th = t2 % P.tiles_h;
+        const int n = t2 / P.tiles_h;
+        const int p0 = th * W::ROWS, q0 = tw * COLS;
+        const int h0 = p0 - P.ph, w0 = q0 - P.pw;
+#pragma unroll
+        for (int j0 = 0; j0 < W::NX; j0 += 2) {
+            const int j = j0 + g;
+            const int px = j * 16 + (lane >> 2);
+            const int row = px / W::IW, col = px - row * W::IW;
+            const int h = h0 + row, wc = w0 + col;
+            const bool ok = live && ch_ok && px < W::XP && (unsigned)h < (unsigned)P.ih &&
+                            (unsigned)wc < (unsigned)P.iw;
+            if (j < W::NX)
+                dma16(lx + (uint32_t)j * 1024u,
+                      ok ? (uint32_t)((n * P.ih + h) * P.iw + wc) * (uint32_t)c2 + ch_ofs : OOB_OFFSET,
+                      rx);
+        }
+#pragma unroll
+        for (int j0 = 0; j0 < W::ND; j0 += 2) {
+            const int j = j0 + g;
+            const int px = j * 16 + (lane >> 2);
+            const int row = px / COLS, col = px - row * COLS;
+            const int p = p0 + row, q = q0 + col;
+            const bool ok = live && ch_ok && px < W::DP && p < P.oh && q < P.ow;
+            if (j < W::ND)
+                dma16(ld + (uint32_t)j * 1024u,
+                      ok ? (uint32_t)((n * P.oh + p) * P.ow + q) * (uint32_t)c2 + ch_ofs : OOB_OFFSET,
+                      rdy);
+        }
+    };
+
+    // transposing reads: lane group gq holds pixels 8 gq .. 8 gq + 7 of the
+    // k-step, four per read; lane li addresses pixel li / 4, channels 4 (li % 4)
+    const int li = lane & 15, gq = lane >> 4;
+    const int k0 = 8 * gq + (li >> 2);
+    const int rpart = k0 / COLS, rcol = k0 % COLS;
+    const uint32_t xa = lx + (uint32_t)((rpart * HR * W::IW + rcol) * 64 + g * 32 + (li & 3) * 8);
+    const uint32_t da = ld + (uint32_t)((rpart * HR * COLS + rcol) * 64 + g * 32 + (li & 3) * 8);
+    auto frag = [&](uint32_t a) -> u32x4 {
+        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a);
+        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)(a + 256));
+        const u32x2 lo = __builtin_bit_cast(u32x2, v0), hi = __builtin_bit_cast(u32x2, v1);
+        return u32x4{lo[0], lo[1], hi[0], hi[1]};
+    };
+
+    f32x4 acc[R][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int s = 0; s < R; ++s) acc[r][s] = f32x4{};
+
+    for (int t0 = begin; t0 < end; t0 += 2) {
+        if (t0 > begin) barrier_lds();  // the previous blocks have been read
+        stage(t0 + pair);
+        wait_vmcnt<0>();
+        barrier_lds();
+        u32x4 df[HR];
+#pragma unroll
+        for (int h = 0; h < HR + R - 1; ++h) {
+            u32x4 xf[R];
+#pragma unroll
+            for (int s = 0; s < R; ++s) xf[s] = frag(xa + (uint32_t)((h * W::IW + s) * 64));
+            if (h < HR) df[h] = frag(da + (uint32_t)(h * COLS * 64));
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (h - r >= 0 && h - r < HR)
+#pragma unroll
+                    for (int s = 0; s < R; ++s) acc[r][s] = mfma16<T>(df[h - r], xf[s], acc[r][s]);
+        }
+    }
+
+    // the diagonal: lane (channel li as column) of group li / 4, element li % 4
+    barrier_lds();
+    float *other = (float *)&lds[0] + g * (RS * 16);
+    const bool mine = gq == (li >> 2);
+    float v[RS];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            const f32x4 a = acc[r][s];
+            v[r * R + s] = (li & 2) ? ((li & 1) ? a[3] : a[2]) : ((li & 1) ? a[1] : a[0]);
+        }
+    if (pair == 1 && mine) {
+#pragma unroll
+        for (int t = 0; t < RS; ++t) other[t * 16 + li] = v[t];
+    }
+    barrier_lds();
+    const int ch = cb * 32 + g * 16 + li;
+    if (pair == 0 && mine && ch < P.c) {
+        float *o = ws + ((int64_t)split * P.c + ch) * RS;
+#pragma unroll
+        for (int t = 0; t < RS; ++t) o[t] = v[t] + other[t * 16 + li];
+    }
+}
+
 namespace {
 
 constexpr int strip_rows(int r) { return r <= 5 ? 14 : 7; }
@@ -324,6 +487,64 @@ hipError_t launch_depthwise_mfma(int dtype, const DWTParams &q, int r, bool flip
                     : launch_dwm_t<Half, false>(q, r, in, w, out, st);
     return flip ? launch_dwm_t<BFloat, true>(q, r, in, w, out, st)
                 : launch_dwm_t<BFloat, false>(q, r, in, w, out, st);
+}
+
+namespace {
+
+// Blocks of the backward-weight kernel: 16 columns x 14 rows, or 8 x 8 for
+// images up to 8 wide.
+template <class T, int R, int COLS, int HR>
+hipError_t launch_dwm_wgrad_cfg(DWTParams q, const void *x, const void *dy, float *ws,
+                                hipStream_t st) {
+    const int64_t nb = (int64_t)q.cblocks * q.splits;
+    if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dwm_wgrad_kernel<T, R, COLS, HR>), dim3((uint32_t)nb), dim3(256), 0, st, q,
+                       (const uint16_t *)x, (const uint16_t *)dy, ws);
+    return hipGetLastError();
+}
+
+template <class T, int R>
+hipError_t launch_dwm_wgrad_r(const DWTParams &q, const void *x, const void *dy, float *ws,
+                              hipStream_t st) {
+    if (q.ow <= 8) return launch_dwm_wgrad_cfg<T, R, 8, 2>(q, x, dy, ws, st);
+    return launch_dwm_wgrad_cfg<T, R, 16, 7>(q, x, dy, ws, st);
+}
+
+}  // namespace
+
+// About 1024 workgroups, no more splits than the LDS-tiled kernel would write
+// (the workspace does not grow), at least two blocks each; below 96 workgroups
+// that kernel's smaller tiles spread better (480 channels, 14x14, 3x3 on one
+// image: both 7.0 us; 16 images 8.6 against 6.8).
+int32_t depthwise_mfma_wgrad_plan(const DWParams &p, int32_t max_splits, DWTParams *q) {
+    if (p.sh != 1 || p.sw != 1 || (p.r != 3 && p.r != 5)) return 0;
+    const int rows = p.q <= 8 ? 8 : 14, cols = p.q <= 8 ? 8 : 16;
+    const int th = (p.p + rows - 1) / rows, tw = (p.q + cols - 1) / cols;
+    const int64_t blocks = (int64_t)p.n * th * tw;
+    const int cblocks = (p.c + 31) / 32;
+    int64_t splits = 1024 / cblocks;
+    if (splits > blocks / 2) splits = blocks / 2;  // two blocks at a time
+    if (splits > max_splits) splits = max_splits;
+    if (splits < 1 || splits * cblocks < 96) return 0;
+    const int64_t per = (blocks + splits - 1) / splits;
+    splits = (blocks + per - 1) / per;
+    if (q) {
+        q->cblocks = cblocks;
+        q->tiles_h = th;
+        q->tiles_w = tw;
+        q->tiles_per_split = (int32_t)per;
+        q->splits = (int32_t)splits;
+    }
+    return (int32_t)splits;
+}
+
+hipError_t launch_depthwise_mfma_wgrad(int dtype, int r, const DWTParams &q, const void *x,
+                                       const void *dy, float *ws, hipStream_t st) {
+    if (dtype == Half::id)
+        return r == 3 ? launch_dwm_wgrad_r<Half, 3>(q, x, dy, ws, st)
+                      : launch_dwm_wgrad_r<Half, 5>(q, x, dy, ws, st);
+    return r == 3 ? launch_dwm_wgrad_r<BFloat, 3>(q, x, dy, ws, st)
+                  : launch_dwm_wgrad_r<BFloat, 5>(q, x, dy, ws, st);
 }
 
 }  // namespace nnconv

@@ -721,6 +721,16 @@ hipError_t launch_wgrad_rs(const DWParams &p, const DWWgPlan &pl, const void *x,
 template <class T>
 hipError_t launch_wgrad_t(const DWParams &p, const void *x, const void *dy, float *ws, hipStream_t st) {
     const DWWgPlan pl = plan_wgrad(p);
+    DWTParams m;
+    memset(&m, 0, sizeof(m));
+    m.n = p.n; m.c = p.c; m.c8 = p.c8;
+    m.ih = p.h; m.iw = p.w; m.oh = p.p; m.ow = p.q;
+    m.ph = p.ph; m.pw = p.pw;
+    m.in_bytes = p.x_bytes; m.dy_bytes = p.dy_bytes;
+    if (depthwise_mfma_wgrad_plan(p, pl.splits, &m) > 0) {
+        if (m.splits != p.splits) return hipErrorInvalidValue;
+        return launch_depthwise_mfma_wgrad(T::id, p.r, m, x, dy, ws, st);
+    }
     if (p.sh == 1) {
         switch (p.r) {
             case 3: return launch_wgrad_rs<T, 3, 1>(p, pl, x, dy, ws, st);
@@ -746,7 +756,11 @@ bool dw_tiled(const DWParams &p, int pass) {
     return p.sh == 1 || p.sh == 2;
 }
 
-int32_t dw_tiled_wgrad_splits(const DWParams &p) { return plan_wgrad(p).splits; }
+int32_t dw_tiled_wgrad_splits(const DWParams &p) {
+    const int32_t s = plan_wgrad(p).splits;
+    const int32_t m = depthwise_mfma_wgrad_plan(p, s, nullptr);
+    return m > 0 ? m : s;
+}
 
 hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const void *a, const void *b,
                                   void *out, hipStream_t st) {

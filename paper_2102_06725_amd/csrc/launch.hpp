@@ -374,6 +374,13 @@ bool depthwise_mfma_pays(const DWTParams &p, int r);
 hipError_t launch_depthwise_mfma(int dtype, const DWTParams &p, int r, bool flip, const void *in,
                                  const void *w, void *out, hipStream_t st);
 
+// Backward-weight on the matrix cores (3x3 and 5x5, stride 1): the number of
+// splits (at most max_splits), or 0 where the LDS-tiled kernel runs it; fills
+// q's tiling when q is given.
+int32_t depthwise_mfma_wgrad_plan(const DWParams &p, int32_t max_splits, DWTParams *q);
+hipError_t launch_depthwise_mfma_wgrad(int dtype, int r, const DWTParams &q, const void *x,
+                                       const void *dy, float *ws, hipStream_t st);
+
 // Training-step pieces (update.hip).  The state type is the C ABI's.
 hipError_t launch_loss_scaler_init(nnconv_loss_scaler *s, float scale, float factor,
                                    int32_t interval, hipStream_t st);

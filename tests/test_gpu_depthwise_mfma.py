@@ -73,3 +73,41 @@ def test_depthwise_mfma_largest_finite_values(nnlib, oracle_lib):
     x, w, _ = U.nchw_f64(case, t)
     ref = U.oracle_conv(case).fwd(x, w, alpha=case.alpha)
     assert orc.rel_err(U.to_nchw(case, "y", got["y"]), ref) <= U.TOL[I.BF16]
+
+
+# backward-weight: at least 96 workgroups of (32 channels, split)
+WG_SHAPES = [
+    ("w8_3x3", 40, 136, 8, 8, 3, 1),       # 8x8 blocks, 5 channel blocks, 8 channels past the end
+    ("w5_5x5", 30, 264, 9, 5, 5, 2),       # ragged columns, two row blocks
+    ("w14_5x5", 40, 200, 14, 14, 5, 2),    # 16x14 blocks
+    ("w17_3x3", 24, 136, 15, 17, 3, 0),    # padding 0: 13x15 outputs
+    ("w33_5x5", 20, 72, 17, 33, 5, 4),     # padding R-1: 21x37 outputs, ragged both ways
+]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("s", WG_SHAPES, ids=[s[0] for s in WG_SHAPES])
+def test_depthwise_mfma_backward_weight(nnlib, oracle_lib, s, dtype):
+    name, n, c, h, w, r, pad = s
+    L = I.Layer(name, n, c, h, w, c, r, r, 1, pad, groups=c)
+    case = U.Case(L, dtype=dtype, loss_scale=256.0, x_kind="normal", cfg=103, layer_id=WG_SHAPES.index(s))
+    U.full_parity(case, passes=("wgrad",))
+    t = case.tensors()
+    a, b = (U.run_gpu(case, t, ("wgrad",)) for _ in range(2))
+    assert np.array_equal(a["dw_bits"], b["dw_bits"])
+
+
+def test_depthwise_mfma_backward_weight_non_finite(nnlib, oracle_lib):
+    """An inf in one channel of dy leaves the other channels' gradients alone."""
+    name, n, c, h, w, r, pad = WG_SHAPES[2]
+    case = U.Case(I.Layer(name, n, c, h, w, c, r, r, 1, pad, groups=c), x_kind="normal", cfg=103, layer_id=2)
+    t = case.tensors()
+    t["dy"].reshape(-1, c)[777, 33] = 0x7C00
+    flag = U.torch().zeros(1, dtype=U.torch().int32, device="cuda")
+    g = U.run_gpu(case, t, ("wgrad",), flag=flag)["dw"].reshape(c, r * r)
+    x, w_, dy = U.nchw_f64(case, t)
+    with np.errstate(invalid="ignore"):
+        ref = U.oracle_conv(case).wgrad(x, dy).reshape(c, r * r)
+    assert np.array_equal(np.isfinite(g), np.isfinite(ref)) and int(flag.item()) == 1
+    ok = np.isfinite(ref)
+    assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
