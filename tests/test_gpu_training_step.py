@@ -247,3 +247,35 @@ def test_training_steps_with_injected_overflow():
         assert np.max(np.abs(gw - rw)) <= err_w + 1e-12, step
         assert np.array_equal(w16.cpu().numpy().view(np.uint16), I.to_bits(gw, I.F16))
     assert ref.skipped == 1
+
+
+@pytest.mark.parametrize("count", [4, 1020, 2044, 2048, 2052, 6148])
+def test_update_vector_tail_and_skip(nnlib, count):
+    """Two vectors per thread: counts around a workgroup's 2048 elements, and a
+    set flag that leaves every array as it was although its loads are issued."""
+    import torch
+    from paper_2102_06725_amd import nnconv as nc
+    g = torch.Generator().manual_seed(count)
+    pad = 64
+    host = [torch.randn(count + pad, generator=g) for _ in range(3)]
+    master, mom, grad = (h.cuda() for h in host)
+    w16 = torch.full((count + pad,), 7.0, dtype=torch.float16, device="cuda")
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+
+    def step():
+        nc.check(nc.nnconv_sgd_update(count, master.data_ptr(), mom.data_ptr(), w16.data_ptr(), nc.NNCONV_F16,
+                                      grad.data_ptr(), None, flag.data_ptr(), 0.5, 0.75, 0.125, st))
+
+    flag.fill_(1)
+    step()
+    assert torch.equal(master.cpu(), host[0]) and torch.equal(mom.cpu(), host[1]) and torch.all(w16 == 7.0)
+    flag.zero_()
+    step()
+    m = (0.75 * host[1].double() + host[2].double() + 0.125 * host[0].double())[:count]
+    w = host[0][:count].double() - 0.5 * m
+    # each fp32 operation rounds once: at most 4 of them on values below 16
+    assert torch.allclose(mom[:count].cpu().double(), m, rtol=0, atol=4 * 16 * 2.0 ** -24)
+    assert torch.allclose(master[:count].cpu().double(), w, rtol=0, atol=6 * 16 * 2.0 ** -24)
+    assert torch.equal(w16[:count], master[:count].half())
+    assert torch.equal(master[count:].cpu(), host[0][count:]) and torch.all(w16[count:] == 7.0)
