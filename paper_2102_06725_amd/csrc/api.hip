@@ -770,12 +770,32 @@ TNPhase phase_of(int64_t m, int64_t mi, int64_t mj, int64_t oi_add, int64_t oj_a
 bool c64_fwd_shape(const Geom &G) { return !stem_shape(G) && G.cg % 64 == 0; }
 bool c64_dgrad_shape(const Geom &G) { return G.kg % 64 == 0 && G.sh * G.sw <= MAX_PHASES; }
 
+// Weights that a pass has to re-lay (backward-data), expand (super-groups) or
+// both before its GEMM.  Most tiles read the result from `wt`, which make()
+// queues; the register-weight halo tiles pack their fragments straight from
+// the caller's weights (raw) instead.  nflags: the non-finite flags written.
+struct WeightPrep {
+    hipError_t (*make)(const Geom &G, const WeightPrep &p, hipStream_t st);
+    const void *w;
+    void *wexp, *wt;
+    int32_t *flags;
+    int64_t make_flags, nflags;
+    PackSource raw;
+};
+hipError_t make_weights(const Geom &G, WeightPrep *p, hipStream_t st) {
+    if (!p) return hipSuccess;
+    p->nflags = p->make_flags;
+    return p->make(G, *p, st);
+}
+
 // tile: a C64Config to force on the 64-channel-slice kernel, or -1 for the
 // per-shape pick.
 // pack: workspace for the register-weight halo tiles' packed weights
 // (hring_ws bytes), or null when the call has none.
+// prep: the caller's weights, when `w` has still to be made from them.
 nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, float alpha,
-                       hipStream_t st, int tile = -1, void *pack = nullptr) {
+                       hipStream_t st, int tile = -1, void *pack = nullptr,
+                       WeightPrep *prep = nullptr) {
     if (stem_shape(G)) {
         StemParams sp;
         sp.x = x;
@@ -839,16 +859,20 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
     p.nphase = 1;
     p.ph[0] = phase_of(p.M, p.mi, p.mj, 0, 0, 0, t);
     const int wc = tile < 0 ? pick_wk(p, p.M, (int64_t)t * G.cg) : -1;
+    const int hc = wc >= 0 || G.cg % 64 != 0 ? -1
+                   : halo_tile(tile)         ? tile - HALO_TILE0
+                   : tile < 0                ? pick_halo(p, pack != nullptr)
+                                             : -1;
+    if (hc >= 0 && (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack)))
+        return NNCONV_ERR_UNSUPPORTED;
+    const PackSource *raw = prep && hc >= 0 && hring_cfg(hc) ? &prep->raw : nullptr;
+    if (!raw) TRY_HIP(make_weights(G, prep, st));
     if (wc >= 0)
         return hip_status(launch_igemm_wk(G.dtype, (WKConfig)wc, p, G.ph > 0 || G.pw > 0, st));
     if (G.cg % 64 == 0) {
-        const int hc = halo_tile(tile) ? tile - HALO_TILE0 : tile < 0 ? pick_halo(p, pack != nullptr) : -1;
-        if (hc >= 0) {
-            if (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack))
-                return NNCONV_ERR_UNSUPPORTED;
+        if (hc >= 0)
             return hip_status(
-                launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, st));
-        }
+                launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, raw, st));
         const C64Config cfg =
             tile >= 0 ? (C64Config)tile : pick_c64_geom(G, p, p.M, G.kg, (int64_t)t * G.cg);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, G.ph > 0 || G.pw > 0, st));
@@ -861,7 +885,8 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
 // output phase (h mod sigma_h, w mod sigma_w): within a phase every pixel
 // sees the same set of contributing taps.  wt is [g][R][S][Cg][Kg].
 nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx, float alpha,
-                         hipStream_t st, int tile = -1, void *pack = nullptr) {
+                         hipStream_t st, int tile = -1, void *pack = nullptr,
+                         WeightPrep *prep = nullptr) {
     TNParams base = tn_base();
     base.a = dy;
     base.a_bytes = (uint32_t)(G.n * G.p * G.q * G.k * 2);
@@ -926,20 +951,29 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
         }
         if (p.nphase == 0) return NNCONV_OK;
         const int wc = tile < 0 ? pick_wk(p, rows, red_rows / rows) : -1;
-        if (wc >= 0) return hip_status(launch_igemm_wk(G.dtype, (WKConfig)wc, p, pad, st));
         const bool c64 = G.kg % 64 == 0;
-        const int hc = !c64 ? -1 : halo_tile(tile) ? tile - HALO_TILE0 : tile < 0 ? pick_halo(p, pack != nullptr) : -1;
-        if (hc >= 0) {
-            if (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack))
-                return NNCONV_ERR_UNSUPPORTED;
-            return hip_status(
-                launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, st));
+        const int hc = wc >= 0 || !c64   ? -1
+                       : halo_tile(tile) ? tile - HALO_TILE0
+                       : tile < 0        ? pick_halo(p, pack != nullptr)
+                                         : -1;
+        if (hc >= 0 && (!halo_cfg_supported(p, (HaloConfig)hc) || (hring_cfg(hc) && !pack)))
+            return NNCONV_ERR_UNSUPPORTED;
+        if (hc >= 0 && hring_cfg(hc) && prep) {
+            prep->nflags = hring_pack_blocks(p.ncols, p.cr, p.groups);
+            return hip_status(launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0,
+                                                &prep->raw, st));
         }
+        TRY_HIP(make_weights(G, prep, st));
+        if (wc >= 0) return hip_status(launch_igemm_wk(G.dtype, (WKConfig)wc, p, pad, st));
+        if (hc >= 0)
+            return hip_status(
+                launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, nullptr, st));
         const C64Config cfg = tile >= 0 ? (C64Config)tile
                               : c64     ? pick_c64_geom(G, p, rows, G.cg, red_rows / rows)
                                         : pick_mix(rows, G.cg, G.g, red_rows / rows);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
     }
+    TRY_HIP(make_weights(G, prep, st));
     // Otherwise sigma_h * sigma_w launches, one per output phase (h mod
     // sigma_h, w mod sigma_w): within a phase every pixel sees the same set of
     // contributing taps.  wt is [g][R][S][Cg][Kg].
@@ -1114,18 +1148,49 @@ nnconv_status dw_wgrad(const Geom &G, const void *x, const void *dy, void *dw, i
                                           (int32_t)(G.r * G.s), st));
 }
 
+// The weights of a super-grouped pass (G: the super-groups) from the caller's.
+WeightPrep sg_prep(const Geom &G, const void *w, char *ws, const Regions &R, bool dgrad) {
+    WeightPrep p;
+    memset(&p, 0, sizeof(p));
+    const bool kcrs = G.layout == NNCONV_NCHW;
+    p.w = w;
+    p.wexp = ws + R.d;
+    p.wt = ws + R.b;
+    p.raw.w = (const uint16_t *)w;
+    p.raw.sk = (int32_t)(G.cg * G.r * G.s);
+    p.raw.sc = kcrs ? (int32_t)(G.r * G.s) : 1;
+    p.raw.st = kcrs ? 1 : (int32_t)G.cg;
+    p.raw.dgrad = dgrad;
+    p.raw.m = (int32_t)G.cg;
+    p.raw.kg = (int32_t)SUPER_GROUP;
+    p.raw.tap_elems = (int32_t)(dgrad ? SUPER_GROUP * SUPER_GROUP : SUPER_GROUP);
+    p.raw.expmask = 0xFFFFFFFFu;  // no flags
+    return p;
+}
+
+hipError_t expand_weights(const Geom &S, const WeightPrep &p, hipStream_t st) {
+    return launch_expand_group_weights(p.w, p.wexp, S.k, (int32_t)(S.r * S.s), p.raw.m,
+                                       (int32_t)SUPER_GROUP, p.raw.st == 1, st);
+}
+
+// [g][Kg][R*S*Cg] -> [g][R*S*Cg][Kg] for the super-groups
+hipError_t expand_relay_weights(const Geom &S, const WeightPrep &p, hipStream_t st) {
+    const hipError_t e = expand_weights(S, p, st);
+    if (e != hipSuccess) return e;
+    return launch_transpose16(p.wexp, p.wt, S.g, S.kg, S.r * S.s * S.cg, S.kg, st);
+}
+
 nnconv_status sg_fwd(const Geom &G, const void *x, const void *w, void *y, float alpha,
                      char *ws, hipStream_t st) {
     const Geom S = sg_geom(G);
     const Regions R = sg_regions(G, NNCONV_FWD);
-    void *wexp = ws + R.d;
-    TRY_HIP(launch_expand_group_weights(w, wexp, G.k, (int32_t)(G.r * G.s), (int32_t)G.cg,
-                                        (int32_t)SUPER_GROUP, G.layout == NNCONV_NCHW, st));
+    WeightPrep prep = sg_prep(G, w, ws, R, false);
+    prep.make = expand_weights;
     void *pack = hring_ws(S, NNCONV_FWD) > 0 ? ws + R.f : nullptr;
-    if (G.layout == NNCONV_NHWC) return fwd_fast(S, x, wexp, y, alpha, st, -1, pack);
+    if (G.layout == NNCONV_NHWC) return fwd_fast(S, x, prep.wexp, y, alpha, st, -1, pack, &prep);
     void *xt = ws + R.a, *yt = ws + R.c;
     TRY_HIP(launch_transpose16(x, xt, G.n, G.c, G.h * G.w, G.c, st));
-    nnconv_status s = fwd_fast(S, xt, wexp, yt, alpha, st, -1, pack);
+    nnconv_status s = fwd_fast(S, xt, prep.wexp, yt, alpha, st, -1, pack, &prep);
     if (s != NNCONV_OK) return s;
     return hip_status(launch_transpose16(yt, y, G.n, G.p * G.q, G.k, G.p * G.q, st));
 }
@@ -1134,16 +1199,13 @@ nnconv_status sg_dgrad(const Geom &G, const void *dy, const void *w, void *dx, f
                        char *ws, hipStream_t st) {
     const Geom S = sg_geom(G);
     const Regions R = sg_regions(G, NNCONV_DGRAD);
-    void *wexp = ws + R.d, *wt = ws + R.b;
-    TRY_HIP(launch_expand_group_weights(w, wexp, G.k, (int32_t)(G.r * G.s), (int32_t)G.cg,
-                                        (int32_t)SUPER_GROUP, G.layout == NNCONV_NCHW, st));
-    // [g][Kg][R*S*Cg] -> [g][R*S*Cg][Kg] for the super-groups
-    TRY_HIP(launch_transpose16(wexp, wt, S.g, S.kg, S.r * S.s * S.cg, S.kg, st));
+    WeightPrep prep = sg_prep(G, w, ws, R, true);
+    prep.make = expand_relay_weights;
     void *pack = hring_ws(S, NNCONV_DGRAD) > 0 ? ws + R.f : nullptr;
-    if (G.layout == NNCONV_NHWC) return dgrad_fast(S, dy, wt, dx, alpha, st, -1, pack);
+    if (G.layout == NNCONV_NHWC) return dgrad_fast(S, dy, prep.wt, dx, alpha, st, -1, pack, &prep);
     void *dyt = ws + R.a, *dxt = ws + R.c;
     TRY_HIP(launch_transpose16(dy, dyt, G.n, G.k, G.p * G.q, G.k, st));
-    nnconv_status s = dgrad_fast(S, dyt, wt, dxt, alpha, st, -1, pack);
+    nnconv_status s = dgrad_fast(S, dyt, prep.wt, dxt, alpha, st, -1, pack, &prep);
     if (s != NNCONV_OK) return s;
     return hip_status(launch_transpose16(dxt, dx, G.n, G.h * G.w, G.c, G.h * G.w, st));
 }
@@ -1370,6 +1432,11 @@ NNCONV_API nnconv_status nnconv_fwd_tile(const nnconv_desc *desc, const void *x,
     return fwd_impl(desc, x, w, y, alpha, ws, ws_bytes, hip_stream, tile);
 }
 
+static hipError_t relay_weights(const Geom &G, const WeightPrep &p, hipStream_t st) {
+    return launch_transpose16_scan(p.w, p.wt, G.g, G.kg, G.r * G.s * G.cg, G.kg, G.dtype, p.flags,
+                                   st);
+}
+
 static nnconv_status dgrad_impl(const nnconv_desc *desc, const void *dy, const void *w,
                                 void *dx, float alpha, void *ws, size_t ws_bytes,
                                 void *hip_stream, int tile) {
@@ -1423,18 +1490,30 @@ static nnconv_status dgrad_impl(const nnconv_desc *desc, const void *dy, const v
         dxn = base + R.c;
     }
     // [g][Kg][R*S*Cg] -> [g][R*S*Cg][Kg], noting any inf or NaN weight
-    int32_t *flags = (int32_t *)(base + R.e);
-    TRY_HIP(launch_transpose16_scan(wkrsc, wt, G.g, G.kg, G.r * G.s * G.cg, G.kg, G.dtype, flags,
-                                    s));
+    WeightPrep prep;
+    memset(&prep, 0, sizeof(prep));
+    prep.make = relay_weights;
+    prep.w = wkrsc;
+    prep.wt = wt;
+    prep.flags = (int32_t *)(base + R.e);
+    prep.make_flags = transpose16_blocks(G.g, G.r * G.s * G.cg, G.kg);
+    prep.raw.w = (const uint16_t *)wkrsc;
+    prep.raw.sk = (int32_t)(G.r * G.s * G.cg);
+    prep.raw.sc = 1;
+    prep.raw.st = (int32_t)G.cg;
+    prep.raw.dgrad = 1;
+    prep.raw.kg = (int32_t)G.kg;
+    prep.raw.tap_elems = (int32_t)(G.cg * G.kg);
+    prep.raw.flags = prep.flags;
+    prep.raw.expmask = G.dtype == NNCONV_F16 ? 0x7C00u : 0x7F80u;
     void *pack = hring_ws(G, NNCONV_DGRAD) > 0 ? base + R.f : nullptr;
-    if ((st = dgrad_fast(G, dyn, wt, dxn, alpha, s, tile, pack)) != NNCONV_OK) return st;
+    if ((st = dgrad_fast(G, dyn, wt, dxn, alpha, s, tile, pack, &prep)) != NNCONV_OK) return st;
     // the implicit-GEMM kernels read dy zero-extended at every tap of a
     // stride phase: recompute the border pixels from the definition when a
     // weight is inf or NaN (with finite weights the kernel exits at once)
     const Border B = dgrad_border(G);
-    TRY_HIP(launch_dgrad_border(G.dtype, direct_params_cl(G, alpha), dyn, w, dxn, flags,
-                                (int32_t)transpose16_blocks(G.g, G.r * G.s * G.cg, G.kg), B.bt,
-                                B.bb, B.bl, B.br, s));
+    TRY_HIP(launch_dgrad_border(G.dtype, direct_params_cl(G, alpha), dyn, w, dxn, prep.flags,
+                                (int32_t)prep.nflags, B.bt, B.bb, B.bl, B.br, s));
     if (G.layout == NNCONV_NCHW)
         return hip_status(launch_transpose16(dxn, dx, G.n, G.h * G.w, G.c, G.h * G.w, s));
     return NNCONV_OK;

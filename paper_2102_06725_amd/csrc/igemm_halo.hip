@@ -325,8 +325,8 @@ bool halo_cfg_supported(const TNParams &p, HaloConfig cfg) {
 }
 
 hipError_t launch_igemm_halo(int dtype, HaloConfig cfg, TNParams &p, void *pack, bool diag32,
-                             hipStream_t st) {
-    if (hring_config(cfg)) return launch_igemm_hring(dtype, cfg, p, pack, diag32, st);
+                             const PackSource *src, hipStream_t st) {
+    if (hring_config(cfg)) return launch_igemm_hring(dtype, cfg, p, pack, diag32, src, st);
     if (dtype == Half::id) return launch_halo_t<Half>(cfg, p, st);
     return launch_halo_t<BFloat>(cfg, p, st);
 }

@@ -133,19 +133,34 @@ bool halo_cfg_supported(const TNParams &p, HaloConfig cfg);
 // the per-tap 64x64 weight blocks are block-diagonal in 32x32 blocks
 // (super-groups of groups of at most 32 channels); the single-slice tile then
 // skips the zero blocks, the others ignore it.
+struct PackSource;
 hipError_t launch_igemm_halo(int dtype, HaloConfig cfg, TNParams &p, void *pack, bool diag32,
-                             hipStream_t st);
+                             const PackSource *src, hipStream_t st);
 // The register-weight halo tiles (igemm_hring.hip) take 3x3 filters (9
 // taps) only, HALO_R256x64S a single 64-channel slice (cr == 64) too, and
 // it alone more than one group (each of 64 output columns).  They read the
 // B operand packed in fragment order: `pack` is caller-provided device
 // memory of hring_pack_bytes(ncols, cr, groups) bytes, which
 // launch_igemm_hring fills from p.b before the GEMM.
+// With src they are packed straight from the caller's weights, without the
+// re-laid (backward-data) or block-diagonal (super-group) copy in p.b.
 constexpr int HRING_TAPS = 9;
+struct PackSource {
+    const uint16_t *w;      // element (k, c, tap) at k * sk + c * sc + tap * st
+    int32_t sk, sc, st;
+    int32_t dgrad;          // columns are channels and the reduction filters
+    int32_t m;              // channels per group within a 64-channel super-group, 0: dense
+    int32_t kg;             // filters per (super-)group
+    int32_t tap_elems;      // p.taps.boff of tap 1
+    int32_t *flags;         // null, or per block whether it met an inf or NaN
+    uint32_t expmask;       // all exponent bits of the operand type
+};
+// blocks of the packing launch with a source: the flags it writes
+int64_t hring_pack_blocks(int64_t ncols, int64_t cr, int64_t groups);
 bool hring_supported(const TNParams &p, int span, bool grouped = false);
 size_t hring_pack_bytes(int64_t ncols, int64_t cr, int64_t groups = 1);
 hipError_t launch_igemm_hring(int dtype, HaloConfig cfg, TNParams &p, void *pack, bool diag32,
-                              hipStream_t st);
+                              const PackSource *src, hipStream_t st);
 
 // Forward pass for 8-channel (16-byte) channel-last pixels, 64 output
 // channels, groups 1, dilation 1 and a compiled filter size / stride (the
