@@ -119,6 +119,20 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks) {
     return base + i;
 }
 
+// Group and rest of a renumbered workgroup id: groups outermost (one XCD then
+// keeps to few groups and their weights), or innermost (it reads whole pixel
+// rows): the host chooses with group_inner().
+__device__ __forceinline__ void split_group(int id, int per_g, int groups, int inner, int &g,
+                                            int &rem) {
+    if (inner) {
+        rem = id / groups;
+        g = id - rem * groups;
+    } else {
+        g = id / per_g;
+        rem = id - g * per_g;
+    }
+}
+
 // LDS row swizzle for tiles of 8 x 16-byte chunks per row: logical chunk c
 // of row r lives at physical chunk c ^ swz(r).  Consecutive rows read at the
 // same logical chunk, and rows 8 apart written at the same logical chunk,

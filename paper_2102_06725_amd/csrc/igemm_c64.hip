@@ -100,9 +100,8 @@ void igemm_c64_kernel(const TNParams P) {
     const int phase_blocks =
         (phi + 1 < P.nphase ? P.ph[phi + 1].block_start : (int)gridDim.x) - F.block_start;
     const int local = (int)xcd_remap(blockIdx.x - F.block_start, phase_blocks);
-    const int per_g = F.tiles_m * P.tiles_n;
-    const int g = local / per_g;
-    const int rem = local - g * per_g;
+    int g, rem;
+    split_group(local, F.tiles_m * P.tiles_n, P.groups, P.group_inner, g, rem);
     const int tm = rem / P.tiles_n;
     const int tn = rem - tm * P.tiles_n;
     const int m0 = tm * BM, n0 = tn * BN;

@@ -82,12 +82,11 @@ void igemm_hring_kernel(const TNParams P) {
     const int l32 = lane & 31, khalf = lane >> 5;
 
     const TNPhase &F = P.ph[0];
-    // group, then column tile outer: the workgroups of one XCD (consecutive
-    // local ids) share the column tile's packed weights in that XCD's L2
+    // column tile outer: the workgroups of one XCD (consecutive local ids)
+    // share the column tile's packed weights in that XCD's L2
     const int local = (int)xcd_remap(blockIdx.x, gridDim.x);
-    const int per_g = F.tiles_m * P.tiles_n;
-    const int g = local / per_g;
-    const int rem = local - g * per_g;
+    int g, rem;
+    split_group(local, F.tiles_m * P.tiles_n, P.groups, P.group_inner, g, rem);
     const int tn = rem / F.tiles_m;
     const int tm = rem - tn * F.tiles_m;
     const int m0 = tm * BM, n0 = tn * BN;

@@ -70,9 +70,8 @@ __global__ __launch_bounds__(NW * 64) void igemm_wk_kernel(const TNParams P) {
     // row tiles fastest: the tiles of one column block, which share its
     // weights, run on one XCD
     const int local = (int)xcd_remap(blockIdx.x - F.block_start, phase_blocks);
-    const int per_g = F.tiles_m * P.tiles_n;
-    const int g = local / per_g;
-    const int rem = local - g * per_g;
+    int g, rem;
+    split_group(local, F.tiles_m * P.tiles_n, P.groups, P.group_inner, g, rem);
     const int tn = rem / F.tiles_m;
     const int tm = rem - tn * F.tiles_m;
     const int m0 = tm * BM, n0 = tn * BN;

@@ -67,6 +67,7 @@ struct TNParams {
     int32_t oi_mul, oi_add, oj_mul, oj_add;
     float alpha;
     int32_t groups;
+    int32_t group_inner;  // workgroup order: groups innermost
     int32_t diag32;  // igemm_wk only: 64x64 weight blocks, block-diagonal in 32x32 blocks
     int32_t tiles_m, tiles_n;  // per group; filled by the launcher
     TapTable taps;
@@ -205,6 +206,7 @@ struct WGParams {
     int32_t sh, sw, ph, pw, dh, dw;
     int32_t rscg;
     int32_t groups, splits, pix_per_split;
+    int32_t group_inner;        // workgroup order: groups inside the splits
     int32_t tiles_m, tiles_n;   // filled by the launcher
 };
 

@@ -77,14 +77,13 @@ void wgrad_splitk_kernel(const WGParams P) {
     const int wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
 
-    // tile: groups x splits x m-tiles x n-tiles, n fastest
+    // tile: groups x splits (or splits x groups) x m-tiles x n-tiles, n fastest
     const uint32_t lid = xcd_remap(blockIdx.x, gridDim.x);
     const int per_split = P.tiles_m * P.tiles_n;
-    const int per_g = per_split * P.splits;
-    const int g = (int)lid / per_g;
-    int rem = (int)lid - g * per_g;
-    const int split = rem / per_split;
-    rem -= split * per_split;
+    const int range = (int)lid / per_split;
+    const int rem = (int)lid - range * per_split;
+    int g, split;
+    split_group(range, P.splits, P.groups, P.group_inner, g, split);
     const int tm = rem / P.tiles_n;
     const int tn = rem - tm * P.tiles_n;
     const int k0 = tm * BM, j0 = tn * BN;
