@@ -249,7 +249,8 @@ __global__ __launch_bounds__(256) void dwm_fwd_kernel(const DWTParams P,
 //   D[i, j] += sum_k dy[pixel k, channel i] * x[pixel k + tap, channel j]
 //
 // of which the diagonal i = j is the gradient: 1 of 16 products is useful, at
-// 512 a clock, and an inf or NaN cannot leave its own row and column.  Both
+// 512 a clock, and an inf or NaN cannot leave its own row and column (nor its
+// own taps: sums that are not finite are taken again from the definition).  Both
 // operands are pixel-major in LDS and read with the transposing reads; k runs
 // over 32 pixels, COLS columns of 32 / COLS image rows HR apart, so that one
 // x fragment (an input row, a column shift s) meets the dy fragments of all R
@@ -399,10 +400,46 @@ __global__ __launch_bounds__(256) void dwm_wgrad_kernel(const DWTParams P,
     }
     barrier_lds();
     const int ch = cb * 32 + g * 16 + li;
-    if (pair == 0 && mine && ch < P.c) {
-        float *o = ws + ((int64_t)split * P.c + ch) * RS;
+    const bool store = pair == 0 && mine && ch < P.c;
+    bool bad = false;
+    if (store) {
 #pragma unroll
-        for (int t = 0; t < RS; ++t) o[t] = v[t] + other[t * 16 + li];
+        for (int t = 0; t < RS; ++t) {
+            v[t] += other[t * 16 + li];
+            bad |= !__builtin_isfinite(v[t]);
+        }
+    }
+    if (!__syncthreads_or(bad)) {
+        if (store) {
+            float *o = ws + ((int64_t)split * P.c + ch) * RS;
+#pragma unroll
+            for (int t = 0; t < RS; ++t) o[t] = v[t];
+        }
+        return;
+    }
+    // The zeros staged for dy past the last output row and column have met x
+    // pixels inside the image: an inf among those is no term of the tap's sum.
+    // The workgroup's sums again, from the terms of the definition.
+    for (int e = tid; e < 32 * RS; e += 256) {
+        const int c = cb * 32 + e / RS, t = e % RS, r = t / R, s = t % R;
+        if (c >= P.c) continue;
+        float sum = 0.f;
+        for (int k = begin; k < end; ++k) {
+            const int tw = k % P.tiles_w, t2 = k / P.tiles_w;
+            const int th = t2 % P.tiles_h, n = t2 / P.tiles_h;
+            const int p1 = min(P.oh, (th + 1) * W::ROWS), q1 = min(P.ow, (tw + 1) * COLS);
+            for (int p = th * W::ROWS; p < p1; ++p)
+                for (int q = tw * COLS; q < q1; ++q) {
+                    const int h = p - P.ph + r, wc = q - P.pw + s;
+                    const float xv =
+                        (unsigned)h < (unsigned)P.ih && (unsigned)wc < (unsigned)P.iw
+                            ? from16<T>(x[(((int64_t)n * P.ih + h) * P.iw + wc) * P.c + c])
+                            : 0.f;
+                    sum = __builtin_fmaf(
+                        from16<T>(dy[(((int64_t)n * P.oh + p) * P.ow + q) * P.c + c]), xv, sum);
+                }
+        }
+        ws[((int64_t)split * P.c + c) * RS + t] = sum;
     }
 }
 

@@ -111,3 +111,22 @@ def test_depthwise_mfma_backward_weight_non_finite(nnlib, oracle_lib):
     assert np.array_equal(np.isfinite(g), np.isfinite(ref)) and int(flag.item()) == 1
     ok = np.isfinite(ref)
     assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
+
+
+@pytest.mark.parametrize("pixel", [(13, 23), (12, 15), (8, 22)], ids=["corner", "last_row", "last_cols"])
+@pytest.mark.parametrize("r", [3, 5])
+def test_depthwise_mfma_backward_weight_non_finite_input(nnlib, oracle_lib, r, pixel):
+    """An inf in x counts for the taps that read it only: blocks of 14 rows x 16
+    columns reach past the 14x24 outputs, where dy has no pixels."""
+    n, c, h, w = 24, 136, 14, 24
+    case = U.Case(I.Layer("w24", n, c, h, w, c, r, r, 1, r // 2, groups=c), x_kind="normal", cfg=103, layer_id=r)
+    t = case.tensors()
+    t["x"].reshape(n, h, w, c)[n // 2, pixel[0], pixel[1], 35] = 0x7C00
+    g = U.run_gpu(case, t, ("wgrad",))["dw"].reshape(c, r * r)
+    x, _, dy = U.nchw_f64(case, t)
+    with np.errstate(invalid="ignore"):
+        ref = U.oracle_conv(case).wgrad(x, dy).reshape(c, r * r)
+    assert not np.isfinite(ref[35]).all() and np.isfinite(np.delete(ref, 35, 0)).all()
+    assert np.array_equal(np.isfinite(g), np.isfinite(ref))
+    ok = np.isfinite(ref)
+    assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
