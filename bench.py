@@ -231,12 +231,12 @@ def stored_traffic(kind="mfma"):
         return None
 
 
-FWD_KERNEL = re.compile(r"nnconv::(igemm|stem_fwd|dw_fwd|dwt_fwd|pack_hring)")
+FWD_KERNEL = re.compile(r"nnconv::(igemm|stem_fwd|dw_fwd|dwt_fwd|dwm_fwd|pack_hring)")
 
 
 def _main_fwd_kernel(n):
     return "nnconv::" in n and ("igemm" in n or "stem_fwd" in n or "dw_fwd" in n or
-                                "dwt_fwd" in n)
+                                "dwt_fwd" in n or "dwm_fwd" in n)
 
 
 def _opens_call(prev):
