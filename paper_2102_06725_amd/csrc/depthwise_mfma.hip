@@ -261,8 +261,7 @@ __global__ __launch_bounds__(256) void dwm_fwd_kernel(const DWTParams P,
 // COLS columns of the split, staged by buffer_load ... lds, rows and columns
 // outside the image as zeros.  The pairs' sums are added in order at the end.
 // 128 images of 28x28x240, 5x5: 47.7 -> 28.8 us (with the split reduction);
-// 14x14x480, 5x5: 31.8 -> 20.1; 7x7x1152, 3x3: 15.3 -> 10.7; 56x56x144, 3x3:
-// 54 -> 51 (the bytes take 47 at the copy rate).
+// 14x14x480, 5x5: 31.8 -> 20.1; 7x7x1152, 3x3: 15.3 -> 10.7.
 namespace dwm {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -512,8 +511,12 @@ hipError_t launch_dwm_t(const DWTParams &q, int r, const void *in, const void *w
 // 6.0 us there against 6.7 here, 128 images 14.6 against 13.3; 5x5: 16 images
 // 7.0 against 8.3, 32 9.0 against 8.8; 1152 channels, 7x7, 3x3, 128 images 9.4
 // against 10.7).
-bool depthwise_mfma_pays(const DWTParams &q, int r) {
-    if (r == 3 && q.ow <= 8) return false;
+// Wide 3x3 images in fp16 stay there too: they are at the HBM rate on either
+// kernel, and its blocks of up to 64 channels touch fewer partial lines (three
+// passes, vector -> matrix cores: 96 channels, 112x112, 128
+// images 413 -> 527 us; 144 channels, 56x56 186 -> 211).
+bool depthwise_mfma_pays(int dtype, const DWTParams &q, int r) {
+    if (r == 3 && (q.ow <= 8 || (q.ow > 16 && dtype == Half::id))) return false;
     return plan(q, r).wgs >= (r == 3 ? 512 : 256);
 }
 
@@ -555,6 +558,7 @@ hipError_t launch_dwm_wgrad_r(const DWTParams &q, const void *x, const void *dy,
 // image: both 7.0 us; 16 images 8.6 against 6.8).
 int32_t depthwise_mfma_wgrad_plan(const DWParams &p, int32_t max_splits, DWTParams *q) {
     if (p.sh != 1 || p.sw != 1 || (p.r != 3 && p.r != 5)) return 0;
+    if (p.r == 3 && p.q > 16) return 0;  // wide images: as for the forward pass
     const int rows = p.q <= 8 ? 8 : 14, cols = p.q <= 8 ? 8 : 16;
     const int th = (p.p + rows - 1) / rows, tw = (p.q + cols - 1) / cols;
     const int64_t blocks = (int64_t)p.n * th * tw;
