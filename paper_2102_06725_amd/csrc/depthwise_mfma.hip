@@ -18,8 +18,7 @@
 // The zeros off the diagonal must not meet an inf or NaN of another channel
 // (0 * inf = NaN): the staging checks every element, and a workgroup whose
 // tile holds one computes it on the vector ALUs, channel by channel.
-// 128 images of 28x28x240, 5x5: bf16 61.5 -> 29.5 us, fp16 39 -> 29.5; 56x56x144,
-// 3x3: bf16 65 -> 44, fp16 56 -> 47.
+// 128 images of 28x28x240, 5x5: bf16 61.5 -> 29.5 us, fp16 39 -> 29.5.
 #include <cstring>
 
 #include "launch.hpp"
@@ -483,7 +482,9 @@ template <class T, int R, bool FLIP>
 hipError_t launch_dwm_rs(const DWTParams &q, const void *in, const void *w, void *out,
                          hipStream_t st) {
     constexpr int TR = strip_rows(R);
-    switch (plan(q, R).cfg) {
+    // 3x3: 9 to 16 wide only (depthwise_mfma_pays)
+    if constexpr (R == 3) return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
+    else switch (plan(q, R).cfg) {
         case 0: return launch_dwm_cfg<T, R, 4, 1, 8, 4, FLIP>(q, in, w, out, st);
         case 1: return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
         case 2: return launch_dwm_cfg<T, R, 1, 4, 8, TR, FLIP>(q, in, w, out, st);
@@ -511,12 +512,12 @@ hipError_t launch_dwm_t(const DWTParams &q, int r, const void *in, const void *w
 // 6.0 us there against 6.7 here, 128 images 14.6 against 13.3; 5x5: 16 images
 // 7.0 against 8.3, 32 9.0 against 8.8; 1152 channels, 7x7, 3x3, 128 images 9.4
 // against 10.7).
-// Wide 3x3 images in fp16 stay there too: they are at the HBM rate on either
-// kernel, and its blocks of up to 64 channels touch fewer partial lines (three
-// passes, vector -> matrix cores: 96 channels, 112x112, 128
-// images 413 -> 527 us; 144 channels, 56x56 186 -> 211).
-bool depthwise_mfma_pays(int dtype, const DWTParams &q, int r) {
-    if (r == 3 && (q.ow <= 8 || (q.ow > 16 && dtype == Half::id))) return false;
+// Wide 3x3 images stay there too: they are near the HBM rate on either kernel,
+// and its blocks of up to 64 channels touch fewer partial lines (three passes,
+// 128 images, vector -> matrix cores: 96 channels, 112x112, fp16 413 -> 527 us,
+// bf16 453 -> 530; 144 channels, 56x56, fp16 186 -> 211, bf16 208 both).
+bool depthwise_mfma_pays(const DWTParams &q, int r) {
+    if (r == 3 && (q.ow <= 8 || q.ow > 16)) return false;
     return plan(q, r).wgs >= (r == 3 ? 512 : 256);
 }
 

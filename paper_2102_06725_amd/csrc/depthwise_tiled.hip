@@ -777,7 +777,7 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
         q.ih = p.h; q.iw = p.w; q.oh = p.p; q.ow = p.q;
         q.ph = p.ph; q.pw = p.pw;
         q.in_bytes = p.x_bytes;
-        if (p.sh == 1 && depthwise_mfma_pays(dtype, q, p.r))
+        if (p.sh == 1 && depthwise_mfma_pays(q, p.r))
             return launch_depthwise_mfma(dtype, q, p.r, false, a, b, out, st);
         if (dtype == Half::id) return launch_fwd_t<Half, false>(q, p.r, p.sh, a, b, out, st);
         return launch_fwd_t<BFloat, false>(q, p.r, p.sh, a, b, out, st);
@@ -794,7 +794,7 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
     }
     // stride 1: dy -> dx with the rotated filter
     q.ph = p.r - 1 - p.ph; q.pw = p.s - 1 - p.pw;
-    if (depthwise_mfma_pays(dtype, q, p.r))
+    if (depthwise_mfma_pays(q, p.r))
         return launch_depthwise_mfma(dtype, q, p.r, true, a, b, out, st);
     if (dtype == Half::id) return launch_fwd_t<Half, true>(q, p.r, 1, a, b, out, st);
     return launch_fwd_t<BFloat, true>(q, p.r, 1, a, b, out, st);

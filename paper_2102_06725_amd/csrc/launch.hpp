@@ -387,7 +387,7 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
 // forward correlation with the rotated filter (flip: backward-data); the input
 // and output images, padding and byte sizes are set in p.
 // whether it is the faster kernel for this launch
-bool depthwise_mfma_pays(int dtype, const DWTParams &p, int r);
+bool depthwise_mfma_pays(const DWTParams &p, int r);
 hipError_t launch_depthwise_mfma(int dtype, const DWTParams &p, int r, bool flip, const void *in,
                                  const void *w, void *out, hipStream_t st);
 
