@@ -219,9 +219,10 @@ __global__ __launch_bounds__(stem::FWD_WAVES * 64, 1) void stem_fwd_kernel(const
 // consecutive pixels per lane; the transposing LDS read supplies them: for dy
 // a 4-pixel x 16-channel block per 16 lanes, for the patch 4 pixels x
 // (2 taps x 8 channels), since consecutive output pixels of a tile row are
-// consecutive patch entries.  Patch entries outside the receptive field of
-// the tile's in-range output pixels are loaded as zeros, so pixels past the
-// output edge (whose dy rows are zero) add exact zeros.
+// consecutive patch entries.  In a tile that reaches past the output edge the
+// rows there are left out, and the patch operand of the columns there is
+// masked: their dy is staged as zeros, which must not meet an inf or NaN pixel
+// that only further taps of the in-range outputs read.
 namespace stem {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -241,9 +242,19 @@ __device__ __forceinline__ u32x4 pack_tr(s16x4 v0, s16x4 v1) {
     r[3] = (uint32_t)(uint16_t)v1[2] | ((uint32_t)(uint16_t)v1[3] << 16);
     return r;
 }
+
+// Mask of a fragment's 8 consecutive pixels that keeps the first n.
+__device__ __forceinline__ u32x4 keep_pixels(int n) {
+    u32x4 m;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        m[d] = (2 * d < n ? 0xFFFFu : 0u) | (2 * d + 1 < n ? 0xFFFF0000u : 0u);
+    return m;
+}
 }  // namespace stem
 
-template <class T, int R, int S, int SH, int SW>
+// EDGE: P or Q is no multiple of 16.
+template <class T, int R, int S, int SH, int SW, bool EDGE>
 __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(const StemParams P, float *part) {
     using namespace stem;
     using G = Geo<R, S, SH, SW>;
@@ -262,6 +273,10 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
     const int tiles_q = (P.q + TW - 1) / TW, tiles_p = (P.p + TH - 1) / TH;
     const int per_img = tiles_p * tiles_q;
     const int total = P.n * per_img;
+
+    // rows and columns of the tile inside the output
+    auto tile_rows = [&](int tile) { return min(TH, P.p - tile % per_img / tiles_q * TH); };
+    auto tile_cols = [&](int tile) { return min(TW, P.q - tile % per_img % tiles_q * TW); };
 
     if (tid == 0) lds[2 * BUF_ENT] = u32x4{};
 
@@ -336,8 +351,11 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
         if (next < total) load_tile(next, buf ^ 1);
         const uint32_t pb = lds0 + (uint32_t)(buf * BUF_ENT) * 16u;
         const uint32_t db = pb + (uint32_t)G::P_ENT * 16u;
+        const int vh = EDGE ? tile_rows(tile) : TH;
+        const u32x4 keep = EDGE ? keep_pixels(tile_cols(tile) - pix_half) : u32x4{};
 #pragma unroll
         for (int row = 0; row < TH; ++row) {   // one k16 step = one tile row of 16 pixels
+            if (EDGE && row >= vh) break;
             u32x4 fa[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -362,7 +380,8 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
                     }
                     const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a0);
                     const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a1);
-                    const u32x4 fb = pack_tr(v0, v1);
+                    u32x4 fb = pack_tr(v0, v1);
+                    if constexpr (EDGE) fb &= keep;
 #pragma unroll
                     for (int i = 0; i < 2; ++i) acc[c][i] = mfma32<T>(fa[i], fb, acc[c][i]);
                 }
@@ -559,7 +578,7 @@ __global__ __launch_bounds__(stem::FWD_WAVES * 64, 1) void stem_fwd4_kernel(cons
 // waves 4-7 do the same for the odd tile rows, so each k-step's dy
 // fragments are read by four waves only, and the workgroup writes two
 // partials (even and odd rows), part[2 * blockIdx.x + half].
-template <class T>
+template <class T, bool EDGE>
 __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(const StemParams P,
                                                                             float *part) {
     using namespace stem;
@@ -577,15 +596,15 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
     const int tiles_q = (P.q + TW - 1) / TW, tiles_p = (P.p + TH - 1) / TH;
     const int per_img = tiles_p * tiles_q;
     const int total = P.n * per_img;
+    auto tile_rows = [&](int tile) { return min(TH, P.p - tile % per_img / tiles_q * TH); };
+    auto tile_cols = [&](int tile) { return min(TW, P.q - tile % per_img % tiles_q * TW); };
 
     auto load_tile = [&](int tile, int b) {
         const int n = tile / per_img;
         const int rem = tile - n * per_img;
         const int tp = rem / tiles_q, tq = rem - tp * tiles_q;
         const int vh = min(TH, P.p - tp * TH), vw = min(TW, P.q - tq * TW);
-        // patch entries of the receptive field of the in-range outputs (the
-        // others load as zeros: their dy rows are zero, and an inf or NaN
-        // input there must not reach the sums)
+        // patch entries of the receptive field of the in-range outputs
         const int prv = (vh - 1) * 2 + 7, jcv = vw + 3;
         const int ih0 = tp * TH * 2 - P.ph, col0 = tq * TW * 2 - P.pw - 1;
         const uint32_t pb = lds0 + (uint32_t)(b * BUF_ENT) * 16u;
@@ -643,9 +662,12 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
         if (next < total) load_tile(next, buf ^ 1);
         const uint32_t pb = lds0 + (uint32_t)(buf * BUF_ENT) * 16u;
         const uint32_t db = pb + (uint32_t)P4_ENT * 16u;
+        const int vh = EDGE ? tile_rows(tile) : TH;
+        const u32x4 keep = EDGE ? keep_pixels(tile_cols(tile) - 8 * (g >> 1)) : u32x4{};
 #pragma unroll
         for (int rr = 0; rr < TH / 2; ++rr) {   // one k16 step = one tile row of 16 pixels
             const int row = 2 * rr + half;
+            if (EDGE && row >= vh) break;
             u32x4 fa[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -664,7 +686,8 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
                     const uint32_t a0 = pb + (uint32_t)((2 * row + r) * P4_ROWB + (2 * src_px + b_slot) * 8);
                     const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)a0);
                     const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)(a0 + 64));
-                    const u32x4 fb = pack_tr(v0, v1);
+                    u32x4 fb = pack_tr(v0, v1);
+                    if constexpr (EDGE) fb &= keep;
 #pragma unroll
                     for (int i = 0; i < 2; ++i) acc[c][i] = mfma32<T>(fa[i], fb, acc[c][i]);
                 }
@@ -711,26 +734,28 @@ bool stem4_supported(const StemParams &p) {
     return stem_fwd_supported(p.r, p.s, p.sh, p.sw) && p.pw % 2 == 1 && p.w % 2 == 0;
 }
 
+template <class T, bool EDGE>
+static hipError_t launch_stem_wgrad_t(const StemParams &p, float *part, int splits, hipStream_t st) {
+    if (p.c == 4)
+        hipLaunchKernelGGL((stem_wgrad4_kernel<T, EDGE>), dim3(splits / 2), dim3(stem::WG4_WAVES * 64), 0,
+                           st, p, part);
+    else
+        hipLaunchKernelGGL((stem_wgrad_kernel<T, 7, 7, 2, 2, EDGE>), dim3(splits),
+                           dim3(stem::WG_WAVES * 64), 0, st, p, part);
+    return hipGetLastError();
+}
+
 hipError_t launch_stem_wgrad(int dtype, const StemParams &p, float *part, int splits,
                              hipStream_t st) {
-    if (p.c == 4) {
-        if (!stem4_supported(p) || splits < 2 || splits % 2 != 0) return hipErrorInvalidValue;
-        if (dtype == Half::id)
-            hipLaunchKernelGGL(stem_wgrad4_kernel<Half>, dim3(splits / 2), dim3(stem::WG4_WAVES * 64), 0,
-                               st, p, part);
-        else
-            hipLaunchKernelGGL(stem_wgrad4_kernel<BFloat>, dim3(splits / 2), dim3(stem::WG4_WAVES * 64),
-                               0, st, p, part);
-        return hipGetLastError();
-    }
-    if (!stem_fwd_supported(p.r, p.s, p.sh, p.sw) || splits < 1) return hipErrorInvalidValue;
+    if (p.c == 4 ? !stem4_supported(p) || splits < 2 || splits % 2 != 0
+                 : !stem_fwd_supported(p.r, p.s, p.sh, p.sw) || splits < 1)
+        return hipErrorInvalidValue;
+    const bool edge = p.p % stem::TH != 0 || p.q % stem::TW != 0;
     if (dtype == Half::id)
-        hipLaunchKernelGGL((stem_wgrad_kernel<Half, 7, 7, 2, 2>), dim3(splits), dim3(stem::WG_WAVES * 64), 0, st, p,
-                           part);
-    else
-        hipLaunchKernelGGL((stem_wgrad_kernel<BFloat, 7, 7, 2, 2>), dim3(splits), dim3(stem::WG_WAVES * 64), 0, st,
-                           p, part);
-    return hipGetLastError();
+        return edge ? launch_stem_wgrad_t<Half, true>(p, part, splits, st)
+                    : launch_stem_wgrad_t<Half, false>(p, part, splits, st);
+    return edge ? launch_stem_wgrad_t<BFloat, true>(p, part, splits, st)
+                : launch_stem_wgrad_t<BFloat, false>(p, part, splits, st);
 }
 
 hipError_t launch_stem_fwd(int dtype, const StemParams &p, int cus, hipStream_t st) {

@@ -91,7 +91,11 @@ __device__ __forceinline__ u32x4 tr_frag(uint32_t a0, uint32_t a1) {
 // blockIdx.y of 64 channels.  DIAG: block-diagonal 32x32 gradient blocks
 // (super-groups of groups of at most 32 channels): a wave computes only the
 // 32-row half of the output channels that matches its 32 input channels.
-template <class T, int WAVES, int NBUF, bool DIAG>
+// EDGE: the image's height is no multiple of RB.  The k-steps past the image's
+// last row are left out, and the input fragments of a k-step across it are
+// masked: dy is staged as zeros there, which must not meet an inf or NaN of the
+// last input row.
+template <class T, int WAVES, int NBUF, bool DIAG, bool EDGE>
 __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHParams P) {
     using namespace wgh;
     static_assert(WAVES == 4 || WAVES == 8, "tap groups");
@@ -226,8 +230,10 @@ __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHPara
     for (int t = 0; t < 9; ++t) toff[t] = __builtin_amdgcn_readfirstlane(tap_off(t));
 
     // the k-steps of one staged block, taps T0 .. T0 + NT - 1
-    auto block = [&](const uint32_t base, auto t0c, auto ntc) {
+    // (of the block's first `valid` pixels)
+    auto block = [&](const uint32_t base, const int valid, auto t0c, auto ntc) {
         constexpr int T0 = decltype(t0c)::value, NT = decltype(ntc)::value;
+        const int ksn = EDGE ? (valid + 15) >> 4 : ksteps;
         // the fragments of k-step ks: NI of dy (the wave's 32-row halves of
         // the output channels), one of the staged input per tap
         auto read = [&](int ks, u32x4 (&fa)[NI], u32x4 (&fb)[NT]) {
@@ -241,6 +247,15 @@ __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHPara
             asm volatile("" : "+v"(x0), "+v"(x1));
 #pragma unroll
             for (int t = 0; t < NT; ++t) fb[t] = tr_frag(x0 + toff[T0 + t], x1 + toff[T0 + t]);
+            if (EDGE && valid < ks * 16 + 16) {
+                const int n = valid - ks * 16 - 8 * (gq >> 1);  // of the lane's 8 pixels
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const uint32_t keep = (2 * d < n ? 0xFFFFu : 0u) | (2 * d + 1 < n ? 0xFFFF0000u : 0u);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) fb[t][d] &= keep;
+                }
+            }
         };
         // each k-step's fragments are read before the previous k-step's
         // matrix-core instructions issue (the fences keep that order and
@@ -249,9 +264,9 @@ __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHPara
         read(0, fa[0], fb[0]);
 #pragma unroll
         for (int ks = 0; ks < MAXKS; ++ks) {
-            if (ks < ksteps) {
+            if (ks < ksn) {
                 const int cur = ks & 1;
-                if (ks + 1 < MAXKS && ks + 1 < ksteps) read(ks + 1, fa[cur ^ 1], fb[cur ^ 1]);
+                if (ks + 1 < MAXKS && ks + 1 < ksn) read(ks + 1, fa[cur ^ 1], fb[cur ^ 1]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
@@ -278,20 +293,21 @@ __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHPara
         const bool ahead = b + AHEAD < b_end;
         if (ahead) stage(b + AHEAD, buf == 0 ? NBUF - 1 : buf - 1);
         const uint32_t base = lds0 + (uint32_t)buf * buf_bytes;
+        const int valid = EDGE ? min(npix, (H - b % P.blocks_per_img * RB) * W) : npix;
         if constexpr (NG == 2) {
             if (tg == 0)
-                block(base, std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
+                block(base, valid, std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
             else
-                block(base, std::integral_constant<int, 5>{}, std::integral_constant<int, 4>{});
+                block(base, valid, std::integral_constant<int, 5>{}, std::integral_constant<int, 4>{});
         } else {
             if (tg == 0)
-                block(base, std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+                block(base, valid, std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
             else if (tg == 1)
-                block(base, std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
+                block(base, valid, std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
             else if (tg == 2)
-                block(base, std::integral_constant<int, 5>{}, std::integral_constant<int, 2>{});
+                block(base, valid, std::integral_constant<int, 5>{}, std::integral_constant<int, 2>{});
             else
-                block(base, std::integral_constant<int, 7>{}, std::integral_constant<int, 2>{});
+                block(base, valid, std::integral_constant<int, 7>{}, std::integral_constant<int, 2>{});
         }
         // block b + 1 has landed (later ones may still be in flight), and no
         // wave reads block b any more
@@ -326,29 +342,30 @@ int wgh_slots(int rb, int w) {
     return (dys + (rb + 2) * (w + 2) * wgh::CHUNKS + 63) & ~63;
 }
 
+// 8 waves and 3 buffers: on the 56x56 layer at batch 256, 86 us against
+// 87 with 2 buffers and 117-120 with 4 waves (one per SIMD does not hide
+// the transposing reads' latency)
+template <class T, bool EDGE>
+static hipError_t launch_wgh(const WGHParams &p, hipStream_t st) {
+    constexpr int WV = 8, NB = 3;
+    const dim3 grid((uint32_t)p.splits, (uint32_t)p.groups);
+    if (p.diag32)
+        hipLaunchKernelGGL((wgrad_halo_kernel<T, WV, NB, true, EDGE>), grid, dim3(WV * 64), 0, st, p);
+    else
+        hipLaunchKernelGGL((wgrad_halo_kernel<T, WV, NB, false, EDGE>), grid, dim3(WV * 64), 0, st, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_wgrad_halo(int dtype, const WGHParams &p, hipStream_t st) {
     if (p.rb < 1 || p.w < 1 || p.rb * p.w > wgh::MAXP || (p.rb * p.w) % 16 != 0 ||
         wgh_slots(p.rb, p.w) > WGH_MAX_SLOTS || p.blocks_per_split < 1 || p.splits < 1 ||
         p.groups < 1 || p.groups > 65535 || p.c_stride < 64 * p.groups ||
         p.k_stride < 64 * p.groups)
         return hipErrorInvalidValue;
-    // 8 waves and 3 buffers: on the 56x56 layer at batch 256, 86 us against
-    // 87 with 2 buffers and 117-120 with 4 waves (one per SIMD does not hide
-    // the transposing reads' latency)
-    constexpr int WV = 8, NB = 3;
-    const dim3 grid((uint32_t)p.splits, (uint32_t)p.groups);
-    if (dtype == Half::id) {
-        if (p.diag32)
-            hipLaunchKernelGGL((wgrad_halo_kernel<Half, WV, NB, true>), grid, dim3(WV * 64), 0, st, p);
-        else
-            hipLaunchKernelGGL((wgrad_halo_kernel<Half, WV, NB, false>), grid, dim3(WV * 64), 0, st, p);
-    } else {
-        if (p.diag32)
-            hipLaunchKernelGGL((wgrad_halo_kernel<BFloat, WV, NB, true>), grid, dim3(WV * 64), 0, st, p);
-        else
-            hipLaunchKernelGGL((wgrad_halo_kernel<BFloat, WV, NB, false>), grid, dim3(WV * 64), 0, st, p);
-    }
-    return hipGetLastError();
+    const bool edge = p.h % p.rb != 0;
+    if (dtype == Half::id)
+        return edge ? launch_wgh<Half, true>(p, st) : launch_wgh<Half, false>(p, st);
+    return edge ? launch_wgh<BFloat, true>(p, st) : launch_wgh<BFloat, false>(p, st);
 }
 
 }  // namespace nnconv

@@ -6,6 +6,7 @@ Outputs are written between guard bands filled with a fixed byte pattern;
 the bands must be untouched afterwards."""
 from __future__ import annotations
 
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -261,3 +262,88 @@ def full_parity(case: Case, passes=("fwd", "dgrad", "wgrad"), tile=None):
     for k, e in errs.items():
         assert e <= tol, "%s rel err %.3e > %.1e for %r" % (k, e, tol, case)
     return errs
+
+
+# --- which kernels a call launches ------------------------------------------------
+
+_HIP = None
+
+
+def _hip():
+    """The HIP runtime that torch and libnnconv share in this process."""
+    global _HIP
+    if _HIP is None:
+        torch().cuda.current_device()
+        with open("/proc/self/maps") as f:
+            path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+        h = ctypes.CDLL(path)
+        vp, sp = ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)
+        h.hipStreamBeginCapture.argtypes = [vp, ctypes.c_int]
+        h.hipStreamEndCapture.argtypes = [vp, ctypes.POINTER(vp)]
+        h.hipGraphGetNodes.argtypes = [vp, ctypes.POINTER(vp), sp]
+        h.hipGraphKernelNodeGetParams.argtypes = [vp, vp]
+        h.hipGraphDestroy.argtypes = [vp]
+        h.hipKernelNameRefByPtr.argtypes = [vp, vp]
+        h.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+        _HIP = h
+    return _HIP
+
+
+def kernels(case: Case, pass_: str, ws_bytes=None):
+    """The names (mangled) of the kernels that a pass of this geometry launches
+    with aligned operands, in order: from its capture into a graph, which runs
+    nothing.  ws_bytes: the workspace offered, by default what the library asks for."""
+    L = case.layer
+    t, h = torch(), _hip()
+    d = case.desc()
+    code = {"fwd": nc.NNCONV_FWD, "dgrad": nc.NNCONV_DGRAD, "wgrad": nc.NNCONV_WGRAD}[pass_]
+    st, nb = nc.nnconv_workspace_size(d, code)
+    nc.check(st, "workspace_size")
+    ws = t.empty(max(nb, 1), dtype=t.uint8, device="cuda")
+    ws_bytes = nb if ws_bytes is None else ws_bytes
+    x, w, y = (t.empty(n, dtype=t.int16, device="cuda") for n in (
+        L.n * L.c * L.h * L.w, L.k * L.r * L.s * (L.c // L.groups), L.n * L.k * L.p * L.q))
+    dw = t.empty(w.numel(), dtype=t.float32, device="cuda")
+    stream_ = t.cuda.Stream()
+    s = stream_.cuda_stream
+    t.cuda.synchronize()
+    graph = ctypes.c_void_p()
+    assert h.hipStreamBeginCapture(s, 2) == 0  # relaxed: other work of the process is not its concern
+    if pass_ == "fwd":
+        st = nc.nnconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), 1.0, ws.data_ptr(), ws_bytes, s)
+    elif pass_ == "dgrad":
+        st = nc.nnconv_dgrad(d, y.data_ptr(), w.data_ptr(), x.data_ptr(), 1.0, ws.data_ptr(), ws_bytes, s)
+    else:
+        st = nc.nnconv_wgrad(d, x.data_ptr(), y.data_ptr(), dw.data_ptr(), nc.NNCONV_F32, 1.0, 0, None,
+                             ws.data_ptr(), ws_bytes, s)
+    assert h.hipStreamEndCapture(s, ctypes.byref(graph)) == 0
+    nc.check(st, pass_)
+    n = ctypes.c_size_t()
+    assert h.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert h.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    names = []
+    for node in nodes:
+        # hipKernelNodeParams: blockDim (12 bytes and 4 of padding), extra, func, ...
+        params = ctypes.create_string_buffer(64)
+        assert h.hipGraphKernelNodeGetParams(node, params) == 0
+        func = ctypes.c_void_p.from_buffer(params, 24).value
+        names.append(h.hipKernelNameRefByPtr(func, s).decode())
+    h.hipGraphDestroy(graph)
+    return names
+
+
+def kernel_name(name: str, dtype: str, *args) -> str:
+    """The part of a mangled kernel name with its first template arguments: the
+    operand type, then integers and truth values."""
+    out = "nnconv%d%sINS_%s" % (len(name), name, {I.F16: "4HalfE", I.BF16: "6BFloatE"}[dtype])
+    for a in args:
+        out += "Lb%dE" % a if isinstance(a, bool) else "Li%dE" % a
+    return out
+
+
+def assert_runs(case: Case, pass_: str, name: str, *args, ws_bytes=None):
+    """The pass launches the kernel with this name and these first template
+    arguments (after the operand type)."""
+    want, got = kernel_name(name, case.dtype, *args), kernels(case, pass_, ws_bytes)
+    assert any(want in k for k in got), "%s of %r runs %s, not %s" % (pass_, case.layer, got, want)

@@ -111,3 +111,55 @@ def test_grouped_reduction_split_lanes(nnlib, oracle_lib, cg, n, h, stride, layo
     reduction at one, a few and many splits."""
     L = I.Layer("grp", n, 64, h, h, 64, 3, 3, stride, 1, groups=64 // cg)
     full_parity(Case(L, layout=layout, loss_scale=128.0, cfg=97, layer_id=50), passes=("wgrad",))
+
+
+# kernels whose tiles or row blocks reach past the output's last row or column
+RAGGED = [
+    # name, n, c, h, w, k, r, stride, pad, kernel
+    ("stem4", 3, 3, 70, 54, 60, 7, 2, 3, "stem_wgrad4_kernel"),       # 35x27 outputs, 16x16 tiles
+    ("stem4_rows", 2, 1, 70, 64, 64, 7, 2, 3, "stem_wgrad4_kernel"),  # ragged rows only
+    ("stem8", 3, 5, 61, 45, 64, 7, 2, 3, "stem_wgrad_kernel"),        # 31x23 outputs
+    ("stem8_cols", 2, 3, 64, 59, 61, 7, 2, 3, "stem_wgrad_kernel"),   # ragged columns only
+    ("rows8_w16", 8, 59, 13, 16, 63, 3, 1, 1, "wgrad_halo_kernel"),   # blocks of 8 rows, 13 of them
+    ("rows4_w28", 2, 62, 27, 28, 57, 3, 1, 1, "wgrad_halo_kernel"),   # 3 rows of 28 pixels end a k-step short
+    ("rows16_w7", 40, 64, 9, 7, 60, 3, 1, 1, "wgrad_halo_kernel"),     # a block taller than the image
+]
+
+
+def _ragged_case(s, layout, dtype):
+    name, n, c, h, w, k, r, stride, pad, kernel = s
+    case = Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, 1), layout=layout, dtype=dtype,
+                loss_scale=128.0, x_kind="normal", cfg=97, layer_id=60 + RAGGED.index(s))
+    U.assert_runs(case, "wgrad", kernel)
+    return case
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", RAGGED, ids=[s[0] for s in RAGGED])
+def test_ragged_backward_weight(nnlib, oracle_lib, s, layout, dtype):
+    full_parity(_ragged_case(s, layout, dtype), passes=("wgrad",))
+
+
+@pytest.mark.parametrize("where", ["last", "last_row", "last_column", "dy_last"])
+@pytest.mark.parametrize("s", RAGGED, ids=[s[0] for s in RAGGED])
+def test_ragged_backward_weight_non_finite(nnlib, oracle_lib, s, where):
+    """An inf in x counts for the taps that read it only: the pixels past the
+    output's edge, staged as zeros of dy, must not meet it.  One in dy meets the
+    zero padding, as the definition has it."""
+    case = _ragged_case(s, "nchw", I.F16)
+    L = case.layer
+    t = case.tensors()
+    if where == "dy_last":
+        t["dy"][L.n - 1, L.k // 2, L.p - 1, L.q - 1] = 0x7C00
+    else:
+        h = L.h // 2 if where == "last_column" else L.h - 1
+        w = L.w // 3 if where == "last_row" else L.w - 1
+        t["x"][L.n - 1, L.c // 2, h, w] = 0x7C00
+    g = U.to_nchw(case, "dw", U.run_gpu(case, t, ("wgrad",))["dw"])
+    x, _, dy = nchw_f64(case, t)
+    with np.errstate(invalid="ignore"):
+        ref = oracle_conv(case).wgrad(x, dy, 1.0 / case.loss_scale)
+    assert np.array_equal(np.isfinite(g), np.isfinite(ref))
+    ok = np.isfinite(ref)
+    assert not ok.all() and orc.rel_err(g[ok], ref[ok]) <= TOL[I.F16]
