@@ -130,3 +130,69 @@ def test_depthwise_mfma_backward_weight_non_finite_input(nnlib, oracle_lib, r, p
     assert np.array_equal(np.isfinite(g), np.isfinite(ref))
     ok = np.isfinite(ref)
     assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
+
+
+def _time(fn, reps=10):
+    t = U.torch()
+    fn()
+    best = float("inf")
+    for _ in range(3):
+        a, b = (t.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(reps):
+            fn()
+        b.record()
+        t.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / reps)
+    return best
+
+
+def test_depthwise_mfma_overflow_step(nnlib):
+    """An overflow of the loss scale is an ordinary event: with every dy inf the
+    backward passes take less than three times as long as with finite ones (1.3
+    and 1.6 times; without a look at x first the sums of backward-weight, taken
+    again term by term, took 90 times as long)."""
+    from paper_2102_06725_amd import nnconv as nc
+    t = U.torch()
+    n, c, h, r = 64, 240, 28, 5
+    case = U.Case(I.Layer("ovf", n, c, h, h, c, r, r, 1, r // 2, groups=c))
+    U.assert_runs(case, "dgrad", "dwm_fwd_kernel", r)
+    U.assert_runs(case, "wgrad", "dwm_wgrad_kernel", r)
+    conv = nc.Conv2d(n, c, h, h, c, r, r, stride=1, pad=r // 2, groups=c)
+    x, dy, dx = (t.randn(n, h, h, c, device="cuda").half() for _ in range(3))
+    w = t.randn(c, r, r, 1, device="cuda").half()
+    dw = t.empty(c, r, r, 1, device="cuda")
+    flag = t.zeros(1, dtype=t.int32, device="cuda")
+    for fn in (lambda: conv.dgrad(dy, w, dx), lambda: conv.wgrad(x, dy, dw, nc.NNCONV_F32, 1.0, 0, flag)):
+        keep = dy.clone()
+        finite = _time(fn)
+        dy.fill_(float("inf"))
+        over = _time(fn)
+        dy.copy_(keep)
+        assert over < 3 * finite, (over, finite)
+    assert int(flag.item()) == 1
+
+
+@pytest.mark.parametrize("where", ["dy", "x", "both"])
+@pytest.mark.parametrize("s", [WG_SHAPES[0], WG_SHAPES[1], WG_SHAPES[2]], ids=lambda s: s[0])
+def test_depthwise_mfma_backward_weight_many_non_finite(nnlib, oracle_lib, s, where):
+    """Infs in a third of the channels of dy, of x, or of both: the non-finite
+    sums are the oracle's and no others, and the rest keeps its accuracy."""
+    name, n, c, h, w, r, pad = s
+    case = U.Case(I.Layer(name, n, c, h, w, c, r, r, 1, pad, groups=c), x_kind="normal", cfg=103, layer_id=7)
+    U.assert_runs(case, "wgrad", "dwm_wgrad_kernel", r)
+    t = case.tensors()
+    rng = np.random.default_rng(11)
+    for k in ("x", "dy"):
+        if where in (k, "both"):
+            a = t[k].reshape(-1, c)
+            at = rng.integers(0, a.shape[0], c // 3)
+            a[at, np.arange(c // 3) * 3] = 0x7C00
+            t[k].reshape(n, -1, w if k == "x" else case.layer.q, c)[-1, -1, :, 1] = 0xFC00  # a whole last row
+    g = U.run_gpu(case, t, ("wgrad",))["dw"].reshape(c, r * r)
+    x, _, dy = U.nchw_f64(case, t)
+    with np.errstate(invalid="ignore"):
+        ref = U.oracle_conv(case).wgrad(x, dy).reshape(c, r * r)
+    assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.array_equal(np.isinf(g), np.isinf(ref))
+    ok = np.isfinite(ref)
+    assert orc.rel_err(g[ok], ref[ok]) <= U.TOL[I.F16]
