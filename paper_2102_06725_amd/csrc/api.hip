@@ -768,7 +768,7 @@ TNPhase phase_of(int64_t m, int64_t mi, int64_t mj, int64_t oi_add, int64_t oj_a
 // Whether the 64-channel-slice kernel runs the forward / backward-data pass
 // of a shape that fast_shape() accepts (the tiles a caller may force).
 bool c64_fwd_shape(const Geom &G) { return !stem_shape(G) && G.cg % 64 == 0; }
-bool c64_dgrad_shape(const Geom &G) { return G.kg % 64 == 0 && G.sh * G.sw <= MAX_PHASES; }
+bool c64_dgrad_shape(const Geom &G) { return G.kg % 64 == 0 && G.sh * G.sw <= 4; }
 
 // Weights that a pass has to re-lay (backward-data), expand (super-groups) or
 // both before its GEMM.  Most tiles read the result from `wt`, which make()
@@ -1021,7 +1021,9 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             const int64_t red = (int64_t)t * G.kg;
             const C64Config cfg = G.kg % 64 == 0 ? pick_c64_geom(G, p, p.M, G.cg, red)
                                                  : pick_mix(p.M, G.cg, G.g, red);
-            TRY_HIP(launch_igemm_c64(G.dtype, cfg, p, pad, st));
+            const int wc = pick_wk(p, p.M, red);
+            TRY_HIP(wc >= 0 ? launch_igemm_wk(G.dtype, (WKConfig)wc, p, pad, st)
+                            : launch_igemm_c64(G.dtype, cfg, p, pad, st));
         }
     }
     return NNCONV_OK;

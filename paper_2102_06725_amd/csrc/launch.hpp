@@ -45,7 +45,7 @@ struct TNPhase {
     int32_t tap_start, tap_count;
     int32_t tiles_m, block_start;  // filled by the launcher
 };
-constexpr int MAX_PHASES = 4;
+constexpr int MAX_PHASES = 16;  // strides up to 4
 
 struct TNParams {
     const void *a;
@@ -71,7 +71,7 @@ struct TNParams {
     int32_t diag32;  // igemm_wk only: 64x64 weight blocks, block-diagonal in 32x32 blocks
     int32_t tiles_m, tiles_n;  // per group; filled by the launcher
     TapTable taps;
-    int32_t nphase;            // igemm_c64 only: phases in ph[]
+    int32_t nphase;            // igemm_c64, igemm_wk: phases in ph[]
     TNPhase ph[MAX_PHASES];
 };
 

@@ -3,7 +3,7 @@ which forward and backward-data take where the grid is small, against the fp64
 oracle: one row or column below, at and above the 32- and 64-wide tiles, fewer
 reduction steps than waves, reductions whose 32-element steps mix taps
 (channels not a multiple of 32), stride phases of different sizes and without
-taps, groups, and the block-diagonal weights of small groups.  The last shapes
+taps (up to 16 in one launch, beyond that one each), groups, and the block-diagonal weights of small groups.  The last shapes
 are large enough for the 64x64 tiles (784 and 196 of them)."""
 import numpy as np
 import pytest
@@ -35,6 +35,17 @@ SHAPES = [
     ("diag32_s2", 2, 128, 7, 8, 128, 3, 2, 1, 1, 4),
     ("tiles64_4w", 8, 512, 28, 27, 120, 1, 1, 0, 1, 1),
     ("tiles64_8w", 8, 128, 27, 29, 120, 3, 1, 1, 1, 1),
+    # long reductions of backward-data
+    ("m33n40_k512", 1, 40, 3, 11, 512, 3, 1, 1, 1, 1),
+    ("c8_k520", 2, 8, 9, 7, 520, 3, 1, 1, 1, 1),          # steps across taps
+    ("c40_k328", 1, 40, 8, 9, 328, 3, 1, 1, 1, 1),
+    ("c72_k1032", 2, 72, 5, 5, 1032, 1, 1, 0, 1, 1),
+    ("dil2_k512", 1, 64, 12, 9, 512, 3, 1, 2, 2, 1),
+    ("s2_tapless_k1024", 3, 64, 7, 6, 1024, 1, 2, 0, 1, 1),
+    ("s2_k264", 1, 64, 13, 11, 264, 3, 2, 1, 1, 1),       # four phases, steps across taps
+    ("s3_k264", 1, 24, 10, 11, 264, 3, 3, 1, 1, 1),       # nine
+    ("s4_k264", 1, 64, 13, 12, 264, 3, 4, 1, 1, 1),       # sixteen, seven of them without taps
+    ("s5_k72", 1, 64, 11, 12, 72, 5, 5, 2, 1, 1),         # 25: one launch each
 ]
 
 
@@ -48,6 +59,15 @@ def _case(s, dtype, layout="nhwc"):
 @pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
 def test_small_grid_parity(nnlib, oracle_lib, s, dtype):
     U.full_parity(_case(s, dtype), passes=("fwd", "dgrad"))
+
+
+@pytest.mark.parametrize("stride,launches", [(2, 1), (3, 1), (4, 1), (5, 25)])
+def test_stride_phases_share_a_launch(nnlib, oracle_lib, stride, launches):
+    """Up to 16 stride phases of backward-data are one launch."""
+    case = U.Case(I.Layer("phases", 2, 40, 45, 46, 88, 5, 5, stride, 2), layer_id=30)
+    gemms = [k for k in U.kernels(case, "dgrad") if "igemm" in k]
+    assert len(gemms) == launches
+    U.full_parity(case, passes=("dgrad",))
 
 
 @pytest.mark.parametrize("s", [SHAPES[2], SHAPES[5], SHAPES[10], SHAPES[15]], ids=lambda s: s[0])
@@ -77,7 +97,8 @@ MIX_SHAPES = [
     ("c240k40", 2, 240, 112, 111, 40, 1, 1, 0, 1, 1),        # 64-column tile, 3.75 slices
     ("c24k72_s2", 3, 24, 120, 121, 72, 3, 2, 1, 1, 1),       # four phases, chunks across taps
     ("c8k16_5x5", 2, 8, 150, 151, 16, 5, 1, 2, 1, 1),        # a tap per chunk, 25 taps
-    ("c16k88_s3", 2, 16, 200, 170, 88, 3, 3, 1, 1, 1),       # nine phases: one launch each
+    ("c16k88_s3", 2, 16, 200, 170, 88, 3, 3, 1, 1, 1),       # nine phases
+    ("c16k88_s4", 4, 16, 250, 220, 88, 3, 4, 1, 1, 1),       # sixteen
     ("c264k72_2stage", 8, 264, 56, 56, 72, 1, 1, 0, 1, 1),   # two-stage tile
     ("c72g3", 1, 72, 130, 131, 72, 3, 1, 1, 1, 3),           # groups of 24
 ]
