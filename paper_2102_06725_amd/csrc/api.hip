@@ -560,20 +560,6 @@ TNParams tn_base() {
     return p;
 }
 
-// Tile for reductions whose channels per tap are not a multiple of 64 (rows =
-// GEMM rows, red = reduction length).  Single-stage tiles cover each other's
-// load latency when several share a CU; with at most two workgroups per CU
-// and more than four slices the two-stage tile is the faster one (672 -> 112
-// 1x1 over 128 14x14 images: 15.5 us against 18.5; 264 -> 296 3x3 over 8
-// 31x31: 36.8 against 41.4), with more it loses (40 -> 80 3x3 over 64 56x56:
-// 52.5 against 39.0).
-int device_cus();
-C64Config pick_mix(int64_t rows, int64_t ncols, int64_t groups, int64_t red) {
-    if (ncols <= 64) return C64M_128x64;
-    const int64_t tiles = (rows + 127) / 128 * ((ncols + 127) / 128) * groups;
-    return red > 256 && tiles <= 2 * device_cus() ? C64M2_128x128 : C64M_128x128;
-}
-
 // Tile configuration for the 64-channel-slice kernel, from measurements on
 // the ResNet-50 layers at batch 256 (m = GEMM rows, ncols = output channels
 // per group, red = reduction length):
@@ -710,16 +696,54 @@ constexpr TileCost C64_COST[] = {{128, 64, 3.71, 0.00989, 0.70, 0.00507},    // 
                                  {128, 128, 5.04, 0.01045, 1.67, 0.01242}};  // C64_128x128
 // Block-diagonal weights (p.diag32) take the 32-column tiles, which read only
 // the half of the 64 channels that their columns meet.
+//
+// Channels per tap that are not a multiple of 64 (the mixed-tap tiles, and the
+// split-reduction ones on whichever step their channels allow) have costs of
+// their own, fitted to 2800 random layers and groups (8 to 320 channels, 9-12%
+// rms); pick_mix is the large tile with the smallest.  Single-stage tiles cover
+// each other's load latency when several share a CU; with few workgroups per CU
+// and more than four slices the two-stage tile is the faster one (672 -> 112
+// 1x1 over 128 14x14 images: 15.5 us against 18.5), with more it loses (40 -> 80
+// 3x3 over 64 56x56: 52.5 against 39.0).
+constexpr TileCost MIX_COST[] = {{128, 64, 4.97, 0.01100, 1.05, 0.00677},    // C64M_128x64
+                                 {128, 128, 5.80, 0.01315, 1.46, 0.00916},   // C64M_128x128
+                                 {128, 128, 5.83, 0.01107, 2.16, 0.01174}};  // C64M2_128x128
+constexpr TileCost WK_MIX_COST[] = {{32, 32, 4.92, 0.00185, 1.51, 0.00216},
+                                    {32, 32, 5.34, 0.00160, 3.16, 0.00284},
+                                    {64, 64, 5.82, 0.00392, 2.12, 0.00373},
+                                    {64, 64, 6.03, 0.00271, 4.19, 0.00524}};
+C64Config pick_mix(const TNParams &p, int64_t red, double *us = nullptr) {
+    const int cus = device_cus();
+    int pick = 0;
+    double best = 0;
+    for (int i = 0; i < 3; ++i) {
+        const double t = MIX_COST[i].us(p, red, cus);
+        if (i == 0 || t < best) {
+            best = t;
+            pick = i;
+        }
+    }
+    if (us) *us = best;
+    return (C64Config)(C64M_128x64 + pick);
+}
+
 int pick_wk(const TNParams &p, int64_t rows, int64_t red) {
     if (red <= 0) return -1;
     const int cus = device_cus();
-    const C64Config big = pick_c64(rows, p.ncols, red);
-    double best = C64_COST[big == C64S_128x64 ? 0 : big == C64S_128x128 ? 1 : 2].us(p, red, cus);
+    const bool mix = p.cr % 64 != 0;
+    double best;
+    if (mix) {
+        pick_mix(p, red, &best);
+    } else {
+        const C64Config big = pick_c64(rows, p.ncols, red);
+        best = C64_COST[big == C64S_128x64 ? 0 : big == C64S_128x128 ? 1 : 2].us(p, red, cus);
+    }
+    const TileCost *cost = mix ? WK_MIX_COST : WK_COST;
     int pick = -1;
-    for (int i = 0; i < (int)(sizeof(WK_COST) / sizeof(WK_COST[0])); ++i) {
-        // 10% off, so that the larger tile stays where the two are close
-        if (p.diag32 && WK_COST[i].bn != 32) continue;
-        const double t = 1.10 * WK_COST[i].us(p, p.diag32 ? red / 2 : red, cus);
+    for (int i = 0; i < 4; ++i) {
+        if (p.diag32 && cost[i].bn != 32) continue;
+        // 5-10% off, so that the larger tile stays where the two are close
+        const double t = (mix ? 1.05 : 1.10) * cost[i].us(p, p.diag32 ? red / 2 : red, cus);
         if (t < best) {
             best = t;
             pick = i;
@@ -900,7 +924,7 @@ nnconv_status fwd_fast(const Geom &G, const void *x, const void *w, void *y, flo
             tile >= 0 ? (C64Config)tile : pick_c64_geom(G, p, p.M, G.kg, (int64_t)t * G.cg);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, G.ph > 0 || G.pw > 0, st));
     }
-    return hip_status(launch_igemm_c64(G.dtype, pick_mix(p.M, G.kg, G.g, (int64_t)t * G.cg), p,
+    return hip_status(launch_igemm_c64(G.dtype, pick_mix(p, (int64_t)t * G.cg), p,
                                        G.ph > 0 || G.pw > 0, st));
 }
 
@@ -994,7 +1018,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
                 launch_igemm_halo(G.dtype, (HaloConfig)hc, p, pack, G.diag32 != 0, nullptr, st));
         const C64Config cfg = tile >= 0 ? (C64Config)tile
                               : c64     ? pick_c64_geom(G, p, rows, G.cg, red_rows / rows)
-                                        : pick_mix(rows, G.cg, G.g, red_rows / rows);
+                                        : pick_mix(p, red_rows / rows);
         return hip_status(launch_igemm_c64(G.dtype, cfg, p, pad, st));
     }
     TRY_HIP(make_weights(G, prep, st));
@@ -1020,7 +1044,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
             p.ph[0] = phase_of(p.M, mi, mj, phh, phw, 0, t);
             const int64_t red = (int64_t)t * G.kg;
             const C64Config cfg = G.kg % 64 == 0 ? pick_c64_geom(G, p, p.M, G.cg, red)
-                                                 : pick_mix(p.M, G.cg, G.g, red);
+                                                 : pick_mix(p, red);
             const int wc = pick_wk(p, p.M, red);
             TRY_HIP(wc >= 0 ? launch_igemm_wk(G.dtype, (WKConfig)wc, p, pad, st)
                             : launch_igemm_c64(G.dtype, cfg, p, pad, st));

@@ -413,7 +413,7 @@ void igemm_c64_kernel(const TNParams P) {
     }
 
     static_assert(BM * BN / 8 <= LDS_SLOTS, "C tile must fit in LDS");
-    store_tile<T, BM, BN, WM, WN, FM, FN>(acc, &lds[0], P, F, m0, n0, g);
+    store_tile<T, BM, BN, WM, WN, FM, FN, MIX>(acc, &lds[0], P, F, m0, n0, g);
 }
 
 template <class T, int BM, int BN, int WM, int WN, int BKC, int STAGES, bool DIAG = false,

@@ -15,7 +15,7 @@ namespace nnconv {
 // pixel l32 of each 32-pixel block and, of each 32-channel block, channels
 // 8*e + 4*khalf + {0..3} (e = 0..3).  `lds` must hold BM * BN / 8 chunks and
 // no other wave may still read it (the first barrier waits for that).
-template <class T, int BM, int BN, int WM, int WN, int FM, int FN>
+template <class T, int BM, int BN, int WM, int WN, int FM, int FN, bool MIX = false>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *lds,
                                            const TNParams &P, const TNPhase &F, int m0, int n0,
                                            int g) {
@@ -52,6 +52,10 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *l
     barrier_lds();
     uint16_t *out = (uint16_t *)P.out;
     constexpr int ROWS_PER_PASS = NW * 64 / CPR;
+    // strided backward-data of groups that share cache lines: a streaming store
+    // of a part of a line costs a whole one (32 groups of 24, 1x1 stride 2, 62
+    // images of 19x77: 160 us against 71)
+    const bool part = MIX && P.oj_mul > 1 && P.groups > 1 && P.o_cg_ofs % 64 != 0;
 #pragma unroll 4
     for (int r = tid / CPR; r < BM; r += ROWS_PER_PASS) {
         const int c = tid % CPR;
@@ -68,7 +72,14 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *l
             ((int64_t)(n * P.o_h + oh) * P.o_w + ow) * P.o_c + (int64_t)g * P.o_cg_ofs;
         // streaming store: the output is not read again by this pass, so it
         // should not displace operand lines in L2
-        __builtin_nontemporal_store(lds[r * CPR + (c ^ (r & CSW))], (u32x4 *)(out + obase + ch));
+        const u32x4 v = lds[r * CPR + (c ^ (r & CSW))];
+        if (part) {
+            // the fences keep the compiler from making one store of the two
+            asm volatile("" ::: "memory");
+            *(u32x4 *)(out + obase + ch) = v;
+            asm volatile("" ::: "memory");
+        } else
+            __builtin_nontemporal_store(v, (u32x4 *)(out + obase + ch));
     }
 }
 

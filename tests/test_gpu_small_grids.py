@@ -3,8 +3,11 @@ which forward and backward-data take where the grid is small, against the fp64
 oracle: one row or column below, at and above the 32- and 64-wide tiles, fewer
 reduction steps than waves, reductions whose 32-element steps mix taps
 (channels not a multiple of 32), stride phases of different sizes and without
-taps (up to 16 in one launch, beyond that one each), groups, and the block-diagonal weights of small groups.  The last shapes
-are large enough for the 64x64 tiles (784 and 196 of them)."""
+taps (up to 16 in one launch, beyond that one each), groups, and the
+block-diagonal weights of small groups.  The shapes of TILES64 are large enough
+for the 64x64 tiles.  Backward-data of the smallest shapes has a kernel of its
+own (one launch): those of LONG have reductions too long for it.  Every test asks
+which kernel the call launches."""
 import numpy as np
 import pytest
 
@@ -47,6 +50,11 @@ SHAPES = [
     ("s4_k264", 1, 64, 13, 12, 264, 3, 4, 1, 1, 1),       # sixteen, seven of them without taps
     ("s5_k72", 1, 64, 11, 12, 72, 5, 5, 2, 1, 1),         # 25: one launch each
 ]
+# backward-data of these runs in one launch on the kernel for very small layers
+TINY_DGRAD = {"m31", "m33n40", "m65n72", "two_steps", "one_pixel_long", "c8", "c16k24", "c40k56", "dil2", "s2_tapless",
+              "s3_c24"}
+MIXED_DGRAD = {"tiles64_4w"}  # the mixed-tap tiles are the faster ones
+TILES64 = {("tiles64_4w", "fwd"), ("tiles64_8w", "fwd"), ("tiles64_8w", "dgrad")}
 
 
 def _case(s, dtype, layout="nhwc"):
@@ -58,7 +66,15 @@ def _case(s, dtype, layout="nhwc"):
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16])
 @pytest.mark.parametrize("s", SHAPES, ids=[s[0] for s in SHAPES])
 def test_small_grid_parity(nnlib, oracle_lib, s, dtype):
-    U.full_parity(_case(s, dtype), passes=("fwd", "dgrad"))
+    case = _case(s, dtype)
+    for p in ("fwd", "dgrad"):
+        if p == "dgrad" and s[0] in TINY_DGRAD:
+            U.assert_runs(case, p, "igemm_tiny_kernel", 1)
+        elif p == "dgrad" and s[0] in MIXED_DGRAD:
+            U.assert_runs(case, p, "igemm_c64_kernel")
+        else:
+            U.assert_runs(case, p, "igemm_wk_kernel", *((64, 64) if (s[0], p) in TILES64 else (32, 32)))
+    U.full_parity(case, passes=("fwd", "dgrad"))
 
 
 @pytest.mark.parametrize("stride,launches", [(2, 1), (3, 1), (4, 1), (5, 25)])
@@ -83,6 +99,7 @@ def test_small_grid_block_diagonal_keeps_inf_in_its_half(nnlib, where):
     """An inf reaches at most the 32 channels that share its diagonal block,
     as in the larger block-diagonal tiles."""
     case = _case(SHAPES[15], I.F16)
+    U.assert_runs(case, "fwd", "igemm_wk_kernel", 32, 32)
     t = case.tensors()
     t[where].reshape(t[where].shape[0], -1)[0, 0] = 0x7C00  # channel 0 / filter 0
     y = U.run_gpu(case, t, ("fwd",))["y"].reshape(U.shape_of(case, "y"))
@@ -92,15 +109,18 @@ def test_small_grid_block_diagonal_keeps_inf_in_its_half(nnlib, where):
 # Grids past the split-reduction tiles whose channels per tap are not a
 # multiple of 64: the mixed-tap tiles of the 64-element-slice kernel.
 MIX_SHAPES = [
-    # name, n, c, h, w, k, r, stride, pad, dil, groups
-    ("c40k240", 2, 40, 112, 111, 240, 1, 1, 0, 1, 1),        # one slice, ragged rows and columns
-    ("c240k40", 2, 240, 112, 111, 40, 1, 1, 0, 1, 1),        # 64-column tile, 3.75 slices
-    ("c24k72_s2", 3, 24, 120, 121, 72, 3, 2, 1, 1, 1),       # four phases, chunks across taps
-    ("c8k16_5x5", 2, 8, 150, 151, 16, 5, 1, 2, 1, 1),        # a tap per chunk, 25 taps
-    ("c16k88_s3", 2, 16, 200, 170, 88, 3, 3, 1, 1, 1),       # nine phases
-    ("c16k88_s4", 4, 16, 250, 220, 88, 3, 4, 1, 1, 1),       # sixteen
-    ("c264k72_2stage", 8, 264, 56, 56, 72, 1, 1, 0, 1, 1),   # two-stage tile
-    ("c72g3", 1, 72, 130, 131, 72, 3, 1, 1, 1, 3),           # groups of 24
+    # name, n, c, h, w, k, r, stride, pad, dil, groups; columns and stages of the tile: fwd, dgrad
+    ("c40k240", 2, 40, 112, 111, 240, 1, 1, 0, 1, 1, (128, 1), (64, 1)),        # one slice, ragged rows and columns
+    ("c240k40", 2, 240, 112, 111, 40, 1, 1, 0, 1, 1, (64, 1), (128, 1)),        # 3.75 slices
+    ("c24k72_s2", 3, 24, 120, 121, 72, 3, 2, 1, 1, 1, None, None),              # four phases, chunks across taps
+    ("c24k72_s2_n6", 6, 24, 150, 151, 72, 3, 2, 1, 1, 1, (128, 2), (64, 1)),
+    ("c8k16_5x5", 2, 8, 150, 151, 16, 5, 1, 2, 1, 1, (64, 1), (64, 1)),         # a tap per chunk, 25 taps
+    ("c16k88_s3_n2", 2, 16, 200, 170, 88, 3, 3, 1, 1, 1, None, None),
+    ("c16k88_s3", 4, 16, 250, 220, 88, 3, 3, 1, 1, 1, (128, 2), (64, 1)),       # nine phases
+    ("c16k88_s4", 4, 16, 250, 220, 88, 3, 4, 1, 1, 1, None, (64, 1)),           # sixteen
+    ("c264k72_2stage", 8, 264, 56, 56, 72, 1, 1, 0, 1, 1, (128, 2), (128, 1)),
+    ("c72g3", 1, 72, 130, 131, 72, 3, 1, 1, 1, 3, (64, 1), (64, 1)),            # groups of 24
+    ("c96g4_s2", 40, 96, 38, 37, 96, 1, 2, 0, 1, 4, None, (64, 1)),             # groups that share cache lines
 ]
 
 
@@ -115,13 +135,19 @@ W8_SHAPES = [
 @pytest.mark.parametrize("s", W8_SHAPES, ids=[s[0] for s in W8_SHAPES])
 def test_eight_wave_tile(nnlib, oracle_lib, s, dtype):
     name, n, c, h, w, k, r, stride, pad, dil, groups = s
-    U.full_parity(U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
-                         x_kind="normal", cfg=102, layer_id=W8_SHAPES.index(s)), passes=("fwd", "dgrad"))
+    case = U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
+                  x_kind="normal", cfg=102, layer_id=W8_SHAPES.index(s))
+    U.assert_runs(case, "fwd", "igemm_c64_kernel", 128, 128, 4, 2)
+    U.full_parity(case, passes=("fwd", "dgrad"))
 
 
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16])
 @pytest.mark.parametrize("s", MIX_SHAPES, ids=[s[0] for s in MIX_SHAPES])
 def test_mixed_tap_tiles(nnlib, oracle_lib, s, dtype):
-    name, n, c, h, w, k, r, stride, pad, dil, groups = s
-    U.full_parity(U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
-                         x_kind="normal", cfg=99, layer_id=MIX_SHAPES.index(s)), passes=("fwd", "dgrad"))
+    name, n, c, h, w, k, r, stride, pad, dil, groups, fwd, dgrad = s
+    case = U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad, dil, groups), dtype=dtype,
+                  x_kind="normal", cfg=99, layer_id=MIX_SHAPES.index(s))
+    for p, tile in (("fwd", fwd), ("dgrad", dgrad)):
+        if tile:  # 128 rows x columns, 4 waves, 64-element slices, stages
+            U.assert_runs(case, p, "igemm_c64_kernel", 128, tile[0], 2, 2, 8, tile[1])
+    U.full_parity(case, passes=("fwd", "dgrad"))
