@@ -4,6 +4,7 @@
 
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "launch.hpp"
@@ -382,6 +383,9 @@ Regions sg_regions(const Geom &G, nnconv_pass pass) {
     return R;
 }
 
+int device_cus();
+bool pad_pays(const Geom &G, const Geom &S, nnconv_pass pass);
+
 // Channel counts that are not multiples of 8 (RGB and grey images, heads with
 // an odd number of classes), one group: the convolution with both counts
 // padded by zero channels, channel-last, on the matrix-core kernels.  The
@@ -401,9 +405,79 @@ bool pad_geom(const Geom &G, nnconv_pass pass, Geom *out) {
         T.c = T.cg = 4;
         if (stem_shape(T)) S = T;
     }
-    if (!fast_pass(S, pass)) return false;
+    if (!fast_pass(S, pass) || !pad_pays(G, S, pass)) return false;
     *out = S;
     return true;
+}
+
+// Estimated time of a forward or backward-data call on the direct kernels, in
+// microseconds: a chain of loads per output, kk channels of the other side
+// long, and rounds of waves beyond what the chip holds.  Fitted to 5000 random
+// layers of 1 to 160 channels (14 and 24% rms).
+double direct_us(const Geom &G, nnconv_pass pass) {
+    const bool fwd = pass == NNCONV_FWD;
+    const double outs = (double)(fwd ? G.n * G.k * G.p * G.q : G.n * G.c * G.h * G.w);
+    const double kk = (double)(fwd ? G.cg : G.kg);
+    // a strided backward-data pass skips taps, but tests them all
+    const double inner = kk * G.r * G.s / (!fwd && G.sh * G.sw > 1 ? 2 : 1);
+    const double rounds = outs / 64 / (32.0 * device_cus());
+    const double u = rounds < 1 ? rounds : 1, v = rounds > 1 ? rounds - 1 : 0;
+    const double nhwc = G.layout == NNCONV_NHWC ? 1 : 0;  // neighbouring threads' loads are apart
+    if (fwd)
+        return 3.31 + 0.111 * kk + 0.161 * inner + u * (0.404 * kk + 0.156 * inner) +
+               v * (2.01 + 0.216 * kk + 0.265 * inner) * (1 + 0.21 * nhwc);
+    return 3.47 + 0.188 * kk + 0.190 * inner + u * (0.766 * kk + 0.379 * inner) +
+           v * (2.70 + 0.457 * kk + 0.470 * inner) * (1 + 0.06 * nhwc);
+}
+
+// The same for backward-weight: a thread per weight and split (at most 64, of
+// 2048 pixels at least), and the reduction.
+double direct_wgrad_us(const Geom &G) {
+    const double splits = plan_wgrad_direct_splits(G);
+    const double pixels = (double)(G.n * G.p * G.q) / splits;
+    const double rounds = (double)(G.k * G.r * G.s * G.cg) * splits / 64 / (32.0 * device_cus());
+    return 4.84 + pixels * (0.364 + 0.770 * (rounds < 1 ? rounds : 1) +
+                            (rounds > 1 ? 1.8 * (rounds - 1) : 0));
+}
+
+// Whether the padded convolution S is the faster way: its copies, padded
+// weights and GEMM are three to five launches of about 2.4 us (4 us of the
+// host's time), over tensors of 8 channels where the call has one to seven.
+// Whatever the direct kernels would spend more than 100 us on with long sums is
+// padded (their loads miss the caches then).  Estimates fitted as above, 12%
+// rms; 10% off, so that calls stay on the direct kernels when the two are close.
+// Direct against padded, us: 1x1 3 -> 1 over 57 images of 14x430 7.8, 30.7; 3x3
+// 4 -> 1, 24 of 36x98 9.9, 20.8; 5x5 2 -> 9, 2 of 327x80 21.5, 16.9;
+// backward-weight of 3x3 687 -> 93, 2 of 1x2 12.3, 16.4.
+bool pad_pays(const Geom &G, const Geom &S, nnconv_pass pass) {
+    const bool fwd = pass == NNCONV_FWD, wgrad = pass == NNCONV_WGRAD;
+    const bool nhwc = G.layout == NNCONV_NHWC;
+    const double direct = wgrad ? direct_wgrad_us(G) : direct_us(G, pass);
+    if (direct > 100 && (wgrad || (fwd ? G.cg : G.kg) >= 16)) return true;
+    const bool copy_x = !nhwc || S.c != G.c, copy_y = !nhwc || S.k != G.k;
+    const double copied = 2e-6 * ((copy_x ? G.n * G.h * G.w * (S.c + G.c) : 0) +
+                                  (copy_y ? G.n * G.p * G.q * (S.k + G.k) : 0));  // MB
+    const int launches = 2 + copy_x + copy_y + (pass == NNCONV_DGRAD && G.r * G.s > 1);
+    double pad;
+    if (wgrad) {
+        const double pixels = 1e-3 * G.n * G.p * G.q, weights = 1e-6 * S.k * S.c * G.r * G.s;
+        pad = 3.53 + 2.47 * launches + 0.352 * copied + 0.0256 * pixels + 4.61 * weights +
+              11.9 * pixels * weights;
+    } else {
+        const double gemm = 2e-6 * (S.n * S.h * S.w * S.c + S.n * S.p * S.q * S.k);
+        const int64_t rows = fwd ? G.n * G.p * G.q : G.n * G.h * G.w, cols = fwd ? G.k : G.c;
+        const double red = (double)(fwd ? S.c * G.r * G.s
+                                        : S.k * ((G.r + G.sh - 1) / G.sh) * ((G.s + G.sw - 1) / G.sw));
+        const int64_t bn = cols <= 64 ? 64 : 128;
+        const double tiles = (double)((rows + 127) / 128 * ((cols + bn - 1) / bn)) / device_cus();
+        const double more = tiles > 1 ? tiles - 1 : 0;
+        pad = fwd ? 1.83 + 2.39 * launches + 0.366 * copied + 0.168 * gemm + 0.0018 * red +
+                        more * (0.53 + 0.0115 * red)
+                  : 1.84 + 2.42 * launches + 0.351 * copied + 0.357 * gemm + 0.0017 * red +
+                        more * (0.39 + 0.0102 * red);
+    }
+    const double pad_host = 0.8 + 4.0 * launches, direct_host = wgrad ? 9.5 : 7.0;
+    return 1.1 * (pad > pad_host ? pad : pad_host) < (direct > direct_host ? direct : direct_host);
 }
 
 // Workspace of the padded convolution S of G: channel-last copies with padded
@@ -509,8 +583,13 @@ bool tiny_shape(const Geom &G, int pass) {
     if (G.n * G.h * G.w * G.c > lim || G.n * G.p * G.q * G.k > lim || G.k * G.r * G.s * G.c > lim)
         return false;
     // without copies the other path is few launches
-    const bool single = G.layout == NNCONV_NHWC && fast_pass(G, (nnconv_pass)pass);
-    return tiny_pays(direct_params(G, 1.0f), pass, single);
+    const bool fast = fast_pass(G, (nnconv_pass)pass);
+    const DirectParams P = direct_params(G, 1.0f);
+    if (!tiny_pays(P, pass, G.layout == NNCONV_NHWC && fast)) return false;
+    // channel counts that would be padded or run on the direct kernels: those
+    // are the faster ones for a few channels (1x1 2 -> 3 over 2 images of
+    // 237x35, backward-data: 8.6 us against 11.3)
+    return fast || pass == NNCONV_WGRAD || tiny_us(P, pass) < direct_us(G, (nnconv_pass)pass);
 }
 
 // dx rows (cols) at the top / bottom (left / right) that may have filter
@@ -763,13 +842,19 @@ C64Config pick_8w(const TNParams &p, C64Config c, int64_t red) {
 }
 
 // Compute units of the current device (the persistent kernels launch one
-// workgroup per CU).
+// workgroup per CU),
+// asked of the runtime once per device: the rules above need it several times
+// a call.
 int device_cus() {
+    static std::atomic<int> known[64];
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    const bool keep = dev >= 0 && dev < 64;
+    if (keep && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus < 1)
-        cus = 256;
+        return 256;
+    if (keep) known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 

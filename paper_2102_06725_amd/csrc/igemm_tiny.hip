@@ -290,6 +290,16 @@ bool tiny_pays(const DirectParams &p, int pass, bool single) {
     return g.steps * (g.wgs > 512 ? g.wgs : 512) <= (int64_t)limit * 512;
 }
 
+// Estimated time of a forward or backward-data pass here, in microseconds
+// (fitted to 8000 random layers, 9% rms).
+double tiny_us(const DirectParams &p, int pass) {
+    const TinyGrid g = grid_of(p, pass);
+    const double s = (double)g.steps, w = (double)g.wgs / 512;
+    const double u = w < 1 ? w : 1, v = w > 1 ? w - 1 : 0;
+    if (pass == 0) return 2.81 + s * (1.23 + 0.57 * u) + v * (0.53 + 0.65 * s);
+    return 3.20 + s * (1.24 + 0.77 * u) + v * (0.35 + 1.21 * s);
+}
+
 hipError_t launch_igemm_tiny(int dtype, int pass, const DirectParams &p, const void *a,
                              const void *b, void *out, int out_code, float inv_scale,
                              int accumulate, int32_t *flag, hipStream_t st) {

@@ -274,6 +274,7 @@ hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, 
 // a = dy, b = w; 2 out = dw (0 fp16, 1 bf16, 2 fp32) from a = dy, b = x with the
 // loss-scale step of launch_wgrad_reduce.
 bool tiny_pays(const DirectParams &p, int pass, bool single);
+double tiny_us(const DirectParams &p, int pass);
 hipError_t launch_igemm_tiny(int dtype, int pass, const DirectParams &p, const void *a,
                              const void *b, void *out, int out_code, float inv_scale,
                              int accumulate, int32_t *flag, hipStream_t st);

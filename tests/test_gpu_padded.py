@@ -1,8 +1,9 @@
 """Channel counts that are not multiples of 8 with one group: padded by zero
-channels for the matrix-core kernels when the workspace holds the copies, on
-the direct kernels when it does not.  Both against the fp64 oracle, at the
-edges of the padding (one channel, one below and one above a multiple of 8),
-of the copies (odd image sizes, one pixel) and of the stem's 4-channel form."""
+channels for the matrix-core kernels where that is the faster way and the
+workspace holds the copies, on the direct kernels otherwise.  Both against the
+fp64 oracle, at the edges of the padding (one channel, one below and one above a
+multiple of 8), of the copies (odd image sizes, one pixel) and of the stem's
+4-channel form."""
 import numpy as np
 import pytest
 
@@ -31,6 +32,21 @@ SHAPES = [
 ]
 
 
+# passes of SHAPES that the direct kernels run faster
+DIRECT = {("grey5x5", "fwd")}
+
+# thin layers: every pass, or the passes named, on the direct kernels
+THIN = [
+    # name, n, c, h, w, k, r, stride, pad, passes
+    ("c3k1_1x1", 57, 3, 14, 430, 1, 1, 1, 0, ("fwd", "dgrad")),
+    ("c4k1_3x3", 24, 4, 36, 98, 1, 3, 1, 1, ("fwd", "dgrad")),
+    ("c2k3_s2", 10, 2, 124, 27, 3, 1, 2, 0, ("dgrad",)),
+    ("c7k2_1x1", 33, 7, 57, 43, 2, 1, 1, 0, ("fwd", "dgrad")),
+    ("c687k93_2px", 2, 687, 1, 2, 93, 3, 1, 1, ("wgrad",)),
+    ("c99k490_1px", 1, 99, 1, 1, 490, 3, 1, 1, ("wgrad",)),
+]
+
+
 def tiny_steps(L, pass_):
     """Reduction steps x queueing of the one-launch kernel for very small
     convolutions; from 5 on no call takes it."""
@@ -56,11 +72,31 @@ def _case(s, layout, dtype):
 def test_padded_channels(nnlib, oracle_lib, s, layout, dtype):
     case = _case(s, layout, dtype)
     assert all(tiny_steps(case.layer, p) > 4 for p in ("fwd", "dgrad", "wgrad"))
+    for p in ("fwd", "dgrad", "wgrad"):
+        direct = any("direct_" in k for k in U.kernels(case, p))
+        assert direct == ((s[0], p) in DIRECT), (s[0], p)
     full_parity(case)
 
 
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
 @pytest.mark.parametrize("layout", ["nchw", "nhwc"])
-@pytest.mark.parametrize("s", SHAPES[3:6] + SHAPES[8:9], ids=[s[0] for s in SHAPES[3:6] + SHAPES[8:9]])
+@pytest.mark.parametrize("s", THIN, ids=[s[0] for s in THIN])
+def test_thin_layers_run_direct(nnlib, oracle_lib, s, layout, dtype):
+    """Where the copies and the padded GEMM would cost more than the direct
+    kernel does (up to 8 times), and no workspace is asked for them."""
+    name, n, c, h, w, k, r, stride, pad, passes = s
+    case = Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad), layout=layout, dtype=dtype, loss_scale=128.0,
+                x_kind="normal", cfg=97, layer_id=80 + THIN.index(s))
+    for p in passes:
+        assert any("direct_%s_kernel" % p in kn for kn in U.kernels(case, p)), p
+    full_parity(case, passes=passes)
+
+
+SMALL_WS = [SHAPES[3], SHAPES[5], SHAPES[6], SHAPES[8]]  # padded in every pass
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", SMALL_WS, ids=[s[0] for s in SMALL_WS])
 def test_small_workspace_takes_the_direct_kernels(nnlib, oracle_lib, s, layout, monkeypatch):
     """No workspace forward and backward-data, the direct kernel's partials
     backward-weight: accepted, and the same result within the tolerance."""
