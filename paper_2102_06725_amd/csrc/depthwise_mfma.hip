@@ -548,8 +548,9 @@ template <class T, int R, bool FLIP>
 hipError_t launch_dwm_rs(const DWTParams &q, const void *in, const void *w, void *out,
                          hipStream_t st) {
     constexpr int TR = strip_rows(R);
-    // 3x3: 9 to 16 wide only (depthwise_mfma_pays)
-    if constexpr (R == 3) return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
+    // 3x3: bf16, 9 to 16 wide only (depthwise_mfma_pays)
+    if constexpr (R == 3 && T::id == Half::id) return hipErrorInvalidValue;
+    else if constexpr (R == 3) return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
     else switch (plan(q, R).cfg) {
         case 0: return launch_dwm_cfg<T, R, 4, 1, 8, 4, FLIP>(q, in, w, out, st);
         case 1: return launch_dwm_cfg<T, R, 4, 1, 16, TR, FLIP>(q, in, w, out, st);
@@ -571,20 +572,39 @@ hipError_t launch_dwm_t(const DWTParams &q, int r, const void *in, const void *w
 
 }  // namespace
 
-// A workgroup's strips are long: below about two workgroups per CU (one for
-// 5x5 and 7x7, which gain more per output) the LDS-tiled vector kernel's
-// smaller tiles are the faster ones, and for 3x3 on images up to 8 wide, where
-// a tile is little more than its set-up (480 channels, 14x14, 3x3: 32 images
-// 6.0 us there against 6.7 here, 128 images 14.6 against 13.3; 5x5: 16 images
-// 7.0 against 8.3, 32 9.0 against 8.8; 1152 channels, 7x7, 3x3, 128 images 9.4
-// against 10.7).
-// Wide 3x3 images stay there too: they are near the HBM rate on either kernel,
-// and its blocks of up to 64 channels touch fewer partial lines (three passes,
-// 128 images, vector -> matrix cores: 96 channels, 112x112, fp16 413 -> 527 us,
-// bf16 453 -> 530; 144 channels, 56x56, fp16 186 -> 211, bf16 208 both).
-bool depthwise_mfma_pays(const DWTParams &q, int r) {
-    if (r == 3 && (q.ow <= 8 || q.ow > 16)) return false;
-    return plan(q, r).wgs >= (r == 3 ? 512 : 256);
+// The faster kernel for a launch by estimates in microseconds, fitted to 8800
+// random and EfficientNet-like layers (6% rms here, 7-15% the LDS-tiled kernel).
+// Both pay for the tensors' MB and for their tiles, inside the image or not: the
+// strips here are long, so the vector kernel keeps small grids and images that
+// fill the tiles badly, and in fp16, where it needs no widening, more of them
+// than in bf16.  tiled_work: its workgroups x rows per thread; tiled_rows: rows
+// per thread.
+// Against thresholds of one or two workgroups per CU, calls that are more than
+// 5% slower than the vector kernel: 423 -> 60 (47 of 464 channels, 15x15, 7x7 fp16
+// 17 us against 25; 106 of 864, 5x8, 5x5 11 against 13), geometric mean 0.903 ->
+// 0.893 of its time.
+// 3x3 layers in fp16 stay there (960 channels, 14x14, 128 images 25.8 us against
+// 28.4), and wide and narrow images: on wide ones both are near the HBM rate,
+// and the blocks of up to 64 channels touch fewer partial lines (three passes, 128
+// images, vector -> matrix cores: 96 channels, 112x112, fp16 413 -> 527 us, bf16
+// 453 -> 530; 144 channels, 56x56, fp16 186 -> 211, bf16 208 both); up to 8 wide a
+// tile is little more than its set-up (1152 channels, 7x7, 128 images 9.4 -> 10.7).
+bool depthwise_mfma_pays(int dtype, const DWTParams &q, int r, int64_t tiled_work, int tiled_rows) {
+    if (r == 3 && (dtype == Half::id || q.ow <= 8 || q.ow > 16)) return false;
+    // start, per MB, per workgroup row (tiled) or workgroup (by tile) on each CU
+    static const double tiled[2][3][3] = {
+        {{0.0, 0.0, 0.0}, {4.25, 0.100, 0.589}, {5.08, 0.109, 1.224}},
+        {{3.82, 0.037, 0.437}, {3.53, 0.0, 1.211}, {4.80, 0.0, 2.183}}};
+    static const double here[3][6] = {{4.86, 0.130, 0.0, 1.07, 0.0, 0.0},
+                                      {5.56, 0.146, 0.44, 2.37, 1.75, 1.99},
+                                      {5.05, 0.163, 2.27, 3.43, 2.50, 2.82}};
+    const double mb = 2e-6 * q.n * q.c * ((double)q.ih * q.iw + (double)q.oh * q.ow);
+    const double *a = tiled[dtype == Half::id ? 0 : 1][(r - 3) / 2], *b = here[(r - 3) / 2];
+    const DwmPlan pl = plan(q, r);
+    const double rows = (double)tiled_work / 256, wgs = (double)pl.wgs / 256;
+    const double t = a[0] + a[1] * mb + a[2] * (rows > tiled_rows ? rows : tiled_rows);
+    const double m = b[0] + b[1] * mb + b[2 + pl.cfg] * (wgs > 1 ? wgs : 1);
+    return 1.03 * m < t;
 }
 
 hipError_t launch_depthwise_mfma(int dtype, const DWTParams &q, int r, bool flip, const void *in,
@@ -634,6 +654,9 @@ int32_t depthwise_mfma_wgrad_plan(const DWParams &p, int32_t max_splits, DWTPara
     if (splits > blocks / 2) splits = blocks / 2;  // two blocks at a time
     if (splits > max_splits) splits = max_splits;
     if (splits < 1 || splits * cblocks < 96) return 0;
+    // two workgroups fit a CU: a few more than that would be a second round (a
+    // 5x5 layer with 513 workgroups 23.2 us, the LDS-tiled kernel 16.0)
+    if (splits * cblocks > 512 && splits * cblocks < 768 && cblocks <= 512) splits = 512 / cblocks;
     const int64_t per = (blocks + splits - 1) / splits;
     splits = (blocks + per - 1) / per;
     if (q) {

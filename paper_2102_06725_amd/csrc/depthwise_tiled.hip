@@ -529,7 +529,8 @@ struct TilePick {
     int cbv;
     bool narrow;
 };
-TilePick pick_tile(const DWTParams &q, int kind, int r, int sh) {
+TilePick pick_tile(const DWTParams &q, int kind, int r, int sh, int64_t *work = nullptr,
+                   int *rows = nullptr) {
     TilePick best = {8, false};
     int64_t best_cost = -1;
     for (int nw = 0; nw < 2; ++nw) {
@@ -542,10 +543,21 @@ TilePick pick_tile(const DWTParams &q, int kind, int r, int sh) {
             if (best_cost < 0 || cost < best_cost) {
                 best = {cbv, nw != 0};
                 best_cost = cost;
+                if (rows) *rows = tp;
             }
         }
     }
+    if (work) *work = best_cost * q.n;
     return best;
+}
+
+// Whether a stride-1 forward launch (or backward-data as one) is the matrix
+// cores'.
+bool mfma_pays(int dtype, const DWTParams &q, int r) {
+    int64_t work;
+    int rows;
+    pick_tile(q, 0, r, 1, &work, &rows);
+    return depthwise_mfma_pays(dtype, q, r, work, rows);
 }
 
 template <class T, int R, int SH, int CBV, bool NARROW, bool FLIP>
@@ -777,7 +789,7 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
         q.ih = p.h; q.iw = p.w; q.oh = p.p; q.ow = p.q;
         q.ph = p.ph; q.pw = p.pw;
         q.in_bytes = p.x_bytes;
-        if (p.sh == 1 && depthwise_mfma_pays(q, p.r))
+        if (p.sh == 1 && mfma_pays(dtype, q, p.r))
             return launch_depthwise_mfma(dtype, q, p.r, false, a, b, out, st);
         if (dtype == Half::id) return launch_fwd_t<Half, false>(q, p.r, p.sh, a, b, out, st);
         return launch_fwd_t<BFloat, false>(q, p.r, p.sh, a, b, out, st);
@@ -794,7 +806,7 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
     }
     // stride 1: dy -> dx with the rotated filter
     q.ph = p.r - 1 - p.ph; q.pw = p.s - 1 - p.pw;
-    if (depthwise_mfma_pays(q, p.r))
+    if (mfma_pays(dtype, q, p.r))
         return launch_depthwise_mfma(dtype, q, p.r, true, a, b, out, st);
     if (dtype == Half::id) return launch_fwd_t<Half, true>(q, p.r, 1, a, b, out, st);
     return launch_fwd_t<BFloat, true>(q, p.r, 1, a, b, out, st);

@@ -387,8 +387,9 @@ hipError_t launch_depthwise_tiled(int dtype, int pass, const DWParams &p, const 
 // Stride-1 depthwise on the matrix cores (depthwise_mfma.hip): forward, or the
 // forward correlation with the rotated filter (flip: backward-data); the input
 // and output images, padding and byte sizes are set in p.
-// whether it is the faster kernel for this launch
-bool depthwise_mfma_pays(const DWTParams &p, int r);
+// whether it is the faster kernel for this launch; the LDS-tiled kernel's
+// workgroups x rows per thread, and rows per thread
+bool depthwise_mfma_pays(int dtype, const DWTParams &p, int r, int64_t tiled_work, int tiled_rows);
 hipError_t launch_depthwise_mfma(int dtype, const DWTParams &p, int r, bool flip, const void *in,
                                  const void *w, void *out, hipStream_t st);
 
