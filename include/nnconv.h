@@ -129,7 +129,8 @@ nnconv_status nnconv_output_dims(const nnconv_desc *desc, int32_t *p, int32_t *q
  * matrix-core kernels; such a call also accepts less, down to nothing
  * (forward, backward-data) or the direct kernel's fp32 partials
  * (backward-weight: up to 64 of dw), and then runs on the slow direct
- * kernels. */
+ * kernels (backward-weight without the copies' room but with the partials':
+ * on the same kernels, slower, with the same results). */
 nnconv_status nnconv_workspace_size(const nnconv_desc *desc, nnconv_pass pass, size_t *bytes);
 
 /* Forward pass (definition above): y = alpha * conv(x, w).
@@ -215,12 +216,12 @@ nnconv_status nnconv_wgrad(const nnconv_desc *desc, const void *x, const void *d
  * hipMalloc: nnconv_wgrad with the workspace taken from a library-owned
  * scratch array of NNCONV_NOALLOC_WS_BYTES (64 MiB) instead of an argument.
  * Same arguments (minus ws, ws_bytes), semantics, results (bitwise equal to
- * nnconv_wgrad's with a workspace of the same size) and errors, plus NNCONV_ERR_WORKSPACE, returned before
- * anything is queued, when the geometry needs more workspace than the
- * scratch holds (nnconv_workspace_size(desc, NNCONV_WGRAD) >
- * NNCONV_NOALLOC_WS_BYTES, for channel counts that are multiples of 8; others
- * run on the direct kernels then; every channel-last ResNet-50 layer at batch
- * 256 fits).
+ * nnconv_wgrad's with the workspace that nnconv_workspace_size asks for) and
+ * errors, plus NNCONV_ERR_WORKSPACE, returned before anything is queued, when
+ * the geometry needs more workspace than the scratch holds
+ * (nnconv_workspace_size(desc, NNCONV_WGRAD) > NNCONV_NOALLOC_WS_BYTES;
+ * channel counts that are not multiples of 8, with one group, need no room for
+ * copies there; every channel-last ResNet-50 layer at batch 256 fits).
  *   - The scratch is a device array of the library: every GPU the library
  *     runs on holds one copy from the first call on it (made with that GPU
  *     current, outside graph capture) until the process ends.  The call

@@ -21,6 +21,8 @@ struct Geom {
     // 1: the 64x64 per-tap weight blocks are block-diagonal in 32x32 blocks
     // (super-groups of groups of at most 32 channels)
     int diag32;
+    // backward-weight partials take at most this many bytes (or one split), 0: any
+    int64_t part_limit;
 };
 
 constexpr int64_t MAX_ELEMS = int64_t(1) << 40;
@@ -56,6 +58,7 @@ nnconv_status validate(const nnconv_desc *d, Geom *G) {
     g.layout = d->layout;
     g.dtype = d->dtype;
     g.diag32 = 0;
+    g.part_limit = 0;
     *G = g;
     return NNCONV_OK;
 }
@@ -257,6 +260,8 @@ WgPlan plan_wgrad_fast(const Geom &G) {
     if (max_splits < 1) max_splits = 1;
     if (splits > max_splits) splits = max_splits;
     if (splits > 1024) splits = 1024;
+    if (G.part_limit > 0 && splits > G.part_limit / (G.k * rscg * 4))
+        splits = G.part_limit / (G.k * rscg * 4);
     if (splits < 1) splits = 1;
     const int64_t per = ((iters + splits - 1) / splits) * 64;
     pl.pix_per_split = (int32_t)per;
@@ -406,6 +411,13 @@ bool pad_geom(const Geom &G, nnconv_pass pass, Geom *out) {
         if (stem_shape(T)) S = T;
     }
     if (!fast_pass(S, pass) || !pad_pays(G, S, pass)) return false;
+    if (pass == NNCONV_WGRAD) {
+        // the partials fit the scratch of nnconv_wgrad_noalloc, which then
+        // sums the same products in the same order
+        S.part_limit = NNCONV_NOALLOC_WS_BYTES;
+        if (S.k * S.r * S.s * S.cg * 4 > S.part_limit && direct_ws(G, pass) <= (size_t)S.part_limit)
+            return false;
+    }
     *out = S;
     return true;
 }
@@ -534,15 +546,21 @@ size_t workspace_bytes(const Geom &G, nnconv_pass pass) {
     return pad > need ? pad : need;
 }
 
-// Whether a call of G with this workspace runs as the padded convolution *S
-// (a tensor that needs no copy must be aligned like any fast operand: xa, ya
-// are x / dx and y / dy).
-bool use_pad(const Geom &G, nnconv_pass pass, const void *xa, const void *ya, const void *ws,
-             size_t ws_bytes, Geom *S) {
-    if (!ws || !aligned(ws, 16) || !pad_geom(G, pass, S)) return false;
-    if (ws_bytes < pad_regions(G, *S, pass).total) return false;
-    if (G.layout == NNCONV_NCHW) return true;
-    return (S->c != G.c || aligned(xa, 16)) && (S->k != G.k || aligned(ya, 16));
+// How a call of G with this workspace runs as the padded convolution *S: on
+// padded copies, or, backward-weight with room for the partials only, on the
+// caller's tensors, gathered while they are staged (the same sums in the same
+// order; slower).  A tensor that needs no copy must be aligned like any fast
+// operand: xa, ya are x / dx and y / dy.
+enum PadMode { PAD_NONE = 0, PAD_COPY, PAD_GATHER };
+PadMode use_pad(const Geom &G, nnconv_pass pass, const void *xa, const void *ya, const void *ws,
+                size_t ws_bytes, Geom *S) {
+    if (!ws || !aligned(ws, 16) || !pad_geom(G, pass, S)) return PAD_NONE;
+    if (G.layout == NNCONV_NHWC &&
+        ((S->c == G.c && !aligned(xa, 16)) || (S->k == G.k && !aligned(ya, 16))))
+        return PAD_NONE;
+    const Regions R = pad_regions(G, *S, pass);
+    if (ws_bytes >= R.total) return PAD_COPY;
+    return pass == NNCONV_WGRAD && ws_bytes >= R.total - R.b ? PAD_GATHER : PAD_NONE;
 }
 
 DirectParams direct_params(const Geom &G, float alpha) {
@@ -1139,7 +1157,7 @@ nnconv_status dgrad_fast(const Geom &G, const void *dy, const void *wt, void *dx
 }
 
 nnconv_status wgrad_fast(const Geom &G, const void *x, const void *dy, float *part,
-                         hipStream_t st) {
+                         hipStream_t st, const WGSource *src = nullptr) {
     const WgPlan pl = plan_wgrad_fast(G);
     if (pl.stem) {
         StemParams sp;
@@ -1155,7 +1173,7 @@ nnconv_status wgrad_fast(const Geom &G, const void *x, const void *dy, float *pa
         sp.ph = (int32_t)G.ph; sp.pw = (int32_t)G.pw;
         sp.c = (int32_t)G.c;
         sp.alpha = 1.0f;
-        TRY_HIP(launch_stem_wgrad(G.dtype, sp, part, pl.splits, st));
+        TRY_HIP(launch_stem_wgrad(G.dtype, sp, part, pl.splits, src, st));
         return NNCONV_OK;
     }
     if (pl.cfg == WG_HALO) {
@@ -1175,7 +1193,7 @@ nnconv_status wgrad_fast(const Geom &G, const void *x, const void *dy, float *pa
         hp.splits = pl.splits;
         hp.groups = (int32_t)G.g;
         hp.diag32 = G.diag32;
-        TRY_HIP(launch_wgrad_halo(G.dtype, hp, st));
+        TRY_HIP(launch_wgrad_halo(G.dtype, hp, src, st));
         return NNCONV_OK;
     }
     WGParams p;
@@ -1199,7 +1217,7 @@ nnconv_status wgrad_fast(const Geom &G, const void *x, const void *dy, float *pa
     p.group_inner = group_inner(G, 8);
     p.splits = pl.splits;
     p.pix_per_split = pl.pix_per_split;
-    TRY_HIP(launch_wgrad_splitk(G.dtype, pl.cfg, p, st));
+    TRY_HIP(launch_wgrad_splitk(G.dtype, pl.cfg, p, src, st));
     return NNCONV_OK;
 }
 
@@ -1434,20 +1452,30 @@ nnconv_status pad_dgrad(const Geom &G, const Geom &S, const void *dy, const void
 
 nnconv_status pad_wgrad(const Geom &G, const Geom &S, const void *x, const void *dy, void *dw,
                         int out_code, float inv_loss_scale, int accumulate, int32_t *flag,
-                        char *ws, hipStream_t st) {
+                        char *ws, PadMode mode, hipStream_t st) {
     const Regions R = pad_regions(G, S, NNCONV_WGRAD);
     const bool nchw = G.layout == NNCONV_NCHW;
+    const auto reduce = [&](const float *part) {
+        return hip_status(launch_wgrad_reduce_pick(
+            part, plan_wgrad_fast(S).splits, S.k * S.r * S.s * S.c, G.k, (int32_t)(G.r * G.s),
+            (int32_t)G.c, (int32_t)S.c, false, dw, out_code, inv_loss_scale, accumulate, flag, nchw,
+            st));
+    };
+    if (mode == PAD_GATHER) {
+        const DirectParams P = direct_params(G, 1.0f);
+        const WGSource src = {
+            {(const uint16_t *)x, P.xs[0], P.xs[1], P.xs[2], P.xs[3], (int32_t)G.c},
+            {(const uint16_t *)dy, P.ys[0], P.ys[1], P.ys[2], P.ys[3], (int32_t)G.k}};
+        const nnconv_status s = wgrad_fast(S, x, dy, (float *)ws, st, &src);
+        return s != NNCONV_OK ? s : reduce((const float *)ws);
+    }
     const bool own_x = !nchw && S.c == G.c, own_y = !nchw && S.k == G.k;
     if (!own_x) TRY_HIP(pad_in(nchw, x, ws + R.a, G.n, G.c, G.h * G.w, S.c, st));
     if (!own_y) TRY_HIP(pad_in(nchw, dy, ws + R.c, G.n, G.k, G.p * G.q, S.k, st));
     float *part = (float *)(ws + R.b);
     const nnconv_status s =
         wgrad_fast(S, own_x ? x : ws + R.a, own_y ? dy : ws + R.c, part, st);
-    if (s != NNCONV_OK) return s;
-    return hip_status(launch_wgrad_reduce_pick(
-        part, plan_wgrad_fast(S).splits, S.k * S.r * S.s * S.c, G.k, (int32_t)(G.r * G.s),
-        (int32_t)G.c, (int32_t)S.c, false, dw, out_code, inv_loss_scale, accumulate, flag, nchw,
-        st));
+    return s != NNCONV_OK ? s : reduce(part);
 }
 
 }  // namespace
@@ -1542,7 +1570,7 @@ static nnconv_status fwd_impl(const nnconv_desc *desc, const void *x, const void
     const bool fast = fast_pass(G, NNCONV_FWD) && aligned(x, 16) && aligned(w, 16) && aligned(y, 16) &&
                       (G.layout == NNCONV_NHWC || aligned(ws, 16));
     Geom S;
-    if (!fast && use_pad(G, NNCONV_FWD, x, y, ws, ws_bytes, &S))
+    if (!fast && use_pad(G, NNCONV_FWD, x, y, ws, ws_bytes, &S) == PAD_COPY)
         return pad_fwd(G, S, x, w, y, alpha, (char *)ws, s);
     if (!fast) return hip_status(launch_direct_fwd(G.dtype, direct_params(G, alpha), x, w, y, s));
     const Regions R = fast_regions(G, NNCONV_FWD);
@@ -1606,7 +1634,7 @@ static nnconv_status dgrad_impl(const nnconv_desc *desc, const void *dy, const v
     const bool fast = fast_shape(G) && aligned(dy, 16) && aligned(w, 16) && aligned(dx, 16) &&
                       aligned(ws, 16);
     Geom S;
-    if (!fast && use_pad(G, NNCONV_DGRAD, dx, dy, ws, ws_bytes, &S))
+    if (!fast && use_pad(G, NNCONV_DGRAD, dx, dy, ws, ws_bytes, &S) == PAD_COPY)
         return pad_dgrad(G, S, dy, w, dx, alpha, (char *)ws, s);
     if (!fast)
         return hip_status(launch_direct_dgrad(G.dtype, direct_params(G, alpha), dy, w, dx, s));
@@ -1710,9 +1738,11 @@ static nnconv_status wgrad_run(const Geom &G, const void *x, const void *dy, voi
     const bool fast = fast_pass(G, NNCONV_WGRAD) && aligned(x, 16) && aligned(dy, 16) &&
                       aligned(ws, 16);
     Geom S;
-    if (!fast && use_pad(G, NNCONV_WGRAD, x, dy, ws, ws_bytes, &S))
+    const PadMode pad =
+        fast ? PAD_NONE : use_pad(G, NNCONV_WGRAD, x, dy, ws, ws_bytes, &S);
+    if (pad != PAD_NONE)
         return pad_wgrad(G, S, x, dy, dw, out_code, inv_loss_scale, accumulate, overflow_flag,
-                         (char *)ws, s);
+                         (char *)ws, pad, s);
     if (!fast) {
         const int32_t splits = plan_wgrad_direct_splits(G);
         float *part = (float *)ws;

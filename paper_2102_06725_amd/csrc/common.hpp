@@ -193,4 +193,26 @@ __device__ __forceinline__ void dma16(uint32_t lds_addr, uint32_t voff, i32x4 de
         : "memory");
 }
 
+// A 16-bit tensor of any layout, read where it lies: element (n, c, h, w) at
+// p[n * sn + c * sc + h * sh + w * sw]; channels from `c` on are zero.
+struct StridedTensor {
+    const uint16_t *p;
+    int64_t sn, sc, sh, sw;
+    int32_t c;
+};
+
+__device__ __forceinline__ uint32_t load_strided(const StridedTensor &t, int n, int c, int h, int w) {
+    return c < t.c ? t.p[n * t.sn + c * t.sc + h * t.sh + w * t.sw] : 0u;
+}
+
+// 8 consecutive channels of a pixel, as a channel-last copy with padded
+// channels would hold them.
+__device__ __forceinline__ u32x4 gather_channels(const StridedTensor &t, int n, int c, int h, int w) {
+    u32x4 v;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        v[d] = load_strided(t, n, c + 2 * d, h, w) | (load_strided(t, n, c + 2 * d + 1, h, w) << 16);
+    return v;
+}
+
 }  // namespace nnconv

@@ -184,11 +184,20 @@ bool stem_fwd_supported(int r, int s, int sh, int sw);
 bool stem4_supported(const StemParams &p);
 // cus: workgroups to launch at most (one per CU; the kernel loops over tiles)
 hipError_t launch_stem_fwd(int dtype, const StemParams &p, int cus, hipStream_t st);
+// Where the operands of a backward-weight launch are taken from: the
+// channel-last tensors of its parameters, or, with a source, the caller's
+// tensors of any layout and channel count, gathered while they are staged.  The
+// same products are summed in the same order either way.
+struct WGSource {
+    StridedTensor x, dy;
+};
+struct NoSource {};
+
 // Backward-weight partials for the same shapes: y holds dy; splits
 // workgroups each write part[split][64][r*s*c] (no loss-scale step); with
 // 4-channel pixels splits is even and splits / 2 workgroups write two each.
 hipError_t launch_stem_wgrad(int dtype, const StemParams &p, float *part, int splits,
-                             hipStream_t st);
+                             const WGSource *src, hipStream_t st);
 
 // Backward-weight split-K partial sums:
 //   ws[split][k][j] = sum over pixels of this split of dy[pix, k] * xcol[pix, j]
@@ -215,7 +224,8 @@ enum WGConfig { WG_128x128 = 0, WG_64x128 = 1, WG_256x256 = 2, WG_128x128S = 3,
                 WG_HALO = 5 };   // wgrad_halo.hip (3x3 stride-1 "same", 64 -> 64 channels)
 
 // Pixel ranges of pix_per_split (a multiple of 32) pixels each.
-hipError_t launch_wgrad_splitk(int dtype, WGConfig cfg, WGParams &p, hipStream_t st);
+hipError_t launch_wgrad_splitk(int dtype, WGConfig cfg, WGParams &p, const WGSource *src,
+                               hipStream_t st);
 
 // Backward-weight of a 3x3 stride-1 convolution with padding 1 and groups of
 // 64 input and 64 output channels (wgrad_halo.hip): blocks of rb whole image
@@ -240,7 +250,7 @@ struct WGHParams {
     int32_t groups;                // of 64 channels, side by side in x and dy pixels
     int32_t diag32;
 };
-hipError_t launch_wgrad_halo(int dtype, const WGHParams &p, hipStream_t st);
+hipError_t launch_wgrad_halo(int dtype, const WGHParams &p, const WGSource *src, hipStream_t st);
 
 // dw[e'] = (accumulate ? dw[e'] : 0) + inv_scale * sum_{s < splits} ws[s][e]
 // over e < count = K * R*S*Cg; e' = e for [K][R][S][Cg] output, or the

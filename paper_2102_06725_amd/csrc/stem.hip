@@ -18,6 +18,8 @@
 // GEMM view per tile: rows = 256 output pixels, columns = 64 output channels,
 // reduction = taps x 8 channels; one v_mfma_f32_32x32x16 k-step covers two
 // taps, so an operand fragment is one 16-byte LDS read per lane.
+#include <type_traits>
+
 #include "launch.hpp"
 
 namespace nnconv {
@@ -253,9 +255,11 @@ __device__ __forceinline__ u32x4 keep_pixels(int n) {
 }
 }  // namespace stem
 
-// EDGE: P or Q is no multiple of 16.
-template <class T, int R, int S, int SH, int SW, bool EDGE>
-__global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(const StemParams P, float *part) {
+// EDGE: P or Q is no multiple of 16.  Src: NoSource, or WGSource (operands
+// gathered from the caller's tensors).
+template <class T, int R, int S, int SH, int SW, bool EDGE, class Src>
+__global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(const StemParams P, float *part, const Src src) {
+    constexpr bool GATHER = std::is_same<Src, WGSource>::value;
     using namespace stem;
     using G = Geo<R, S, SH, SW>;
     constexpr int CB = (G::TAPS + 3) / 4;            // 32-column blocks (4 taps each)
@@ -300,6 +304,10 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
                 const int ih = ih0 + pr, iw = iw0 + pc;
                 const bool ok = pr < prv && pc < pcv && (unsigned)ih < (unsigned)P.h &&
                                 (unsigned)iw < (unsigned)P.w;
+                if constexpr (GATHER) {
+                    lds[b * BUF_ENT + e] = ok ? gather_channels(src.x, n, 0, ih, iw) : u32x4{};
+                    continue;
+                }
                 const uint32_t off = ok ? (uint32_t)((n * P.h + ih) * P.w + iw) * 16u : OOB_OFFSET;
                 dma16(pb + (uint32_t)e0 * 16u, off, dx);
             }
@@ -313,6 +321,11 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
             const int p = e >> 3, q8 = e & 7;
             const int lchunk = (((q8 >> 2) ^ ((p >> 1) & 1)) << 2) | (q8 & 3);
             const int oh = tp * TH + (p >> 4), ow = tq * TW + (p & 15);
+            if constexpr (GATHER) {
+                lds[b * BUF_ENT + G::P_ENT + e] =
+                    oh < P.p && ow < P.q ? gather_channels(src.dy, n, lchunk * 8, oh, ow) : u32x4{};
+                continue;
+            }
             const uint32_t off = (oh < P.p && ow < P.q)
                                      ? (uint32_t)(((n * P.p + oh) * P.q + ow) * K + lchunk * 8) * 2u
                                      : OOB_OFFSET;
@@ -355,7 +368,7 @@ __global__ __launch_bounds__(stem::WG_WAVES * 64, 1) void stem_wgrad_kernel(cons
         const u32x4 keep = EDGE ? keep_pixels(tile_cols(tile) - pix_half) : u32x4{};
 #pragma unroll
         for (int row = 0; row < TH; ++row) {   // one k16 step = one tile row of 16 pixels
-            if (EDGE && row >= vh) break;
+            if (EDGE && row >= vh) continue;
             u32x4 fa[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -578,9 +591,10 @@ __global__ __launch_bounds__(stem::FWD_WAVES * 64, 1) void stem_fwd4_kernel(cons
 // waves 4-7 do the same for the odd tile rows, so each k-step's dy
 // fragments are read by four waves only, and the workgroup writes two
 // partials (even and odd rows), part[2 * blockIdx.x + half].
-template <class T, bool EDGE>
+template <class T, bool EDGE, class Src>
 __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(const StemParams P,
-                                                                            float *part) {
+                                                                            float *part, const Src src) {
+    constexpr bool GATHER = std::is_same<Src, WGSource>::value;
     using namespace stem;
     constexpr int DY_ENT = TH * TW * K / 8;
     constexpr int BUF_ENT = P4_ENT + DY_ENT;
@@ -617,6 +631,17 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
                 const int ih = ih0 + pr, iw = col0 + 2 * jc;
                 const bool ok = pr < prv && jc < jcv && (unsigned)ih < (unsigned)P.h &&
                                 (unsigned)iw < (unsigned)P.w;
+                if constexpr (GATHER) {  // two pixels of 4 channels
+                    u32x4 v = {};
+                    if (ok) {
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)
+                            v[d] = load_strided(src.x, n, 2 * (d & 1), ih, iw + (d >> 1)) |
+                                   (load_strided(src.x, n, 2 * (d & 1) + 1, ih, iw + (d >> 1)) << 16);
+                    }
+                    lds[b * BUF_ENT + e] = v;
+                    continue;
+                }
                 const uint32_t off = ok ? (uint32_t)((n * P.h + ih) * P.w + iw) * 8u : OOB_OFFSET;
                 dma16(pb + (uint32_t)e0 * 16u, off, dx);
             }
@@ -628,6 +653,11 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
             const int p = e >> 3, q8 = e & 7;
             const int lchunk = (((q8 >> 2) ^ ((p >> 1) & 1)) << 2) | (q8 & 3);
             const int oh = tp * TH + (p >> 4), ow = tq * TW + (p & 15);
+            if constexpr (GATHER) {
+                lds[b * BUF_ENT + P4_ENT + e] =
+                    oh < P.p && ow < P.q ? gather_channels(src.dy, n, lchunk * 8, oh, ow) : u32x4{};
+                continue;
+            }
             const uint32_t off = (oh < P.p && ow < P.q)
                                      ? (uint32_t)(((n * P.p + oh) * P.q + ow) * K + lchunk * 8) * 2u
                                      : OOB_OFFSET;
@@ -667,7 +697,7 @@ __global__ __launch_bounds__(stem::WG4_WAVES * 64, 1) void stem_wgrad4_kernel(co
 #pragma unroll
         for (int rr = 0; rr < TH / 2; ++rr) {   // one k16 step = one tile row of 16 pixels
             const int row = 2 * rr + half;
-            if (EDGE && row >= vh) break;
+            if (EDGE && row >= vh) continue;
             u32x4 fa[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -734,28 +764,34 @@ bool stem4_supported(const StemParams &p) {
     return stem_fwd_supported(p.r, p.s, p.sh, p.sw) && p.pw % 2 == 1 && p.w % 2 == 0;
 }
 
-template <class T, bool EDGE>
-static hipError_t launch_stem_wgrad_t(const StemParams &p, float *part, int splits, hipStream_t st) {
+template <class T, bool EDGE, class Src>
+static hipError_t launch_stem_wgrad_cfg(const StemParams &p, float *part, int splits, const Src &src,
+                                        hipStream_t st) {
     if (p.c == 4)
-        hipLaunchKernelGGL((stem_wgrad4_kernel<T, EDGE>), dim3(splits / 2), dim3(stem::WG4_WAVES * 64), 0,
-                           st, p, part);
+        hipLaunchKernelGGL((stem_wgrad4_kernel<T, EDGE, Src>), dim3(splits / 2),
+                           dim3(stem::WG4_WAVES * 64), 0, st, p, part, src);
     else
-        hipLaunchKernelGGL((stem_wgrad_kernel<T, 7, 7, 2, 2, EDGE>), dim3(splits),
-                           dim3(stem::WG_WAVES * 64), 0, st, p, part);
+        hipLaunchKernelGGL((stem_wgrad_kernel<T, 7, 7, 2, 2, EDGE, Src>), dim3(splits),
+                           dim3(stem::WG_WAVES * 64), 0, st, p, part, src);
     return hipGetLastError();
 }
 
+template <class T>
+static hipError_t launch_stem_wgrad_t(const StemParams &p, float *part, int splits,
+                                      const WGSource *src, hipStream_t st) {
+    const bool edge = p.p % stem::TH != 0 || p.q % stem::TW != 0;
+    if (src) return launch_stem_wgrad_cfg<T, true>(p, part, splits, *src, st);  // right for whole tiles too
+    return edge ? launch_stem_wgrad_cfg<T, true>(p, part, splits, NoSource{}, st)
+                : launch_stem_wgrad_cfg<T, false>(p, part, splits, NoSource{}, st);
+}
+
 hipError_t launch_stem_wgrad(int dtype, const StemParams &p, float *part, int splits,
-                             hipStream_t st) {
+                             const WGSource *src, hipStream_t st) {
     if (p.c == 4 ? !stem4_supported(p) || splits < 2 || splits % 2 != 0
                  : !stem_fwd_supported(p.r, p.s, p.sh, p.sw) || splits < 1)
         return hipErrorInvalidValue;
-    const bool edge = p.p % stem::TH != 0 || p.q % stem::TW != 0;
-    if (dtype == Half::id)
-        return edge ? launch_stem_wgrad_t<Half, true>(p, part, splits, st)
-                    : launch_stem_wgrad_t<Half, false>(p, part, splits, st);
-    return edge ? launch_stem_wgrad_t<BFloat, true>(p, part, splits, st)
-                : launch_stem_wgrad_t<BFloat, false>(p, part, splits, st);
+    return dtype == Half::id ? launch_stem_wgrad_t<Half>(p, part, splits, src, st)
+                             : launch_stem_wgrad_t<BFloat>(p, part, splits, src, st);
 }
 
 hipError_t launch_stem_fwd(int dtype, const StemParams &p, int cus, hipStream_t st) {

@@ -95,8 +95,10 @@ __device__ __forceinline__ u32x4 tr_frag(uint32_t a0, uint32_t a1) {
 // last row are left out, and the input fragments of a k-step across it are
 // masked: dy is staged as zeros there, which must not meet an inf or NaN of the
 // last input row.
-template <class T, int WAVES, int NBUF, bool DIAG, bool EDGE>
-__global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHParams P) {
+// Src: NoSource, or WGSource (operands gathered from the caller's tensors).
+template <class T, int WAVES, int NBUF, bool DIAG, bool EDGE, class Src>
+__global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHParams P, const Src S) {
+    constexpr bool GATHER = std::is_same<Src, WGSource>::value;
     using namespace wgh;
     static_assert(WAVES == 4 || WAVES == 8, "tap groups");
     static_assert(NBUF == 2 || NBUF == 3, "buffers");
@@ -176,6 +178,18 @@ __global__ __launch_bounds__(WAVES * 64, 1) void wgrad_halo_kernel(const WGHPara
                 const int ih = h0 + (int)((pk[j] >> 16) & 0xFFu) - 1;
                 const uint32_t chb = ((pk[j] >> 24) & 15u) * 16u;
                 const bool ok = (pk[j] >> 31) != 0 && (unsigned)ih < (unsigned)H;
+                if constexpr (GATHER) {
+                    const int col = rel - (ih - h0) * W, c = (int)(chb >> 1);
+                    u32x4 v = {};
+                    if (ok) {
+                        if (e0 < dys)
+                            v = gather_channels(S.dy, n, c, ih, col);
+                        else
+                            v = gather_channels(S.x, n, c, ih, col);
+                    }
+                    lds[buf * nslot + e0 + lane] = v;
+                    continue;
+                }
                 if (e0 < dys) {
                     const uint32_t off =
                         ok ? (uint32_t)(pix0 + rel) * (uint32_t)P.k_stride * 2u + goff + chb
@@ -345,27 +359,33 @@ int wgh_slots(int rb, int w) {
 // 8 waves and 3 buffers: on the 56x56 layer at batch 256, 86 us against
 // 87 with 2 buffers and 117-120 with 4 waves (one per SIMD does not hide
 // the transposing reads' latency)
-template <class T, bool EDGE>
-static hipError_t launch_wgh(const WGHParams &p, hipStream_t st) {
+template <class T, bool DIAG, bool EDGE, class Src>
+static hipError_t launch_wgh(const WGHParams &p, const Src &src, hipStream_t st) {
     constexpr int WV = 8, NB = 3;
     const dim3 grid((uint32_t)p.splits, (uint32_t)p.groups);
-    if (p.diag32)
-        hipLaunchKernelGGL((wgrad_halo_kernel<T, WV, NB, true, EDGE>), grid, dim3(WV * 64), 0, st, p);
-    else
-        hipLaunchKernelGGL((wgrad_halo_kernel<T, WV, NB, false, EDGE>), grid, dim3(WV * 64), 0, st, p);
+    hipLaunchKernelGGL((wgrad_halo_kernel<T, WV, NB, DIAG, EDGE, Src>), grid, dim3(WV * 64), 0, st, p,
+                       src);
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad_halo(int dtype, const WGHParams &p, hipStream_t st) {
+template <class T>
+static hipError_t launch_wgh_t(const WGHParams &p, const WGSource *src, hipStream_t st) {
+    const bool edge = p.h % p.rb != 0;
+    if (src) return launch_wgh<T, false, true>(p, *src, st);  // right for whole blocks too
+    if (p.diag32)
+        return edge ? launch_wgh<T, true, true>(p, NoSource{}, st)
+                    : launch_wgh<T, true, false>(p, NoSource{}, st);
+    return edge ? launch_wgh<T, false, true>(p, NoSource{}, st)
+                : launch_wgh<T, false, false>(p, NoSource{}, st);
+}
+
+hipError_t launch_wgrad_halo(int dtype, const WGHParams &p, const WGSource *src, hipStream_t st) {
     if (p.rb < 1 || p.w < 1 || p.rb * p.w > wgh::MAXP || (p.rb * p.w) % 16 != 0 ||
         wgh_slots(p.rb, p.w) > WGH_MAX_SLOTS || p.blocks_per_split < 1 || p.splits < 1 ||
         p.groups < 1 || p.groups > 65535 || p.c_stride < 64 * p.groups ||
-        p.k_stride < 64 * p.groups)
+        p.k_stride < 64 * p.groups || (src && (p.groups != 1 || p.diag32)))
         return hipErrorInvalidValue;
-    const bool edge = p.h % p.rb != 0;
-    if (dtype == Half::id)
-        return edge ? launch_wgh<Half, true>(p, st) : launch_wgh<Half, false>(p, st);
-    return edge ? launch_wgh<BFloat, true>(p, st) : launch_wgh<BFloat, false>(p, st);
+    return dtype == Half::id ? launch_wgh_t<Half>(p, src, st) : launch_wgh_t<BFloat>(p, src, st);
 }
 
 }  // namespace nnconv

@@ -15,6 +15,8 @@
 // read fall in 4 different 64-byte bank segments.
 // Pixels are split into `splits` ranges; each range writes an fp32 partial
 // tile to the workspace (summed later in a fixed order).
+#include <type_traits>
+
 #include "launch.hpp"
 
 namespace nnconv {
@@ -47,11 +49,13 @@ __device__ __forceinline__ uint32_t tile_off(int p, int co) {
 // and input channels lie in the same half of a 64-channel group are kept by
 // the reduction, so each wave computes and writes only the column block that
 // matches its 32 rows.
-template <class T, int BM, int BN, int WM, int WN, int BKP, int STAGES, bool DIAG>
+// Src: NoSource, or WGSource (operands gathered from the caller's tensors).
+template <class T, int BM, int BN, int WM, int WN, int BKP, int STAGES, bool DIAG, class Src>
 __global__ __launch_bounds__(WM * WN * 64, (STAGES * BKP * (BM + BN) * 2 > 80 * 1024) ? 1
                                            : (STAGES * BKP * (BM + BN) * 2 > 40 * 1024) ? 2
                                                                                        : 4)
-void wgrad_splitk_kernel(const WGParams P) {
+void wgrad_splitk_kernel(const WGParams P, const Src S) {
+    constexpr bool GATHER = std::is_same<Src, WGSource>::value;
     using namespace wgs;
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -142,6 +146,14 @@ void wgrad_splitk_kernel(const WGParams P) {
         for (int j = 0; j < A_LD; ++j) {
             const int pix = base + a_row[j];
             const bool ok = a_ok[j] && pix < pix_end;
+            if constexpr (GATHER) {
+                const int n = (int)fdiv((uint32_t)pix, P.div_pq);
+                const int rm = pix - n * (P.p * P.q);
+                const int pp = (int)fdiv((uint32_t)rm, P.div_q);
+                lds[buf * (STAGE_BYTES / 16) + (wave * A_LD + j) * 64 + lane] =
+                    ok ? gather_channels(S.dy, n, (int)(a_col[j] >> 1), pp, rm - pp * P.q) : u32x4{};
+                continue;
+            }
             const uint32_t off = (uint32_t)pix * (uint32_t)P.k * 2u + a_col[j];
             dma16(sb + (uint32_t)((wave * A_LD + j) * 1024), ok ? off : OOB_OFFSET, ddy);
         }
@@ -157,6 +169,11 @@ void wgrad_splitk_kernel(const WGParams P) {
             const int h = pp * P.sh + b_dh[j];
             const int w = qq * P.sw + b_dw[j];
             ok = ok && (unsigned)h < (unsigned)P.h && (unsigned)w < (unsigned)P.w;
+            if constexpr (GATHER) {
+                lds[(buf * STAGE_BYTES + A_BYTES) / 16 + (wave * B_LD + j) * 64 + lane] =
+                    ok ? gather_channels(S.x, n, (int)(b_col[j] >> 1), h, w) : u32x4{};
+                continue;
+            }
             const uint32_t off = (uint32_t)((n * P.h + h) * P.w + w) * (uint32_t)P.c * 2u + b_col[j];
             dma16(sb + (uint32_t)(A_BYTES + (wave * B_LD + j) * 1024), ok ? off : OOB_OFFSET, dx);
         }
@@ -256,14 +273,23 @@ void wgrad_splitk_kernel(const WGParams P) {
 }
 
 template <class T, int BM, int BN, int WM, int WN, int BKP, int STAGES, bool DIAG = false>
-static hipError_t launch_wgs(WGParams &p, hipStream_t st) {
+static hipError_t launch_wgs(WGParams &p, const WGSource *src, hipStream_t st) {
     p.tiles_m = (p.kg + BM - 1) / BM;
     p.tiles_n = (p.rscg + BN - 1) / BN;
     const int64_t nb = (int64_t)p.tiles_m * p.tiles_n * p.splits * p.groups;
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((wgrad_splitk_kernel<T, BM, BN, WM, WN, BKP, STAGES, DIAG>), dim3((uint32_t)nb),
-                       dim3(WM * WN * 64), 0, st, p);
+    if constexpr (!DIAG) {
+        if (src) {
+            if (p.groups != 1) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((wgrad_splitk_kernel<T, BM, BN, WM, WN, BKP, STAGES, DIAG, WGSource>),
+                               dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p, *src);
+            return hipGetLastError();
+        }
+    }
+    if (src) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((wgrad_splitk_kernel<T, BM, BN, WM, WN, BKP, STAGES, DIAG, NoSource>),
+                       dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p, NoSource{});
     return hipGetLastError();
 }
 
@@ -279,20 +305,21 @@ static hipError_t launch_wgs(WGParams &p, hipStream_t st) {
 // fragment-read latency; on the ResNet-50 3x3 layers with 128 filters this
 // cut the backward-weight time by a fifth against 4 waves of 64x64.
 template <class T>
-static hipError_t launch_wgs_t(WGConfig cfg, WGParams &p, hipStream_t st) {
+static hipError_t launch_wgs_t(WGConfig cfg, WGParams &p, const WGSource *src, hipStream_t st) {
     switch (cfg) {
-        case WG_64x128: return launch_wgs<T, 64, 128, 2, 2, 64, 1>(p, st);
-        case WG_64x128D: return launch_wgs<T, 64, 128, 2, 2, 64, 1, true>(p, st);
-        case WG_256x256: return launch_wgs<T, 256, 256, 4, 4, 32, 2>(p, st);
-        case WG_128x128S: return launch_wgs<T, 128, 128, 2, 2, 64, 1>(p, st);
+        case WG_64x128: return launch_wgs<T, 64, 128, 2, 2, 64, 1>(p, src, st);
+        case WG_64x128D: return launch_wgs<T, 64, 128, 2, 2, 64, 1, true>(p, src, st);
+        case WG_256x256: return launch_wgs<T, 256, 256, 4, 4, 32, 2>(p, src, st);
+        case WG_128x128S: return launch_wgs<T, 128, 128, 2, 2, 64, 1>(p, src, st);
         case WG_128x128:
-        default: return launch_wgs<T, 128, 128, 2, 4, 64, 2>(p, st);
+        default: return launch_wgs<T, 128, 128, 2, 4, 64, 2>(p, src, st);
     }
 }
 
-hipError_t launch_wgrad_splitk(int dtype, WGConfig cfg, WGParams &p, hipStream_t st) {
-    if (dtype == Half::id) return launch_wgs_t<Half>(cfg, p, st);
-    return launch_wgs_t<BFloat>(cfg, p, st);
+hipError_t launch_wgrad_splitk(int dtype, WGConfig cfg, WGParams &p, const WGSource *src,
+                               hipStream_t st) {
+    if (dtype == Half::id) return launch_wgs_t<Half>(cfg, p, src, st);
+    return launch_wgs_t<BFloat>(cfg, p, src, st);
 }
 
 }  // namespace nnconv

@@ -84,3 +84,44 @@ def test_noalloc_accumulate_and_16bit_output(nnlib, oracle_lib):
                                     dw_old=U.to_nchw(case, "dw", I.from_bits(old, I.F16)))
     got = U.to_nchw(case, "dw", I.from_bits(gb, I.F16))
     assert orc.rel_err(got, ref) <= U.TOL[I.F16]
+
+
+# Channel counts that are not multiples of 8 whose channel-last copies pass the
+# scratch's 64 MiB: the operands are gathered from the caller's tensors there.
+ODD = [
+    # name, n, c, h, w, k, r, stride, pad, kernel of the partials
+    ("rgb_stem4", 32, 3, 224, 224, 64, 7, 2, 3, "stem_wgrad4_kernel"),
+    ("rgb_stem4_ragged", 40, 3, 203, 222, 61, 7, 2, 3, "stem_wgrad4_kernel"),
+    ("stem8", 40, 7, 200, 203, 64, 7, 2, 3, "stem_wgrad_kernel"),
+    ("rows", 72, 60, 100, 56, 63, 3, 1, 1, "wgrad_halo_kernel"),
+    ("splitk_64", 12, 66, 190, 187, 21, 3, 1, 1, "wgrad_splitk_kernel"),
+    ("splitk_128", 24, 130, 61, 63, 255, 1, 1, 0, "wgrad_splitk_kernel"),
+    ("splitk_128_s2", 20, 333, 59, 61, 130, 3, 2, 2, "wgrad_splitk_kernel"),
+    ("splitk_256", 11, 255, 65, 75, 255, 3, 1, 1, "wgrad_splitk_kernel"),  # 29 splits would pass it alone
+]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("s", ODD, ids=[s[0] for s in ODD])
+def test_noalloc_equals_workspace_call_on_odd_channels(nnlib, s, layout, dtype):
+    name, n, c, h, w, k, r, stride, pad, kernel = s
+    t = U.torch()
+    case = U.Case(I.Layer(name, n, c, h, w, k, r, r, stride, pad), layout=layout, dtype=dtype)
+    L, d = case.layer, case.desc()
+    U.assert_runs(case, "wgrad", kernel)
+    st, nb = nc.nnconv_workspace_size(d, nc.NNCONV_WGRAD)
+    nc.check(st)
+    assert nb > nc.NNCONV_NOALLOC_WS_BYTES or layout == "nhwc"
+    half = t.float16 if dtype == I.F16 else t.bfloat16
+    g = t.Generator(device="cuda").manual_seed(17)
+    x = t.randn(n * c * h * w, generator=g, device="cuda").to(half)
+    dy = t.randn(n * k * L.p * L.q, generator=g, device="cuda").to(half)
+    ws = t.empty(nb, dtype=t.uint8, device="cuda")
+    dw = [t.empty(k * c * r * r, device="cuda") for _ in range(2)]
+    flag = t.zeros(1, dtype=t.int32, device="cuda")
+    nc.check(nc.nnconv_wgrad(d, x.data_ptr(), dy.data_ptr(), dw[0].data_ptr(), nc.NNCONV_F32, 0.25, 0, flag.data_ptr(),
+                             ws.data_ptr(), nb, U.stream()))
+    nc.check(nc.nnconv_wgrad_noalloc(d, x.data_ptr(), dy.data_ptr(), dw[1].data_ptr(), nc.NNCONV_F32, 0.25, 0,
+                                     flag.data_ptr(), U.stream()))
+    assert t.equal(dw[0], dw[1]) and t.isfinite(dw[0]).all() and int(flag.item()) == 0
