@@ -603,7 +603,7 @@ bool tiny_shape(const Geom &G, int pass) {
     // without copies the other path is few launches
     const bool fast = fast_pass(G, (nnconv_pass)pass);
     const DirectParams P = direct_params(G, 1.0f);
-    if (!tiny_pays(P, pass, G.layout == NNCONV_NHWC && fast)) return false;
+    if (!tiny_pays(P, pass, fast, G.layout == NNCONV_NHWC && fast)) return false;
     // channel counts that would be padded or run on the direct kernels: those
     // are the faster ones for a few channels (1x1 2 -> 3 over 2 images of
     // 237x35, backward-data: 8.6 us against 11.3)

@@ -280,12 +280,17 @@ hipError_t go_pass(int pass, const DirectParams &p, const void *a, const void *b
 
 // A step costs about 2 us whatever the layer, and from 512 workgroups (two
 // rounds of four per CU's worth of waves) on they queue; against that stand the
-// launches of the other path.  single: that path is one launch of a
-// matrix-core kernel for the forward pass (4.7 us), three for backward-data
-// (8.8), two for backward-weight (7.8): worth 0, 3 and 2 steps; with the copies
-// of channel-first layout or padded channels 10.5, 13 and 11 us: worth 4, 4, 3.
-bool tiny_pays(const DirectParams &p, int pass, bool single) {
+// launches of the other path.  fast: that path needs no padded channels.  single:
+// it is one launch of a matrix-core kernel for the forward pass (4.7 us), three
+// for backward-data (8.8), two for backward-weight (7.8): worth 0, 3 and 2 steps;
+// with the copies of channel-first layout or padded channels 10.5, 13 and 11 us:
+// worth 4, 4, 3.
+// Backward-weight of channel-first filters of several taps scatters its stores,
+// which the split reduction's copy does not: 900 workgroups 12.9 us against 14.3
+// there, 1152 16.4 against 14.0, 1250 20.0 against 13.9.
+bool tiny_pays(const DirectParams &p, int pass, bool fast, bool single) {
     const TinyGrid g = grid_of(p, pass);
+    if (pass == 2 && fast && p.wsd[1] > 1 && g.wgs > 1024) return false;
     const int limit = single ? (pass == 0 ? 0 : pass == 1 ? 3 : 2) : (pass == 2 ? 3 : 4);
     return g.steps * (g.wgs > 512 ? g.wgs : 512) <= (int64_t)limit * 512;
 }

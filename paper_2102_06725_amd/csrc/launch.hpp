@@ -283,7 +283,7 @@ hipError_t launch_direct_wgrad(int dtype, const DirectParams &p, const void *x, 
 // layout (igemm_tiny.hip): pass 0 out = y from a = x, b = w; 1 out = dx from
 // a = dy, b = w; 2 out = dw (0 fp16, 1 bf16, 2 fp32) from a = dy, b = x with the
 // loss-scale step of launch_wgrad_reduce.
-bool tiny_pays(const DirectParams &p, int pass, bool single);
+bool tiny_pays(const DirectParams &p, int pass, bool fast, bool single);
 double tiny_us(const DirectParams &p, int pass);
 hipError_t launch_igemm_tiny(int dtype, int pass, const DirectParams &p, const void *a,
                              const void *b, void *out, int out_code, float inv_scale,

@@ -44,6 +44,15 @@ def test_tiny_parity(nnlib, oracle_lib, s, layout, dtype):
     U.full_parity(_case(s, layout, dtype))
 
 
+@pytest.mark.parametrize("c,kernel", [(80, "igemm_tiny_kernel"), (160, "igemm_tiny_kernel"), (192, "wgrad_splitk_kernel")])
+def test_tiny_channel_first_backward_weight_limit(nnlib, oracle_lib, c, kernel):
+    """Up to 1024 workgroups of filters of several taps: 450, 900 and 1080 here."""
+    case = U.Case(I.Layer("limit", 1, c, 8, 22, 160, 3, 3, 1, 1), layout="nchw", loss_scale=64.0, x_kind="normal",
+                  cfg=101, layer_id=20)
+    U.assert_runs(case, "wgrad", kernel)
+    U.full_parity(case, passes=("wgrad",))
+
+
 @pytest.mark.parametrize("layout", ["nchw", "nhwc"])
 def test_tiny_unaligned(nnlib, oracle_lib, layout):
     case = _case(SHAPES[0], layout)
