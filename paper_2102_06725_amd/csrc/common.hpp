@@ -44,6 +44,26 @@ __device__ __forceinline__ f32x16 mfma32<BFloat>(u32x4 a, u32x4 b, f32x16 c) {
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// D += A * B on a 16x16 output tile with a 32-deep reduction
+// (v_mfma_f32_16x16x32_{f16,bf16}).  Each lane supplies 8 consecutive
+// reduction elements (8 * (lane / 16) on) of row lane % 16 of A and of column
+// lane % 16 of B.  Result: lane holds column lane % 16, rows
+// 4 * (lane / 16) + i for i = 0..3.
+template <class T>
+__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c);
+
+template <>
+__device__ __forceinline__ f32x4 mfma16<Half>(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
+                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+template <>
+__device__ __forceinline__ f32x4 mfma16<BFloat>(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 // fp32 -> 16-bit storage, round to nearest even, overflow to +-inf.
 template <class T>
 __device__ __forceinline__ uint32_t to16(float v);

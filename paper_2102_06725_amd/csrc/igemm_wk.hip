@@ -26,30 +26,12 @@
 
 namespace nnconv {
 
-namespace wk {
-
-template <class T>
-__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c);
-template <>
-__device__ __forceinline__ f32x4 mfma16<Half>(u32x4 a, u32x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
-                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ f32x4 mfma16<BFloat>(u32x4 a, u32x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-}  // namespace wk
-
 // BM pixels x BN channels per tile, NW waves, LDS ring of DEPTH steps per
 // wave.  PAD: some (row, tap) pairs fall outside the A image.  MIX: cr is not
 // a multiple of 32, so the four 8-channel chunks of a step may belong to
 // different taps, decoded per lane.
 template <class T, int BM, int BN, int NW, int DEPTH, bool PAD, bool MIX>
 __global__ __launch_bounds__(NW * 64) void igemm_wk_kernel(const TNParams P) {
-    using namespace wk;
     constexpr int FM = BM / 16, FN = BN / 16;  // 16x16 blocks; also loads per step
     constexpr int LOADS = FM + FN;
     constexpr int STEP = (BM + BN) * 64;       // LDS bytes of a step
