@@ -39,15 +39,19 @@
  *   - Fast (matrix-core) paths need 16-byte aligned pointers and Cg, Kg that
  *     are multiples of 8, or one group: other channel counts are then padded
  *     with zero channels in the workspace (operands that are copied for it
- *     may have any alignment).  Other valid shapes run on slower direct
- *     kernels with identical semantics.
+ *     may have any alignment) where that is the faster way.  Other valid
+ *     shapes, and layers of a few channels that padding would slow down, run
+ *     on direct kernels with identical semantics.
  *   - Depthwise convolution (groups == c == k, one channel per group, the
  *     MobileNet / EfficientNet layers trained with the paper's framework)
  *     with c a multiple of 8, a square 3x3, 5x5 or 7x7 filter and 16-byte
- *     aligned activations runs on dedicated kernels (stride 1 from about one
- *     workgroup per compute unit up on the matrix cores, with diagonal weight
- *     matrices; the rest on the vector ALUs); w and dw are [K][R][S] in both
- *     layouts (one channel per filter).
+ *     aligned activations runs on dedicated kernels: stride 1 without
+ *     dilation on the matrix cores, with diagonal weight matrices, where an
+ *     estimate of both kernels' times says so (large enough grids and well
+ *     filled tiles; forward and backward-data of 3x3 filters only in bf16 with
+ *     outputs 9 to 16 wide; backward-weight of 3x3 filters up to 16 wide and
+ *     of 5x5 ones, from 96 workgroups up), the rest on the vector ALUs.  w and
+ *     dw are [K][R][S] in both layouts (one channel per filter).
  *   - Grouped convolution with m = C/groups = K/groups channels per group,
  *     m < 64 dividing 64 and c a multiple of 64 (e.g. 32 groups of 4-32
  *     channels) runs as groups of 64 channels with block-diagonal weights on

@@ -77,8 +77,9 @@ bool fast_shape(const Geom &G) {
     return true;
 }
 
-// Depthwise convolution on its vector-ALU kernels: one input and one output
-// channel per group, 8-channel vectors, square 3x3 / 5x5 / 7x7 filters.
+// Depthwise convolution on its own kernels (matrix cores or vector ALUs): one
+// input and one output channel per group, 8-channel vectors, square 3x3 / 5x5 /
+// 7x7 filters.
 bool dw_shape(const Geom &G) {
     if (!(G.g == G.c && G.k == G.c && G.c % 8 == 0 && dw_supported((int)G.r, (int)G.s)))
         return false;

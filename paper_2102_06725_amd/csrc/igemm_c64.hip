@@ -61,9 +61,13 @@ __device__ __forceinline__ int slot(int r, int c) {
 // 8 bytes per lane straight from the accumulators, the shared output stage
 // (whole lines, streaming) and the smaller tiles' occupancy took 40 -> 240 and
 // 240 -> 40 1x1 over 128 28x28 images from 25-31 to 20 us a pass (56 MB: 11 us
-// at the copy rate), 16 -> 96 over 128 112x112 from 154 to 82.
+// at the copy rate), 16 -> 96 over 128 112x112 from 154 to 76.
+//
+// PART: ordinary stores, for strided backward-data of groups that share cache
+// lines: a streaming store of a part of a line costs a whole one (32 groups of
+// 24, 1x1 stride 2, 62 images of 19x77: 160 us against 71).
 template <class T, int BM, int BN, int WM, int WN, int BKC, int STAGES, bool PAD, bool DIAG,
-          bool RING, int OCC, bool MIX = false>
+          bool RING, int OCC, bool MIX = false, bool PART = false>
 __global__ __launch_bounds__(WM * WN * 64, OCC)
 void igemm_c64_kernel(const TNParams P) {
     using namespace c64;
@@ -413,7 +417,7 @@ void igemm_c64_kernel(const TNParams P) {
     }
 
     static_assert(BM * BN / 8 <= LDS_SLOTS, "C tile must fit in LDS");
-    store_tile<T, BM, BN, WM, WN, FM, FN, MIX>(acc, &lds[0], P, F, m0, n0, g);
+    store_tile<T, BM, BN, WM, WN, FM, FN, PART>(acc, &lds[0], P, F, m0, n0, g);
 }
 
 template <class T, int BM, int BN, int WM, int WN, int BKC, int STAGES, bool DIAG = false,
@@ -429,6 +433,17 @@ static hipError_t launch_c64_cfg(TNParams &p, bool pad, hipStream_t st) {
     }
     if (nb <= 0) return hipSuccess;
     if (nb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if constexpr (MIX) {
+        if (p.oj_mul > 1 && p.groups > 1 && p.o_cg_ofs % 64 != 0) {
+            if (pad)
+                hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, true, DIAG, RING, OCC, true, true>),
+                                   dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p);
+            else
+                hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, false, DIAG, RING, OCC, true, true>),
+                                   dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p);
+            return hipGetLastError();
+        }
+    }
     if (pad)
         hipLaunchKernelGGL((igemm_c64_kernel<T, BM, BN, WM, WN, BKC, STAGES, true, DIAG, RING, OCC, MIX>),
                            dim3((uint32_t)nb), dim3(WM * WN * 64), 0, st, p);

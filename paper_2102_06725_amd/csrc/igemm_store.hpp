@@ -15,7 +15,8 @@ namespace nnconv {
 // pixel l32 of each 32-pixel block and, of each 32-channel block, channels
 // 8*e + 4*khalf + {0..3} (e = 0..3).  `lds` must hold BM * BN / 8 chunks and
 // no other wave may still read it (the first barrier waits for that).
-template <class T, int BM, int BN, int WM, int WN, int FM, int FN, bool MIX = false>
+// PART: ordinary stores, for rows that are parts of cache lines.
+template <class T, int BM, int BN, int WM, int WN, int FM, int FN, bool PART = false>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *lds,
                                            const TNParams &P, const TNPhase &F, int m0, int n0,
                                            int g) {
@@ -52,10 +53,6 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *l
     barrier_lds();
     uint16_t *out = (uint16_t *)P.out;
     constexpr int ROWS_PER_PASS = NW * 64 / CPR;
-    // strided backward-data of groups that share cache lines: a streaming store
-    // of a part of a line costs a whole one (32 groups of 24, 1x1 stride 2, 62
-    // images of 19x77: 160 us against 71)
-    const bool part = MIX && P.oj_mul > 1 && P.groups > 1 && P.o_cg_ofs % 64 != 0;
 #pragma unroll 4
     for (int r = tid / CPR; r < BM; r += ROWS_PER_PASS) {
         const int c = tid % CPR;
@@ -73,12 +70,9 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[FN][FM], u32x4 *l
         // streaming store: the output is not read again by this pass, so it
         // should not displace operand lines in L2
         const u32x4 v = lds[r * CPR + (c ^ (r & CSW))];
-        if (part) {
-            // the fences keep the compiler from making one store of the two
-            asm volatile("" ::: "memory");
+        if constexpr (PART)
             *(u32x4 *)(out + obase + ch) = v;
-            asm volatile("" ::: "memory");
-        } else
+        else
             __builtin_nontemporal_store(v, (u32x4 *)(out + obase + ch));
     }
 }

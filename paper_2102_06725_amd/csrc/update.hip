@@ -62,10 +62,19 @@ constexpr int SGD_VECS = 2;
 // bytes per parameter, all but the 16-bit copy (the next forward's weights)
 // not touched again before the next step, so they stream past the caches.
 // The data loads are issued before the flag and the scale are waited for.
-// 23.45 M parameters: 98.6 us with ordinary accesses, one vector per thread and
-// the loads behind the flag (5.2 TB/s); 95.7 with two vectors ahead of it, 91.9
-// with streaming loads too, 78.4 (6.6 TB/s) with streaming fp32 stores as well
-// (83.3 when the 16-bit copy streams too).
+// 23.45 M parameters, update and loss scaler in turn: 98.6 us with ordinary
+// accesses, one vector per thread and the loads behind the flag (5.2 TB/s); 95.7
+// with two vectors ahead of it, 91.9 with streaming loads too, 78.4 (6.6 TB/s)
+// with streaming fp32 stores as well (83.3 when the 16-bit copy streams too).
+// What they win depends on what the last-level cache holds; ordinary -> this, us, by
+// parameters:
+//                          3 M           12 M          23.45 M       60 M
+//   back to back           9.2 -> 10.7   38.5 -> 42.4  74.2 -> 78.9  247 -> 199
+//   after 1 GiB of writes  19.4 -> 15.0  61.1 -> 48.1  111 -> 90     259 -> 235
+//   gradients just written 15.8 -> 14.0  46.8 -> 43.1  85.0 -> 78.7  252 -> 196
+//   after 128 MB           12.1 -> 14.6  40.8 -> 43.9  82.6 -> 78.2  252 -> 196
+// Neither is faster in every state; between two updates of one array a training
+// step writes its gradients and more than the cache holds.
 template <int OUT, bool VEC>
 __global__ __launch_bounds__(256) void sgd_update_kernel(int64_t count, float *__restrict__ master,
                                                          float *__restrict__ mom,
